@@ -124,9 +124,11 @@ def _table_rows(c):
     return [max(1, int(round(lo * (hi / lo) ** ((k / (nt - 1)) ** c["bend"])))) for k in range(nt)]
 
 
-def _cdf(n, s, device=DEV):
-    p = torch.arange(1, n + 1, dtype=torch.float64, device=device).pow_(-s).cumsum_(0)
-    return p.div_(p[-1].clone())
+def _weights(n, s, device=DEV):
+    """Running sums of r ** -s over the ranks r = 1..n, in whole numbers: the same from run to run, in whatever order
+    the GPU adds them."""
+    p = torch.arange(1, n + 1, dtype=torch.float64, device=device).pow_(-s)
+    return (p * 2.0 ** 44).to(torch.int64).clamp_(min=1).cumsum_(0)
 
 
 def _lookups(c, seed):
@@ -157,7 +159,8 @@ def _lookups(c, seed):
         perm = torch.randperm(n, generator=gen, device=DEV)
         where = ids.view(T * B, nt)[:, t] if one else torch.nonzero(table_of == t).reshape(-1)
         u = torch.rand(where.shape[0], dtype=torch.float64, generator=popularity, device=DEV)
-        rank = torch.searchsorted(_cdf(n, c["zipf"]), u, right=True).clamp_(max=n - 1)
+        upto = _weights(n, c["zipf"])
+        rank = torch.searchsorted(upto, (u * upto[-1]).to(torch.int64), right=True).clamp_(max=n - 1)
         got = perm[rank] + base
         if one:
             where.copy_(got)
