@@ -223,15 +223,19 @@ __global__ __launch_bounds__(kBlock) void plan_hist_kernel(const uint64_t* __res
                                                            int Lcap, int lds_gaps,
                                                            uint32_t* __restrict__ H, uint32_t* __restrict__ ucount,
                                                            uint32_t* __restrict__ first_use, int chunk,
-                                                           uint32_t* __restrict__ V) {
+                                                           uint32_t* __restrict__ V, int v_in_lds) {
     const uint32_t M = *n_pairs;
     const uint32_t per_block = (M + gridDim.x - 1) / gridDim.x;
     if ((uint64_t)blockIdx.x * per_block >= M) return;
-    extern __shared__ uint32_t lds[];   // [T] unique counts, [T] first uses, then [lds_gaps][T] histogram rows
+    // [T] unique counts, [T] first uses, in a chunk [T + 1] next uses of the carried rows (where they fit), then
+    // [lds_gaps][T] histogram rows
+    extern __shared__ uint32_t lds[];
+    const int v_cells = v_in_lds ? T + 1 : 0;
     uint32_t* lds_u = lds;
     uint32_t* lds_f = lds + T;
-    uint32_t* lds_h = lds + 2 * T;
-    const int cells = (2 + lds_gaps) * T;
+    uint32_t* v_count = v_in_lds ? lds + 2 * T : V;
+    uint32_t* lds_h = lds + 2 * T + v_cells;
+    const int cells = (2 + lds_gaps) * T + v_cells;
     for (int i = threadIdx.x; i < cells; i += kBlock) lds[i] = 0;
     __syncthreads();
     const uint64_t imask = (uint64_t(1) << ib) - 1;
@@ -254,13 +258,27 @@ __global__ __launch_bounds__(kBlock) void plan_hist_kernel(const uint64_t* __res
             if (q0 + (uint64_t)r * kBlock >= end) break;
             const uint64_t a = key[r];
             const uint32_t i = (uint32_t)(a & imask);
-            atomicAdd(&lds_u[i], 1u);
-            if ((prev[r] >> ib) != (a >> ib)) atomicAdd(&lds_f[i], 1u);   // the id's first batch
             const uint32_t gap = (a >> ib) == (next[r] >> ib) ? (uint32_t)((next[r] & imask) - i) : kGapInf;
-            if (chunk && i == 0) {      // a carried resident stays until its next use, whatever the lookahead
-                atomicAdd(&V[gap == kGapInf ? (uint32_t)T : gap], 1u);
+            if (chunk && i == 0) {
+                // A carried resident stays until its next use, whatever the lookahead.  Nearly all of them have none in
+                // the chunk and would meet on one counter (and on batch 0's): the lanes that hold such a pair count
+                // themselves with one addition (1.4 M pairs with 0.35 M carried rows: 413 us with an addition to memory
+                // each, 25 us this way).
+                const uint64_t idle = __ballot(gap == kGapInf);
+                if (gap != kGapInf) {
+                    atomicAdd(&v_count[gap], 1u);
+                    atomicAdd(&lds_u[0], 1u);
+                    atomicAdd(&lds_f[0], 1u);
+                } else if ((idle & lanemask_lt()) == 0) {
+                    const uint32_t lanes = (uint32_t)__popcll(idle);
+                    atomicAdd(&v_count[T], lanes);
+                    atomicAdd(&lds_u[0], lanes);
+                    atomicAdd(&lds_f[0], lanes);
+                }
                 continue;
             }
+            atomicAdd(&lds_u[i], 1u);
+            if ((prev[r] >> ib) != (a >> ib)) atomicAdd(&lds_f[i], 1u);   // the id's first batch
             if (gap >= 2u && gap < (uint32_t)Lcap) {
                 if (gap < 2u + (uint32_t)lds_gaps) atomicAdd(&lds_h[(gap - 2u) * T + i], 1u);
                 else atomicAdd(&H[(size_t)gap * T + i], 1u);
@@ -272,6 +290,9 @@ __global__ __launch_bounds__(kBlock) void plan_hist_kernel(const uint64_t* __res
         if (lds_u[i]) atomicAdd(&ucount[i], lds_u[i]);
         if (lds_f[i]) atomicAdd(&first_use[i], lds_f[i]);
     }
+    if (v_in_lds)
+        for (int i = threadIdx.x; i <= T; i += kBlock)
+            if (v_count[i]) atomicAdd(&V[i], v_count[i]);
     for (int x = threadIdx.x; x < lds_gaps * T; x += kBlock)
         if (lds_h[x]) atomicAdd(&H[(size_t)2 * T + x], lds_h[x]);      // row (2 + x / T), column x % T
 }
@@ -1110,15 +1131,21 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
     // H, ucount, first_use, V, vcover and peak lie one after the other in the workspace: one clear for all of them
     BP_HIP(hipMemsetAsync(w.H, 0, (size_t)((char*)(w.peak + (Lcap + 2)) - (char*)w.H), stream));
     {
-        int lds_gaps = (int)((48 * 1024 / 4 - 2 * T) / T);              // histogram rows that fit in 48 KiB next to 2 x [T]
+        const int v_cells = chunk && 3 * T + 1 <= 48 * 1024 / 4 ? T + 1 : 0;
+        int lds_gaps = (int)((48 * 1024 / 4 - 2 * T - v_cells) / T);    // histogram rows that fit in 48 KiB next to the rest
         if (lds_gaps > Lcap - 2) lds_gaps = Lcap - 2;
         if (lds_gaps < 0) lds_gaps = 0;
-        int64_t blocks = ceil_div(N, 4 * 32 * 1024);                     // >= 32 Ki pairs per workgroup amortise the flush
-        if (blocks > 1024) blocks = 1024;                                // (about one lookup in four starts a pair)
+        const size_t lds_cells = (size_t)(2 + lds_gaps) * T + v_cells;
+        // A workgroup's share of the pairs (about one lookup in four starts one) is large enough to amortise clearing
+        // and flushing its counters: 32 Ki pairs beside a full 48 KiB of them, fewer where the counters are few (a
+        // trace of 50 small batches: one workgroup took 55 us for 40 K pairs).
+        const int64_t share = std::min<int64_t>(32 * 1024, std::max<int64_t>(1024, 2 * (int64_t)lds_cells));
+        int64_t blocks = ceil_div(N, 4 * share);
+        if (blocks > 1024) blocks = 1024;
         if (blocks < 1) blocks = 1;
         BP_LAUNCH(K_PLAN_HIST, plan_hist_kernel, dim3((unsigned)blocks), dim3(kBlock),
-                  sizeof(uint32_t) * (size_t)(2 + lds_gaps) * T, stream, (const uint64_t*)ukey, n_pairs_dev, ib, T, Lcap,
-                  lds_gaps, w.H, w.ucount, w.first_use, (int)chunk, w.V);
+                  sizeof(uint32_t) * lds_cells, stream, (const uint64_t*)ukey, n_pairs_dev, ib, T, Lcap,
+                  lds_gaps, w.H, w.ucount, w.first_use, (int)chunk, w.V, (int)(v_cells > 0));
     }
     const uint32_t* vcover = nullptr;
     if (chunk) {

@@ -952,6 +952,19 @@ def test_plan_chunked_medium(bp):
         assert state.n_resident == whole.prefetch_off[b] - whole.evict_off[b]
 
 
+@pytest.mark.parametrize("n_emit", [4085, 4110])
+def test_plan_chunked_many_batches(bp, n_emit):
+    """Two chunks of about 4,096 batches: the next uses of the carried rows are counted in LDS up to there, in memory
+    beyond."""
+    say(f"plan chunked, {n_emit} batches a chunk")
+    rng = np.random.default_rng(n_emit)
+    T = 2 * n_emit
+    off = np.zeros(T + 1, dtype=np.int64)
+    off[1:] = np.cumsum(rng.integers(0, 5, size=T))
+    ids = np.minimum(rng.zipf(1.3, size=int(off[-1])) - 1, 299).astype(np.int64)
+    run_chunked(bp, ids, off, 300, 3, 400, n_emit)
+
+
 @pytest.mark.parametrize("optimizer,dtype,bag_max,capacity,lookahead,n_emit", [
     ("adagrad", "f32", 1, 4096, 6, 7), ("sgd", "f32", 5, 2200, 8, 4), ("adagrad_rowwise", "bf16", 1, 1300, 5, 1),
     ("adagrad", "bf16", 3, 3000, 1, 6),
