@@ -225,8 +225,8 @@ int device_scan(In in, Out out, int64_t n, T* partials, Op op, T identity, hipSt
 // ---------------------------------------------------------------------------------------------
 // stable LSD radix sort of (key, 32-bit value) pairs, RB = 8 or 9 bits per pass
 //   upsweep    per-tile digit histogram              -> counts[digit][tile]
-//   scan       exclusive scan of counts (digit-major) -> global base of every (digit, tile)
-//   downsweep  per-tile stable ranking in LDS, coalesced scatter
+//   scan       every digit's counts by one workgroup  -> the digit's elements before every tile, and its total
+//   downsweep  per-tile stable ranking in LDS, coalesced scatter; a tile adds the totals of the lower digits itself
 // Ranking inside a tile: each wavefront owns a contiguous 64*IPT stretch, lane l holds elements
 // j*64+l; for every j the lanes that share a digit find each other with ballots (one per digit bit),
 // rank = running per-wave digit count + number of lower lanes among the peers.
@@ -309,28 +309,88 @@ __global__ __launch_bounds__(kSortBlock) void sort_upsweep_kernel(Src src, uint3
     for (int d = threadIdx.x; d < RADIX; d += kSortBlock) counts[(size_t)d * ntiles + tile] = hist[d];
 }
 
+// Digit d's counts, one per tile, lie side by side: one workgroup per digit turns them into the counts of the tiles
+// before (from `in` to `out`, which may be the same array) and leaves their sum in totals[d].  Nothing here meets
+// another workgroup, so this is one launch where a scan over all digits and tiles at once takes three.  A round takes
+// BLOCK * SCAN_ROUNDS counts, the next round's loads out before this one's sums; it is bound by the launch where the
+// tiles are few (25 tiles: 3 us for 10.5 us of reduce, spine and apply) and by memory where they are many (20,800
+// tiles and 512 digits: 20 us for 33 us).
+template <int BLOCK, int SCAN_ROUNDS>
+__global__ __launch_bounds__(BLOCK) void sort_digit_scan_kernel(const uint32_t* in, uint32_t* out, uint32_t ntiles,
+                                                                uint32_t* __restrict__ totals) {
+    constexpr int WAVES = BLOCK / kWave;
+    __shared__ uint32_t wave_tot[2][WAVES];
+    const int w = threadIdx.x / kWave, lane = lane_id();
+    const size_t row = (size_t)blockIdx.x * ntiles;
+    const uint32_t mine = w * (kWave * SCAN_ROUNDS) + lane;
+    uint32_t v[SCAN_ROUNDS], carry = 0;
+#pragma unroll
+    for (int r = 0; r < SCAN_ROUNDS; ++r) v[r] = mine + r * kWave < ntiles ? in[row + mine + r * kWave] : 0u;
+    for (uint32_t base = 0, turn = 0; base < ntiles; base += BLOCK * SCAN_ROUNDS, turn ^= 1u) {
+        uint32_t next[SCAN_ROUNDS];
+        uint32_t sum = 0;
+#pragma unroll
+        for (int r = 0; r < SCAN_ROUNDS; ++r) {
+            const uint32_t i = base + BLOCK * SCAN_ROUNDS + mine + r * kWave;
+            next[r] = i < ntiles ? in[row + i] : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < SCAN_ROUNDS; ++r) sum += v[r];
+        sum = wave_reduce(sum, AddOp());
+        if (lane == 0) wave_tot[turn][w] = sum;          // two sets in turn: one barrier a round
+        __syncthreads();
+        uint32_t run = carry;
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) {
+            const uint32_t t = wave_tot[turn][k];
+            if (k < w) run += t;
+            carry += t;
+        }
+#pragma unroll
+        for (int r = 0; r < SCAN_ROUNDS; ++r) {
+            const uint32_t i = base + mine + r * kWave;
+            const uint32_t inc = wave_inclusive_scan(v[r], AddOp());
+            if (i < ntiles) out[row + i] = run + inc - v[r];
+            run += __shfl(inc, kWave - 1, kWave);
+            v[r] = next[r];
+        }
+    }
+    if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+}
+
+// What hides the loads' and the LDS's latency here is the number of workgroups a CU holds: 4 of keys alone (39 KB of LDS
+// each, 128 VGPRs), 3 of keys and values (2 at 9 bits), all at 4096 64-bit keys.  (With 32-bit wave counters and the
+// digits' starts beside them it was 3 of keys alone; 85 M words: 530 -> 478 us where the keys are made on the way, 314
+// -> 307 us from plain arrays.)
 template <typename K, int IPT, int RB, typename Src, bool VALS>
-__global__ __launch_bounds__(kSortBlock) void sort_downsweep_kernel(Src src, K* __restrict__ kout,
+__global__ __launch_bounds__(kSortBlock, !VALS ? 4 : RB > 8 ? 2 : 3) void sort_downsweep_kernel(Src src, K* __restrict__ kout,
                                                                     uint32_t* __restrict__ vout, uint32_t n, int shift,
-                                                                    uint32_t mask, const uint32_t* __restrict__ bases,
-                                                                    uint32_t ntiles) {
+                                                                    uint32_t mask, const uint32_t* __restrict__ before,
+                                                                    const uint32_t* __restrict__ totals, uint32_t ntiles) {
     constexpr int RADIX = 1 << RB;
     constexpr int DPT = RADIX / kSortBlock;    // consecutive digits owned by a thread in the digit scan (1 or 2)
     constexpr int WAVES = kSortBlock / kWave;
     constexpr int TILE = kSortBlock * IPT;
     constexpr int WTILE = kWave * IPT;
+    static_assert(TILE < 65536, "places in a tile fit 16 bits");
     static_assert(RADIX % kSortBlock == 0, "radix must be a multiple of the workgroup size");
-    __shared__ uint32_t wcnt[WAVES][RADIX];    // per-wave digit counts, then per-wave exclusive offsets
-    __shared__ uint32_t dstart[RADIX];         // tile-local start of each digit
-    __shared__ uint32_t gbase[RADIX];          // global base of the digit for this tile, minus dstart
-    __shared__ uint32_t wave_tot[WAVES];
+    __shared__ __attribute__((aligned(4))) uint16_t wcnt[WAVES][RADIX];    // per-wave digit counts, then where the wave's elements start in the tile
+    __shared__ uint32_t gbase[RADIX];          // global base of the digit for this tile, minus its start in the tile
+    __shared__ uint64_t wave_tot[WAVES];
     __shared__ K skeys[TILE];
     __shared__ uint32_t svals[VALS ? TILE : 1];
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
     const uint32_t tile = sort_tile_of_block(ntiles);
     if (tile >= ntiles) return;
-    for (int d = tid; d < WAVES * RADIX; d += kSortBlock) (&wcnt[0][0])[d] = 0;
+    for (int d = tid; d < WAVES * RADIX / 2; d += kSortBlock) reinterpret_cast<uint32_t*>(&wcnt[0][0])[d] = 0;
+    // asked for now, used after the ranking
+    uint32_t all[DPT], earlier[DPT];           // elements of the thread's digits: in all tiles, in the tiles before
+#pragma unroll
+    for (int k = 0; k < DPT; ++k) {
+        all[k] = totals[tid * DPT + k];
+        earlier[k] = before[(size_t)(tid * DPT + k) * ntiles + tile];
+    }
     __syncthreads();
 
     const uint32_t tile_base = tile * TILE;
@@ -365,38 +425,41 @@ __global__ __launch_bounds__(kSortBlock) void sort_downsweep_kernel(Src src, K* 
             const uint64_t m = __ballot(bit);
             peers &= bit ? m : ~m;
         }
-        const uint32_t before = wcnt[w][d];
-        rank[j] = before + (uint32_t)__popcll(peers & lt);
+        const uint32_t seen = wcnt[w][d];
+        rank[j] = seen + (uint32_t)__popcll(peers & lt);
         __builtin_amdgcn_wave_barrier();
-        if (valid && (peers & lt) == 0) wcnt[w][d] = before + (uint32_t)__popcll(peers);   // lowest peer lane
+        if (valid && (peers & lt) == 0) wcnt[w][d] = (uint16_t)(seen + (uint32_t)__popcll(peers));   // lowest peer lane
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
 
     {   // thread tid owns digits tid*DPT .. tid*DPT+DPT-1: offsets of the waves inside each digit, then digit starts
-        uint32_t tot[DPT];
-        uint32_t sum = 0;
+        // (one scan for both the tile's own digit counts, low word, and the digits' totals, high word)
+        uint32_t tot[DPT], start[DPT][WAVES];
+        uint64_t sum = 0;
 #pragma unroll
         for (int k = 0; k < DPT; ++k) {
             const int d = tid * DPT + k;
             uint32_t run = 0;
 #pragma unroll
             for (int i = 0; i < WAVES; ++i) {
-                uint32_t c = wcnt[i][d];
-                wcnt[i][d] = run;
-                run += c;
+                start[k][i] = run;
+                run += wcnt[i][d];
             }
             tot[k] = run;
-            sum += run;
+            sum += ((uint64_t)all[k] << 32) | run;
         }
-        uint32_t exc, inc, total;
-        block_scan<kSortBlock>(sum, AddOp(), 0u, wave_tot, &exc, &inc, &total);
+        uint64_t exc2, inc2, total2;
+        block_scan<kSortBlock>(sum, AddOp(), uint64_t(0), wave_tot, &exc2, &inc2, &total2);
+        uint32_t exc = (uint32_t)exc2, below = (uint32_t)(exc2 >> 32);
 #pragma unroll
         for (int k = 0; k < DPT; ++k) {
             const int d = tid * DPT + k;
-            dstart[d] = exc;
-            gbase[d] = bases[(size_t)d * ntiles + tile] - exc;
+#pragma unroll
+            for (int i = 0; i < WAVES; ++i) wcnt[i][d] = (uint16_t)(exc + start[k][i]);
+            gbase[d] = below + earlier[k] - exc;
             exc += tot[k];
+            below += all[k];
         }
     }
     __syncthreads();
@@ -405,7 +468,7 @@ __global__ __launch_bounds__(kSortBlock) void sort_downsweep_kernel(Src src, K* 
     for (int j = 0; j < IPT; ++j) {
         if (wbase + j * kWave + lane < n) {
             const uint32_t d = (uint32_t)(key[j] >> shift) & mask;
-            const uint32_t pos = dstart[d] + wcnt[w][d] + rank[j];
+            const uint32_t pos = wcnt[w][d] + rank[j];
             skeys[pos] = key[j];
             if constexpr (VALS) svals[pos] = val[j];
         }
@@ -425,10 +488,6 @@ __global__ __launch_bounds__(kSortBlock) void sort_downsweep_kernel(Src src, K* 
     }
 }
 
-struct LoadU32 {
-    const uint32_t* p;
-    __device__ __forceinline__ uint32_t operator()(int64_t i) const { return p[i]; }
-};
 struct StoreExclusiveU32 {
     uint32_t* p;
     __device__ __forceinline__ void operator()(int64_t i, uint32_t exc, uint32_t) const { p[i] = exc; }
@@ -440,8 +499,7 @@ inline uint32_t sort_num_tiles(int64_t n) { return (uint32_t)(n > 0 ? ceil_div(n
 // uint32 words of temporary storage for radix_sort_pairs<.., IPT> of n elements
 template <int IPT>
 inline size_t sort_temp_words(int64_t n) {
-    size_t counts = (size_t)kMaxRadix * sort_num_tiles<IPT>(n);
-    return counts + 64 + scan_partials((int64_t)counts) + 64;
+    return (((size_t)kMaxRadix * sort_num_tiles<IPT>(n) + 63) & ~size_t(63)) + kMaxRadix;
 }
 
 // One pass.  The histogram reads `up`, the scatter reads `src`: the same elements, but a source that has to fetch
@@ -450,27 +508,32 @@ inline size_t sort_temp_words(int64_t n) {
 // read the same elements anyway; NULL: the upsweep makes it.
 template <typename K, int IPT, int RB, typename Up, typename Src, bool VALS>
 int radix_sort_pass(const Up& up, const Src& src, K* kout, uint32_t* vout, int64_t n, int bit, int nb, uint32_t* counts,
-                    uint32_t* partials, uint32_t ntiles, hipStream_t stream, const uint32_t* ready) {
-    const int64_t ncounts = (int64_t)(1 << RB) * ntiles;
+                    uint32_t* totals, uint32_t ntiles, hipStream_t stream, const uint32_t* ready) {
     const uint32_t mask = (1u << nb) - 1u;
     if (!ready)
         BP_LAUNCH(K_SORT_UPSWEEP, (sort_upsweep_kernel<K, IPT, RB, Up>), dim3(sort_grid(ntiles)), dim3(kSortBlock), 0, stream,
                   up, (uint32_t)n, bit, mask, counts, ntiles);
-    BP_TRY((device_scan<uint32_t, AddOp, LoadU32, StoreExclusiveU32>(LoadU32{ready ? ready : counts}, StoreExclusiveU32{counts},
-                                                                     ncounts, partials, AddOp(), 0u, stream)));
+    // few tiles: one round of a small workgroup; many: large workgroups, which keep their number of rounds down
+    const uint32_t* digit_counts = ready ? ready : counts;
+    if (ntiles <= 4 * 256)
+        BP_LAUNCH(K_SORT_SCAN, (sort_digit_scan_kernel<256, 4>), dim3(1 << RB), dim3(256), 0, stream, digit_counts, counts, ntiles,
+                  totals);
+    else
+        BP_LAUNCH(K_SORT_SCAN, (sort_digit_scan_kernel<1024, 4>), dim3(1 << RB), dim3(1024), 0, stream, digit_counts, counts,
+                  ntiles, totals);
     BP_LAUNCH(K_SORT_DOWNSWEEP, (sort_downsweep_kernel<K, IPT, RB, Src, VALS>), dim3(sort_grid(ntiles)), dim3(kSortBlock), 0,
-              stream, src, kout, vout, (uint32_t)n, bit, mask, (const uint32_t*)counts, ntiles);
+              stream, src, kout, vout, (uint32_t)n, bit, mask, (const uint32_t*)counts, (const uint32_t*)totals, ntiles);
     return BP_OK;
 }
 
 template <typename K, int IPT, typename Up, typename Src, bool VALS>
 int radix_sort_one_pass(const Up& up, const Src& src, K* kout, uint32_t* vout, int64_t n, int bit, int nb,
-                        uint32_t* counts, uint32_t* partials, uint32_t ntiles, hipStream_t stream,
+                        uint32_t* counts, uint32_t* totals, uint32_t ntiles, hipStream_t stream,
                         const uint32_t* ready = nullptr) {
     if (nb > 8)
-        return radix_sort_pass<K, IPT, 9, Up, Src, VALS>(up, src, kout, vout, n, bit, nb, counts, partials, ntiles, stream,
+        return radix_sort_pass<K, IPT, 9, Up, Src, VALS>(up, src, kout, vout, n, bit, nb, counts, totals, ntiles, stream,
                                                          ready);
-    return radix_sort_pass<K, IPT, 8, Up, Src, VALS>(up, src, kout, vout, n, bit, nb, counts, partials, ntiles, stream, ready);
+    return radix_sort_pass<K, IPT, 8, Up, Src, VALS>(up, src, kout, vout, n, bit, nb, counts, totals, ntiles, stream, ready);
 }
 
 // Bits the first pass of a sort over [begin_bit, end_bit) takes (the passes share the bits evenly).
@@ -494,7 +557,7 @@ int radix_sort_from(const Up& first_up, const Src& first, K* const kbuf[2], uint
     if (n <= 0 || end_bit <= begin_bit) return BP_OK;
     const uint32_t ntiles = sort_num_tiles<IPT>(n);
     uint32_t* counts = temp;
-    uint32_t* partials = temp + (((size_t)kMaxRadix * ntiles + 63) & ~size_t(63));
+    uint32_t* totals = temp + (((size_t)kMaxRadix * ntiles + 63) & ~size_t(63));
     const int total = end_bit - begin_bit;
     const int passes = (total + kMaxRadixBits - 1) / kMaxRadixBits;
     int bit = begin_bit;
@@ -504,12 +567,12 @@ int radix_sort_from(const Up& first_up, const Src& first, K* const kbuf[2], uint
         const int out = p & 1;
         if (p == 0) {
             BP_TRY((radix_sort_one_pass<K, IPT, Up, Src, VALS>(first_up, first, kbuf[out], VALS ? vbuf[out] : nullptr, n, bit,
-                                                               nb, counts, partials, ntiles, stream, first_counts)));
+                                                               nb, counts, totals, ntiles, stream, first_counts)));
         } else {
             const SortArrays<K> in{kbuf[out ^ 1], VALS ? vbuf[out ^ 1] : nullptr};
             BP_TRY((radix_sort_one_pass<K, IPT, SortArrays<K>, SortArrays<K>, VALS>(in, in, kbuf[out],
                                                                                     VALS ? vbuf[out] : nullptr, n, bit, nb,
-                                                                                    counts, partials, ntiles, stream)));
+                                                                                    counts, totals, ntiles, stream)));
         }
         bit += nb;
         *result = out;

@@ -621,6 +621,22 @@ def test_plan_medium_multi_tile(bp):
     plan_both(bp, tr.ids, tr.iter_offsets, cfg.total_rows, 60, 10 ** 6)         # lookahead beyond the trace
 
 
+@pytest.mark.parametrize("n", [4095, 4097, 1024 * 4096, 1024 * 4096 + 1, 2 * 1024 * 4096 + 4097])
+def test_plan_sizes_around_the_sort_tiles(bp, n):
+    """Lookups around one tile of the sort, and around the number of tiles up to which a small workgroup scans a
+    digit's counts; beyond it a large workgroup takes them in rounds of 4,096."""
+    say(f"plan of {n} lookups")
+    rng = np.random.default_rng(n)
+    R = 200_003
+    off = np.array([0, n // 3, n // 3, n // 2, n], dtype=np.int64)
+    ids = (np.minimum(rng.zipf(1.3, size=n), R) * 7919 % R).astype(np.int64)
+    umax = max(len(np.unique(ids[off[i]:off[i + 1]])) for i in range(4))
+    got = bp.bp_oracle_plan(bp.make_config(R, umax + 7, 16, lookahead=3), dev(ids), off, grouping=True)
+    want = oracle.plan(ids, off, R, 3, umax + 7)
+    assert_plan_equal(got, want, n)
+    assert_grouping_valid(got, want, ids, off)
+
+
 @pytest.mark.parametrize("largest", [1, 2, 255, 256, 257, 4096, 4097])
 def test_plan_word_field_boundaries(bp, largest):
     """The place field of a lookup's word has as many bits as the largest batch needs: sizes at and around powers of
