@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "common.h"
@@ -66,17 +67,24 @@ __device__ __forceinline__ void block_scan(T x, Op op, T identity, T* wave_tot, 
 // ---------------------------------------------------------------------------------------------
 // device-wide scan:  out(i, exclusive_prefix_i, inclusive_prefix_i)  for value_i = in(i), i in [0, n)
 //   pass 1  per-tile reduction                   -> partials[tile]
-//   pass 2  one workgroup scans the partials in place (exclusive) and appends the grand total
+//   pass 2  one workgroup scans the partials in place (exclusive) and appends the grand total; left out where the
+//           tiles are few: every workgroup of pass 3 then adds up the partials before its own
 //   pass 3  per-tile scan seeded with its partial
-// A tile is kScanTile consecutive elements; each wavefront owns a contiguous stretch of it and takes it in
-// kScanRounds rounds of 64 consecutive elements (lane l holds element r*64 + l of the stretch), so loads coalesce
+// A tile is kScanBlock * ROUNDS consecutive elements; each wavefront owns a contiguous stretch of it and takes it in
+// ROUNDS rounds of 64 consecutive elements (lane l holds element r*64 + l of the stretch), so loads coalesce
 // and a round is scanned with lane shuffles alone; the workgroup meets at one barrier per tile.
 // Op must be associative and commutative (add, max).
 // ---------------------------------------------------------------------------------------------
 constexpr int kScanBlock = 256;
-constexpr int kScanRounds = 8;
-constexpr int kScanTile = kScanBlock * kScanRounds;
-constexpr int kScanWaveStretch = kWave * kScanRounds;
+// Rounds of a tile by the number of elements.  The rounds of pass 3 follow one another (what `out` fetches for one is
+// asked for after the stores of the one before), so small inputs are dealt to as many workgroups as they fill: 40 K
+// rows took 12.4 us on 20 workgroups of 8 rounds, 4.4 us on 160 of one.  Large ones take long tiles, which keep the
+// partials few.
+constexpr int64_t kScanSmall = int64_t(1) << 18, kScanMiddle = int64_t(1) << 21;
+inline int scan_rounds(int64_t n) { return n <= kScanSmall ? 1 : n <= kScanMiddle ? 4 : 8; }
+// Up to here pass 2 is left out: the partials are 8 KB at most, read from L2 by every workgroup at once, where the one
+// workgroup of pass 2 is a launch of its own (2.5 to 4 us, with the gaps on both sides).
+constexpr int64_t kScanFewTiles = 2048;
 
 template <typename T, typename Op>
 __device__ __forceinline__ T wave_reduce(T x, Op op) {
@@ -85,14 +93,14 @@ __device__ __forceinline__ T wave_reduce(T x, Op op) {
     return x;
 }
 
-template <typename T, typename Op, typename In>
+template <int ROUNDS, typename T, typename Op, typename In>
 __global__ __launch_bounds__(kScanBlock) void scan_reduce_kernel(In in, int64_t n, T* partials, Op op, T identity) {
     __shared__ T wave_tot[kScanBlock / kWave];
     const int w = threadIdx.x / kWave, lane = lane_id();
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + w * kScanWaveStretch + lane;
+    const int64_t base = (int64_t)blockIdx.x * (kScanBlock * ROUNDS) + w * (kWave * ROUNDS) + lane;
     T acc = identity;
 #pragma unroll
-    for (int r = 0; r < kScanRounds; ++r) {
+    for (int r = 0; r < ROUNDS; ++r) {
         const int64_t i = base + r * kWave;
         if (i < n) acc = op(acc, in(i));
     }
@@ -160,27 +168,50 @@ __global__ __launch_bounds__(1024) void scan_spine_kernel(T* partials, int64_t n
     if (threadIdx.x == 0) partials[nparts] = carry;
 }
 
-template <typename T, typename Op, typename In, typename Out>
-__global__ __launch_bounds__(kScanBlock) void scan_apply_kernel(In in, Out out, int64_t n, const T* partials, Op op,
-                                                                T identity) {
-    __shared__ T wave_tot[kScanBlock / kWave];
+// SPINE: pass 2 has run.  Without it, `partials` holds the bare sums of the tiles, the workgroup adds up those before
+// its own, and the last one writes the grand total behind them (where no other workgroup reads).
+template <int ROUNDS, bool SPINE, typename T, typename Op, typename In, typename Out>
+__global__ __launch_bounds__(kScanBlock) void scan_apply_kernel(In in, Out out, int64_t n, T* partials, Op op, T identity) {
+    constexpr int WAVES = kScanBlock / kWave;
+    __shared__ T wave_tot[WAVES];
+    __shared__ T wave_before[SPINE ? 1 : WAVES];
     const int w = threadIdx.x / kWave, lane = lane_id();
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + w * kScanWaveStretch + lane;
-    T v[kScanRounds];
+    const int64_t base = (int64_t)blockIdx.x * (kScanBlock * ROUNDS) + w * (kWave * ROUNDS) + lane;
+    T v[ROUNDS];
     T mine = identity;
 #pragma unroll
-    for (int r = 0; r < kScanRounds; ++r) {
+    for (int r = 0; r < ROUNDS; ++r) {
         const int64_t i = base + r * kWave;
         v[r] = i < n ? in(i) : identity;
-        mine = op(mine, v[r]);
     }
+    if constexpr (!SPINE) {
+        T before = identity;
+        for (uint32_t t = threadIdx.x; t < blockIdx.x; t += kScanBlock) before = op(before, partials[t]);
+        before = wave_reduce(before, op);
+        if (lane == 0) wave_before[w] = before;
+    }
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) mine = op(mine, v[r]);
     mine = wave_reduce(mine, op);
     if (lane == 0) wave_tot[w] = mine;
     __syncthreads();
-    T carry = partials[blockIdx.x];                       // everything before this wavefront's stretch
+    T carry;                                              // everything before this wavefront's stretch
+    if constexpr (SPINE) {
+        carry = partials[blockIdx.x];
+    } else {
+        carry = identity;
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) carry = op(carry, wave_before[k]);
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+            T total = carry;
+#pragma unroll
+            for (int k = 0; k < WAVES; ++k) total = op(total, wave_tot[k]);
+            partials[gridDim.x] = total;
+        }
+    }
     for (int k = 0; k < w; ++k) carry = op(carry, wave_tot[k]);
 #pragma unroll
-    for (int r = 0; r < kScanRounds; ++r) {
+    for (int r = 0; r < ROUNDS; ++r) {
         const int64_t i = base + r * kWave;
         const T inc = wave_inclusive_scan(v[r], op);
         T exc = __shfl_up(inc, 1, kWave);
@@ -190,36 +221,58 @@ __global__ __launch_bounds__(kScanBlock) void scan_apply_kernel(In in, Out out, 
     }
 }
 
-inline int64_t scan_num_tiles(int64_t n) { return n > 0 ? ceil_div(n, kScanTile) : 1; }
-// partials needed by device_scan: one per tile plus the grand total
-inline size_t scan_partials(int64_t n) { return (size_t)scan_num_tiles(n) + 1; }
+inline int64_t scan_num_tiles(int64_t n) { return n > 0 ? ceil_div(n, (int64_t)kScanBlock * scan_rounds(n)) : 1; }
+// Partials needed by the scans of up to n elements: one per tile, of which a shorter input may have more, plus the
+// grand total.
+inline size_t scan_partials(int64_t n) {
+    int64_t most = scan_num_tiles(n);
+    if (n > kScanSmall) most = std::max(most, scan_num_tiles(kScanSmall));
+    if (n > kScanMiddle) most = std::max(most, scan_num_tiles(kScanMiddle));
+    return (size_t)most + 1;
+}
 
-// Runs the three passes on `stream`.  partials[scan_num_tiles(n)] holds the grand total afterwards.  The per-tile
-// reduction reads its values through `in_reduce`, the final pass through `in_apply`: the same values, but the first
-// may leave notes for the second (flags that are costly to derive twice).
-template <typename T, typename Op, typename InReduce, typename InApply, typename Out>
-int device_scan2(InReduce in_reduce, InApply in_apply, Out out, int64_t n, T* partials, Op op, T identity,
-                 hipStream_t stream) {
+// Passes 2 and 3 for a caller whose own kernel has left the per-tile reductions in `partials`.
+template <int ROUNDS, typename T, typename Op, typename In, typename Out>
+int scan_finish(In in, Out out, int64_t n, T* partials, Op op, T identity, hipStream_t stream) {
     const int64_t tiles = scan_num_tiles(n);
-    BP_LAUNCH(K_SCAN_REDUCE, (scan_reduce_kernel<T, Op, InReduce>), dim3((unsigned)tiles), dim3(kScanBlock), 0, stream,
-              in_reduce, n, partials, op, identity);
-    BP_LAUNCH(K_SCAN_SPINE, (scan_spine_kernel<T, Op>), dim3(1), dim3(1024), 0, stream, partials, tiles, op, identity);
-    BP_LAUNCH(K_SCAN_APPLY, (scan_apply_kernel<T, Op, InApply, Out>), dim3((unsigned)tiles), dim3(kScanBlock), 0, stream,
-              in_apply, out, n, (const T*)partials, op, identity);
-    return BP_OK;
+    const dim3 grid((unsigned)tiles), block(kScanBlock);
+    if constexpr (ROUNDS < 8) {                           // at most kScanFewTiles tiles
+        BP_LAUNCH(K_SCAN_APPLY, (scan_apply_kernel<ROUNDS, false, T, Op, In, Out>), grid, block, 0, stream, in, out, n, partials,
+                  op, identity);
+        return BP_OK;
+    } else {
+        if (tiles <= kScanFewTiles) {
+            BP_LAUNCH(K_SCAN_APPLY, (scan_apply_kernel<ROUNDS, false, T, Op, In, Out>), grid, block, 0, stream, in, out, n,
+                      partials, op, identity);
+            return BP_OK;
+        }
+        BP_LAUNCH(K_SCAN_SPINE, (scan_spine_kernel<T, Op>), dim3(1), dim3(1024), 0, stream, partials, tiles, op, identity);
+        BP_LAUNCH(K_SCAN_APPLY, (scan_apply_kernel<ROUNDS, true, T, Op, In, Out>), grid, block, 0, stream, in, out, n, partials,
+                  op, identity);
+        return BP_OK;
+    }
 }
-// Passes 2 and 3 alone, for a caller whose own kernel has left the per-tile reductions in `partials`.
-template <typename T, typename Op, typename InApply, typename Out>
-int device_scan_reduced(InApply in_apply, Out out, int64_t n, T* partials, Op op, T identity, hipStream_t stream) {
-    const int64_t tiles = scan_num_tiles(n);
-    BP_LAUNCH(K_SCAN_SPINE, (scan_spine_kernel<T, Op>), dim3(1), dim3(1024), 0, stream, partials, tiles, op, identity);
-    BP_LAUNCH(K_SCAN_APPLY, (scan_apply_kernel<T, Op, InApply, Out>), dim3((unsigned)tiles), dim3(kScanBlock), 0, stream,
-              in_apply, out, n, (const T*)partials, op, identity);
-    return BP_OK;
+static_assert(kScanSmall <= kScanFewTiles * kScanBlock && kScanMiddle <= kScanFewTiles * kScanBlock * 4, "no spine for these");
+
+template <typename T, typename Op, typename In, typename Out>
+int device_scan_reduced(In in, Out out, int64_t n, T* partials, Op op, T identity, hipStream_t stream) {
+    switch (scan_rounds(n)) {
+        case 1: return scan_finish<1, T, Op, In, Out>(in, out, n, partials, op, identity, stream);
+        case 4: return scan_finish<4, T, Op, In, Out>(in, out, n, partials, op, identity, stream);
+        default: return scan_finish<8, T, Op, In, Out>(in, out, n, partials, op, identity, stream);
+    }
 }
+
+// All passes on `stream`.  partials[scan_num_tiles(n)] holds the grand total afterwards.
 template <typename T, typename Op, typename In, typename Out>
 int device_scan(In in, Out out, int64_t n, T* partials, Op op, T identity, hipStream_t stream) {
-    return device_scan2<T, Op, In, In, Out>(in, in, out, n, partials, op, identity, stream);
+    const dim3 grid((unsigned)scan_num_tiles(n)), block(kScanBlock);
+    switch (scan_rounds(n)) {
+        case 1: BP_LAUNCH(K_SCAN_REDUCE, (scan_reduce_kernel<1, T, Op, In>), grid, block, 0, stream, in, n, partials, op, identity); break;
+        case 4: BP_LAUNCH(K_SCAN_REDUCE, (scan_reduce_kernel<4, T, Op, In>), grid, block, 0, stream, in, n, partials, op, identity); break;
+        default: BP_LAUNCH(K_SCAN_REDUCE, (scan_reduce_kernel<8, T, Op, In>), grid, block, 0, stream, in, n, partials, op, identity); break;
+    }
+    return device_scan_reduced<T, Op, In, Out>(in, out, n, partials, op, identity, stream);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -25,6 +25,7 @@
 //      pass need not sort
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -34,7 +35,15 @@
 namespace bp {
 namespace {
 
-constexpr int kPlanSortIPT = 16;       // 4096 keys per tile for the big (id, batch) sort
+// Elements per thread of the plan's sorts: tiles of 4096 keys, or of 1024 where 4096 would leave most of the CUs
+// without one (102,400 lookups: 25 tiles and 11 to 14 us a scatter, 100 tiles and 5 to 6 us).
+constexpr int kPlanSortIPT = 16, kPlanSmallIPT = 4;
+constexpr int64_t kPlanSmallSort = int64_t(1) << 18;
+template <typename F>
+int with_plan_ipt(int64_t n_lookups, F&& f) {
+    if (n_lookups <= kPlanSmallSort) return f(std::integral_constant<int, kPlanSmallIPT>{});
+    return f(std::integral_constant<int, kPlanSortIPT>{});
+}
 constexpr int kBlock = 256;
 constexpr uint32_t kGapInf = 0x7fffffffu;
 constexpr int kMaxIters = 8192;
@@ -149,16 +158,17 @@ struct PairOut {
 // number of the scan's tiles, counts the heads of each of them (what scan_reduce_kernel would leave in `partials`)
 // and the tile's batch digits (what sort_upsweep_kernel would leave in `counts`).  Elements are dealt to lanes as in
 // the scan, so a lane's left neighbour is the lane below it, the round before, or one word fetched per wavefront.
-template <int RB>
+template <int RB, int IPT, int ROUNDS>
 __global__ __launch_bounds__(kSortBlock) void plan_head_hist_kernel(const uint64_t* __restrict__ keys, uint32_t n, int pb,
                                                                     uint32_t* __restrict__ partials, uint32_t scan_tiles,
                                                                     uint32_t mask, uint32_t* __restrict__ counts,
                                                                     uint32_t ntiles) {
     constexpr int RADIX = 1 << RB;
-    constexpr int TILE = kSortBlock * kPlanSortIPT;
-    constexpr int PARTS = TILE / kScanTile;
+    constexpr int TILE = kSortBlock * IPT;
+    constexpr int SCAN_TILE = kScanBlock * ROUNDS;
+    constexpr int PARTS = TILE / SCAN_TILE;
     constexpr int WAVES = kSortBlock / kWave;
-    static_assert(kSortBlock == kScanBlock && TILE % kScanTile == 0, "a tile of the sort is a whole number of scan tiles");
+    static_assert(kSortBlock == kScanBlock && TILE % SCAN_TILE == 0, "a tile of the sort is a whole number of scan tiles");
     __shared__ uint32_t hist[RADIX];
     __shared__ uint32_t wave_tot[PARTS][WAVES];
     const uint32_t tile = blockIdx.x;
@@ -167,17 +177,17 @@ __global__ __launch_bounds__(kSortBlock) void plan_head_hist_kernel(const uint64
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < PARTS; ++h) {
-        const int64_t first = (int64_t)tile * TILE + h * kScanTile + w * kScanWaveStretch;      // of this wavefront
-        uint64_t k[kScanRounds];
+        const int64_t first = (int64_t)tile * TILE + h * SCAN_TILE + w * (kWave * ROUNDS);      // of this wavefront
+        uint64_t k[ROUNDS];
 #pragma unroll
-        for (int r = 0; r < kScanRounds; ++r) {
+        for (int r = 0; r < ROUNDS; ++r) {
             const int64_t i = first + r * kWave + lane;
             k[r] = i < (int64_t)n ? keys[i] : 0;
         }
         uint64_t before = first > 0 && first <= (int64_t)n ? keys[first - 1] : 0;               // left of lane 0, round 0
         uint32_t heads = 0;
 #pragma unroll
-        for (int r = 0; r < kScanRounds; ++r) {
+        for (int r = 0; r < ROUNDS; ++r) {
             const int64_t i = first + r * kWave + lane;
             uint64_t left = __shfl_up(k[r], 1, kWave);
             if (lane == 0) left = before;
@@ -204,6 +214,24 @@ __global__ __launch_bounds__(kSortBlock) void plan_head_hist_kernel(const uint64
         if (st < scan_tiles) partials[st] = total;
     }
     for (int d = threadIdx.x; d < RADIX; d += kSortBlock) counts[(size_t)d * ntiles + tile] = hist[d];
+}
+
+template <int IPT, int ROUNDS>
+int launch_head_hist(const uint64_t* skeys, int64_t N, int pb, uint32_t* partials, int bits, uint32_t* counts, hipStream_t stream) {
+    const uint32_t ntiles = sort_num_tiles<IPT>(N), mask = (1u << bits) - 1u, scan_tiles = (uint32_t)scan_num_tiles(N);
+    if (bits > 8)
+        BP_LAUNCH(K_SCAN_REDUCE, (plan_head_hist_kernel<9, IPT, ROUNDS>), dim3(ntiles), dim3(kSortBlock), 0, stream, skeys,
+                  (uint32_t)N, pb, partials, scan_tiles, mask, counts, ntiles);
+    else
+        BP_LAUNCH(K_SCAN_REDUCE, (plan_head_hist_kernel<8, IPT, ROUNDS>), dim3(ntiles), dim3(kSortBlock), 0, stream, skeys,
+                  (uint32_t)N, pb, partials, scan_tiles, mask, counts, ntiles);
+    return BP_OK;
+}
+int plan_head_hist(const uint64_t* skeys, int64_t N, int pb, uint32_t* partials, int bits, uint32_t* counts, hipStream_t stream) {
+    static_assert(kPlanSmallSort == kScanSmall, "one length of input decides both tiles");
+    if (N <= kPlanSmallSort) return launch_head_hist<kPlanSmallIPT, 1>(skeys, N, pb, partials, bits, counts, stream);
+    if (scan_rounds(N) == 4) return launch_head_hist<kPlanSortIPT, 4>(skeys, N, pb, partials, bits, counts, stream);
+    return launch_head_hist<kPlanSortIPT, 8>(skeys, N, pb, partials, bits, counts, stream);
 }
 
 // ---- 3. gaps, histogram, occupancy -----------------------------------------------------------
@@ -920,7 +948,9 @@ PlanWorkspace carve_plan(void* base, size_t cap, int64_t N, int T, int Lcap, boo
     w.keys_b = c.take<uint64_t>(n);
     w.uq = c.take<uint32_t>(n < 64 ? 64 : n);      // later the rows' first positions of the grouping step
     w.tile_batch = c.take<int32_t>((n >> kPosTileShift) + 2);
-    w.sort_temp = c.take<uint32_t>(sort_temp_words<kPlanSortIPT>(N));
+    // a workspace that is large enough for N lookups is so for fewer, which may have more tiles
+    const int64_t in_small_tiles = std::min(N, kPlanSmallSort);
+    w.sort_temp = c.take<uint32_t>(std::max(sort_temp_words<kPlanSortIPT>(N), sort_temp_words<kPlanSmallIPT>(in_small_tiles)));
     w.scan_partials32 = c.take<uint32_t>(scan_partials(N));
     w.scan_partials64 = c.take<uint64_t>(scan_partials(N));
     w.H = c.take<uint32_t>((size_t)(Lcap + 1) * T);
@@ -952,7 +982,8 @@ PlanWorkspace carve_plan(void* base, size_t cap, int64_t N, int T, int Lcap, boo
     w.slot_of_pair = c.take<int32_t>(n);
     if (grouping) {
         w.keys_c = c.take<uint64_t>(n);
-        w.group_counts = c.take<uint32_t>((size_t)kMaxRadix * sort_num_tiles<kPlanSortIPT>(N));
+        w.group_counts = c.take<uint32_t>((size_t)kMaxRadix * std::max(sort_num_tiles<kPlanSortIPT>(N),
+                                                                        sort_num_tiles<kPlanSmallIPT>(in_small_tiles)));
     }
     w.bytes = c.used();
     return w;
@@ -1102,8 +1133,10 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
     uint64_t* const kbuf[2] = {w.keys_a, w.keys_b};
     uint32_t* const no_vals[2] = {nullptr, nullptr};
     int sorted_in = -1;
-    BP_TRY((radix_sort_from<uint64_t, kPlanSortIPT, PlanKeySource, PlanKeySource, false>(
-        source, source, kbuf, no_vals, N, ib + pb, ib + pb + gb, w.sort_temp, stream, &sorted_in)));
+    BP_TRY(with_plan_ipt(N, [&](auto ipt) {
+        return radix_sort_from<uint64_t, ipt(), PlanKeySource, PlanKeySource, false>(
+            source, source, kbuf, no_vals, N, ib + pb, ib + pb + gb, w.sort_temp, stream, &sorted_in);
+    }));
     const uint64_t* skeys = kbuf[sorted_in];
     uint64_t* ukey = kbuf[sorted_in ^ 1];          // the other ping-pong buffer is free now
     uint32_t* uq = w.uq;
@@ -1111,14 +1144,7 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
     // ---- 2. unique pairs
     const int group_bits = grouping ? radix_first_pass_bits(pb, pb + ib) : 0;     // of the regrouping sort's first pass
     if (grouping) {
-        const uint32_t ntiles = sort_num_tiles<kPlanSortIPT>(N);
-        const uint32_t mask = (1u << group_bits) - 1u;
-        if (group_bits > 8)
-            BP_LAUNCH(K_SCAN_REDUCE, plan_head_hist_kernel<9>, dim3(ntiles), dim3(kSortBlock), 0, stream, skeys, (uint32_t)N, pb,
-                      w.scan_partials32, (uint32_t)scan_num_tiles(N), mask, w.group_counts, ntiles);
-        else
-            BP_LAUNCH(K_SCAN_REDUCE, plan_head_hist_kernel<8>, dim3(ntiles), dim3(kSortBlock), 0, stream, skeys, (uint32_t)N, pb,
-                      w.scan_partials32, (uint32_t)scan_num_tiles(N), mask, w.group_counts, ntiles);
+        BP_TRY(plan_head_hist(skeys, N, pb, w.scan_partials32, group_bits, w.group_counts, stream));
         BP_TRY((device_scan_reduced<uint32_t, AddOp, HeadFlagIn, PairOut>(
             HeadFlagIn{skeys, pb}, PairOut{skeys, pb, ukey, uq, w.pair_start}, N, w.scan_partials32, AddOp(), 0u, stream)));
     } else {
@@ -1199,15 +1225,19 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
     // pass then looks the fetching pair up.
     bool ord_in_b = false;
     if (owners) {
-        BP_TRY((radix_sort_numbered<uint64_t, kPlanSortIPT>(w.rec_a, w.rec_b, w.val2_a, w.val2_b, M, 0, ib, w.sort_temp,
-                                                            stream, &ord_in_b)));
+        BP_TRY(with_plan_ipt(N, [&](auto ipt) {
+            return radix_sort_numbered<uint64_t, ipt()>(w.rec_a, w.rec_b, w.val2_a, w.val2_b, M, 0, ib, w.sort_temp, stream,
+                                                        &ord_in_b);
+        }));
     } else {
         uint64_t* const rbuf[2] = {w.rec_b, w.rec_a};
         uint32_t* const vbuf[2] = {w.val2_b, w.val2_a};
         const SortArrays<uint64_t> rup{w.rec_a, nullptr}, rsrc{w.rec_a, w.chain};
         int r_in = -1;
-        BP_TRY((radix_sort_from<uint64_t, kPlanSortIPT, SortArrays<uint64_t>, SortArrays<uint64_t>, true>(
-            rup, rsrc, rbuf, vbuf, M, 0, ib, w.sort_temp, stream, &r_in)));
+        BP_TRY(with_plan_ipt(N, [&](auto ipt) {
+            return radix_sort_from<uint64_t, ipt(), SortArrays<uint64_t>, SortArrays<uint64_t>, true>(
+                rup, rsrc, rbuf, vbuf, M, 0, ib, w.sort_temp, stream, &r_in);
+        }));
         ord_in_b = r_in == 0;
     }
     const uint64_t* srec = ord_in_b ? w.rec_b : w.rec_a;
@@ -1255,8 +1285,10 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
         const SortArrays<uint64_t> gup{skeys, nullptr};
         uint64_t* const gbuf[2] = {w.keys_c, const_cast<uint64_t*>(skeys)};
         int g_in = -1;
-        BP_TRY((radix_sort_from<uint64_t, kPlanSortIPT, SortArrays<uint64_t>, GroupWordSource, false>(
-            gup, gsrc, gbuf, no_vals, N, pb, pb + ib, w.sort_temp, stream, &g_in, w.group_counts)));
+        BP_TRY(with_plan_ipt(N, [&](auto ipt) {
+            return radix_sort_from<uint64_t, ipt(), SortArrays<uint64_t>, GroupWordSource, false>(
+                gup, gsrc, gbuf, no_vals, N, pb, pb + ib, w.sort_temp, stream, &g_in, w.group_counts);
+        }));
         const uint64_t* gkeys = gbuf[g_in];
         const GroupWord gw{ib, pb};
         // one pass over the grouped words: slot map, grouped_lookups, row starts as bit masks (the masks go to a

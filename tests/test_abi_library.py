@@ -74,3 +74,14 @@ def test_argument_errors_without_gpu(lib):
     # bf16 rows need dim % 8 == 0
     with pytest.raises(bp.BagpipeError):
         bp.bp_embbag_bwd_update_workspace_bytes(bp.make_config(1000, 64, 12, "bf16"), 128, 128)
+
+
+@pytest.mark.parametrize("around", [1 << 10, 1 << 18, 1 << 21])
+def test_plan_workspace_for_more_lookups_is_enough_for_fewer(lib, around):
+    """Short traces are cut into smaller tiles, of which they may have more than a longer trace has of its own."""
+    import paper_2202_12429_amd as bp
+    cfg = bp.make_config(10_000, 512, 16, lookahead=8)
+    sizes = [around + d for d in (-4097, -1, 0, 1, 4097) if around + d > 0]
+    for grouping in (False, True):
+        need = [bp.bp_oracle_plan_workspace_bytes(cfg, n, 10, grouping) for n in sizes]
+        assert need == sorted(need)
