@@ -80,6 +80,27 @@ def test_forward(bp, D, dtype, max_len):
     helpers.assert_outputs_close(out.cpu().numpy(), want, max_len)
 
 
+@pytest.mark.parametrize("D,dtype", [(4, "f32"), (20, "f32"), (64, "f32"), (256, "f32"), (512, "bf16")])
+def test_forward_bags_around_the_bursts(bp, D, dtype):
+    """Bags of 0 to 25 lookups in turn, some of slots that are not there: whole and partial bursts of rows, fp32 sums in
+    lookup order bit for bit."""
+    say(f"forward bursts D={D} {dtype}")
+    C = 300
+    w = random_cache(C, D, dtype, D)
+    rng = np.random.default_rng(D)
+    off = np.concatenate([[0], np.cumsum(np.arange(78) % 26)]).astype(np.int64)
+    slots = rng.integers(-2, C + 3, size=int(off[-1])).astype(np.int32)
+    out = torch.full((78, D), 3.0, device="cuda")
+    bp.bp_embbag_fwd(bp.make_config(1000, C, D, dtype), w.cuda(), dev(slots), dev(off), 78, out)
+    rows = w.float().numpy()
+    want = np.zeros((78, D), np.float32)
+    for b in range(78):
+        for s in slots[off[b]:off[b + 1]]:
+            if 0 <= s < C:
+                want[b] += rows[s]
+    assert np.array_equal(out.cpu().numpy(), want)
+
+
 def test_forward_edge_cases(bp):
     say("forward edge cases")
     C, D = 64, 16
