@@ -162,9 +162,41 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
+class _Span:
+    """Entries [a, b) of a contiguous device array, as the entry points below read a tensor.  A tensor view costs the
+    host about as much as a whole library call, and a training step hands over eleven of them."""
+    __slots__ = ("ptr", "n")
+
+    def __init__(self, ptr: int, n: int):
+        self.ptr, self.n = ptr, n
+
+    def numel(self) -> int:
+        return self.n
+
+    @property
+    def shape(self):
+        return (self.n,)
+
+    def is_contiguous(self) -> bool:
+        return True
+
+    def data_ptr(self) -> int:
+        return self.ptr
+
+
+def _span(t, a: int, b: int):
+    """What t[a:b] is to the library (same bounds as a slice); the caller keeps t."""
+    if t is None or not t.is_contiguous():
+        return t[a:b]
+    a, b, _ = slice(a, b).indices(t.shape[0])
+    return _Span(t.data_ptr() + a * t.stride(0) * t.element_size(), b - a if b > a else 0)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
+        if torch.cuda.is_initialized():      # the number alone: a Stream object costs the host more than the call itself
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
         return torch.cuda.current_stream().cuda_stream or None
     if isinstance(stream, int):
         return stream or None

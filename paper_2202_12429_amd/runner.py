@@ -84,6 +84,7 @@ class CachedEmbeddingTrainer:
             self._cw, self._cs = self.cache_w, self.cache_state
         self.plan_: Optional[B.Plan] = None
         self.iter_offsets: Optional[np.ndarray] = None
+        self._sizes_held = set()       # (lookups, bags) of batches that the buffers below were seen to hold
         self._bwd_ws = None
         self._tickets = None           # counters of the backward pass: zeroed here once, every call leaves them zero
         self._out = None
@@ -95,6 +96,8 @@ class CachedEmbeddingTrainer:
             self._reserve(max_lookups, max_bags or max_lookups)
 
     def _reserve(self, n: int, bags: int):
+        if (n, bags) in self._sizes_held:      # the buffers only grow: a size that fitted once still fits
+            return
         import torch
         need = max(B.bp_embbag_bwd_update_workspace_bytes(self.cfg, n, bags),
                    B.bp_embbag_bwd_update_grouped_workspace_bytes(self.cfg, n, bags, True))
@@ -104,6 +107,9 @@ class CachedEmbeddingTrainer:
             self._tickets = B.bwd_tickets(n, device=self.device)
         if self._out is None or self._out.shape[0] < bags:
             self._out = torch.empty((bags, int(self.cfg.dim)), dtype=torch.float32, device=self.device)
+        if len(self._sizes_held) >= 4096:
+            self._sizes_held.clear()
+        self._sizes_held.add((n, bags))
 
     # ---- (1)
     def plan(self, ids_dev, iter_offsets, list_capacity: Optional[int] = None, workspace=None) -> B.Plan:
@@ -152,19 +158,25 @@ class CachedEmbeddingTrainer:
         a, b = int(off[i]), int(off[i + 1])
         return getattr(p, which + "_ids")[a:b], getattr(p, which + "_slots")[a:b]
 
+    def _spans(self, which: str, i: int):
+        p = self.plan_
+        off = getattr(p, which + "_offsets")
+        a, b = int(off[i]), int(off[i + 1])
+        return B._span(getattr(p, which + "_ids"), a, b), B._span(getattr(p, which + "_slots"), a, b)
+
     def slots(self, i: int):
         a, b = int(self.iter_offsets[i]), int(self.iter_offsets[i + 1])
         return self.plan_.lookup_slots[a:b]
 
     # ---- (2)
     def maintain(self, i: int, stream=None) -> None:
-        e_ids, e_slots = self._slice("evict", i - 1) if i > 0 else (None, None)
+        e_ids, e_slots = self._spans("evict", i - 1) if i > 0 else (None, None)
         disjoint = self.plan_.L_eff >= 2          # a row evicted after batch i-1 is then not fetched for batch i
         if i == 0 and self._carried_evict is not None:
             e_ids, e_slots, l_prev = self._carried_evict
             disjoint = disjoint and l_prev >= 2    # ... under the lookahead the eviction was decided with
             self._carried_evict = None
-        p_ids, p_slots = self._slice("prefetch", i)
+        p_ids, p_slots = self._spans("prefetch", i)
         if self._early is not None and disjoint and not self._n_emit:
             n_early = int(self._early[i]) if i > 0 else int(p_ids.numel())
             B.bp_cache_apply_handoff(self.cfg, self._cw, self._cs, self.backing_w, self.backing_state, e_ids,
@@ -207,7 +219,7 @@ class CachedEmbeddingTrainer:
 
     def flush(self, stream=None) -> None:
         T = self._n_emit if self._n_emit else self.iter_offsets.shape[0] - 1
-        e_ids, e_slots = self._slice("evict", T - 1)
+        e_ids, e_slots = self._spans("evict", T - 1)
         B.bp_cache_apply(self.cfg, self._cw, self._cs, self.backing_w, self.backing_state, e_ids, e_slots,
                          None, None, stream=stream)
         if self._early is not None and int(self._mismatch.item()) != 0:       # synchronises
@@ -226,10 +238,10 @@ class CachedEmbeddingTrainer:
                 raise ValueError("the forward pass over the row records takes bags of one lookup; plan with slot_map=True")
             ka, kb = int(p.keep_offsets[i]), int(p.keep_offsets[i + 1])
             pa, pb = int(p.piece_offsets[i]), int(p.piece_offsets[i + 1])
-            B.bp_embbag_fwd_grouped(self.cfg, self._cw, p.grouped_lookups[a:b], p.row_recs[ka:kb], p.piece_recs[pa:pb],
-                                    bags, out, stream=stream)
+            B.bp_embbag_fwd_grouped(self.cfg, self._cw, B._span(p.grouped_lookups, a, b),
+                                    B._span(p.row_recs, ka, kb), B._span(p.piece_recs, pa, pb), bags, out, stream=stream)
         else:
-            B.bp_embbag_fwd(self.cfg, self._cw, p.lookup_slots[a:b], bag_offsets_dev, bags, out, stream=stream)
+            B.bp_embbag_fwd(self.cfg, self._cw, B._span(p.lookup_slots, a, b), bag_offsets_dev, bags, out, stream=stream)
         return out
 
     # ---- (4)
@@ -243,9 +255,9 @@ class CachedEmbeddingTrainer:
                 return
             ka, kb = int(p.keep_offsets[i]), int(p.keep_offsets[i + 1])       # a batch's rows are its keep-list entries
             pa, pb = int(p.piece_offsets[i]), int(p.piece_offsets[i + 1])
-            B.bp_embbag_bwd_update_grouped(self.cfg, self._cw, self._cs, p.grouped_lookups[a:b],
-                                           p.row_recs[ka:kb], p.piece_recs[pa:pb], bag_offsets_dev, bags, grad_out,
-                                           self._bwd_ws, self._tickets, stream=stream)
+            B.bp_embbag_bwd_update_grouped(self.cfg, self._cw, self._cs, B._span(p.grouped_lookups, a, b),
+                                           B._span(p.row_recs, ka, kb), B._span(p.piece_recs, pa, pb),
+                                           bag_offsets_dev, bags, grad_out, self._bwd_ws, self._tickets, stream=stream)
         else:
-            B.bp_embbag_bwd_update(self.cfg, self._cw, self._cs, p.lookup_slots[a:b], bag_offsets_dev,
+            B.bp_embbag_bwd_update(self.cfg, self._cw, self._cs, B._span(p.lookup_slots, a, b), bag_offsets_dev,
                                    bags, grad_out, self._bwd_ws, self._tickets, stream=stream)
