@@ -469,7 +469,9 @@ struct PairRecord {
 
 // The search for the TTL probes up to L_eff - 1 pairs ahead, one probe behind the other: the workgroup first copies
 // its own pairs (kFlagsPerThread per thread), the one before them and the next kFlagsWindow into LDS, where a probe
-// costs a fraction of a trip to L2 (probes beyond that window go to memory as before).
+// costs a fraction of a trip to L2.  Only a lookahead beyond the window has probes outside it, and only then is a
+// probe's place tested: with the test in every probe the compiler picks the address instead and reads it with a flat
+// load, which waits for both kinds of memory (29 M pairs, lookahead 400: 129 -> 78 us).
 constexpr int kFlagsWindow = 1024;
 constexpr int kFlagsPerThread = 4;
 constexpr int kFlagsTile = kBlock * kFlagsPerThread;
@@ -479,34 +481,32 @@ __global__ __launch_bounds__(kBlock) void plan_flags_kernel(const uint64_t* __re
     const uint64_t imask = (uint64_t(1) << ib) - 1;
     const int64_t Leff = sc->L_eff;
     const int64_t win_first = (int64_t)blockIdx.x * kFlagsTile - 1;             // pair number of win[0]
-    const int ahead = (int)(Leff - 1 < kFlagsWindow ? (Leff > 1 ? Leff - 1 : 0) : kFlagsWindow);
+    const bool near = Leff - 1 <= kFlagsWindow;                                 // no probe leaves the window
+    const int ahead = (int)(near ? (Leff > 1 ? Leff - 1 : 1) : kFlagsWindow);   // the next pair at least
     const int span = kFlagsTile + 1 + ahead;
     for (int t = threadIdx.x; t < span; t += kBlock) {
         const int64_t p = win_first + t;
         win[t] = p >= 0 && p < (int64_t)M ? ukey[p] : ~uint64_t(0);
     }
     __syncthreads();
-    const auto key_at = [&](int64_t p) -> uint64_t {                            // first pair of the tile - 1 <= p < M
-        const int64_t t = p - win_first;
-        return t < span ? win[t] : ukey[p];
-    };
 #pragma unroll
     for (int e = 0; e < kFlagsPerThread; ++e) {
         const uint32_t q = blockIdx.x * kFlagsTile + e * kBlock + threadIdx.x;
         if (q >= M) break;
-        const uint64_t k = key_at(q);
+        const int w = e * kBlock + (int)threadIdx.x + 1;    // win[w] is pair q
+        const uint64_t k = win[w];
         const uint64_t g = k >> ib;
         const int64_t i = (int64_t)(k & imask);
         uint32_t gap = kGapInf;
         if (q + 1 < M) {
-            const uint64_t kn = key_at((int64_t)q + 1);
+            const uint64_t kn = win[w + 1];
             if ((kn >> ib) == g) gap = (uint32_t)((kn & imask) - (k & imask));
         }
         const bool carried = chunk && i == 0;              // resident since before the chunk: stays until its next use
         const bool keep = carried || (int64_t)gap < Leff;
         bool miss = true;
         if (q > 0) {
-            const uint64_t kp = key_at((int64_t)q - 1);
+            const uint64_t kp = win[w - 1];
             if ((kp >> ib) == g && ((chunk && (kp & imask) == 0) || i - (int64_t)(kp & imask) < Leff)) miss = false;
         }
         uint32_t t = (uint32_t)i;
@@ -514,13 +514,27 @@ __global__ __launch_bounds__(kBlock) void plan_flags_kernel(const uint64_t* __re
             // last pair of this id whose batch is <= i + L_eff - 1: it lies within L_eff - 1 pairs of q
             const int64_t last_iter = i + Leff - 1 < (int64_t)imask ? i + Leff - 1 : (int64_t)imask;
             const uint64_t bound = (g << ib) | (uint64_t)last_iter;
-            int64_t lo = q, hi = (int64_t)q + Leff - 1;     // pair lo <= bound; answer in [lo, hi]
-            if (hi > (int64_t)M - 1) hi = (int64_t)M - 1;
-            while (lo < hi) {
-                const int64_t mid = (lo + hi + 1) >> 1;
-                if (key_at(mid) <= bound) lo = mid; else hi = mid - 1;
+            if (near) {
+                int lo = w, hi = w + (int)Leff - 1;         // win[lo] <= bound; answer in [lo, hi]
+                if (hi > (int64_t)M - 1 - win_first) hi = (int)((int64_t)M - 1 - win_first);
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (win[mid] <= bound) lo = mid; else hi = mid - 1;
+                }
+                t = (uint32_t)(win[lo] & imask);
+            } else {
+                int64_t lo = q, hi = (int64_t)q + Leff - 1;
+                if (hi > (int64_t)M - 1) hi = (int64_t)M - 1;
+                const auto key_at = [&](int64_t p) -> uint64_t {
+                    const int64_t x = p - win_first;
+                    return x < span ? win[x] : ukey[p];
+                };
+                while (lo < hi) {
+                    const int64_t mid = (lo + hi + 1) >> 1;
+                    if (key_at(mid) <= bound) lo = mid; else hi = mid - 1;
+                }
+                t = (uint32_t)(key_at(lo) & imask);
             }
-            t = (uint32_t)(key_at(lo) & imask);
         }
         rec[q] = PairRecord{ib}.pack(g, t, (miss ? kMiss : 0) | (keep ? 0 : kEvict), (uint32_t)i);
     }

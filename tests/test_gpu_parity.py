@@ -715,6 +715,19 @@ def test_plan_many_batches_wide_group_keys(bp):
     plan_both(bp, ids, off, 5000, 12, 1500)
 
 
+@pytest.mark.parametrize("lookahead", [1, 2, 3, 1024, 1025, 1026, 1500])
+def test_plan_lookaheads_around_the_probe_window(bp, lookahead):
+    """1,400 batches of a few rows each, popular ones in nearly every batch: the last use inside the lookahead lies up to
+    1,399 pairs ahead, within the LDS window of the flags kernel (1,024 pairs) and beyond it."""
+    say(f"plan with lookahead {lookahead}")
+    rng = np.random.default_rng(lookahead)
+    T, R = 1400, 40
+    off = np.zeros(T + 1, dtype=np.int64)
+    off[1:] = np.cumsum(rng.integers(1, 9, size=T))
+    ids = np.minimum(rng.zipf(1.4, size=int(off[-1])) - 1, R - 1).astype(np.int64)
+    plan_both(bp, ids, off, R, lookahead, 64)
+
+
 def test_plan_errors(bp):
     say("plan errors")
     ids = np.array([0, 1, 2, 3, 0, 1], dtype=np.int64)
