@@ -171,7 +171,8 @@ __global__ __launch_bounds__(kSortBlock) void plan_head_hist_kernel(const uint64
     static_assert(kSortBlock == kScanBlock && TILE % SCAN_TILE == 0, "a tile of the sort is a whole number of scan tiles");
     __shared__ uint32_t hist[RADIX];
     __shared__ uint32_t wave_tot[PARTS][WAVES];
-    const uint32_t tile = blockIdx.x;
+    const uint32_t tile = sort_tile_of_block(ntiles);
+    if (tile >= ntiles) return;
     const int w = threadIdx.x / kWave, lane = lane_id();
     for (int d = threadIdx.x; d < RADIX; d += kSortBlock) hist[d] = 0;
     __syncthreads();
@@ -220,10 +221,10 @@ template <int IPT, int ROUNDS>
 int launch_head_hist(const uint64_t* skeys, int64_t N, int pb, uint32_t* partials, int bits, uint32_t* counts, hipStream_t stream) {
     const uint32_t ntiles = sort_num_tiles<IPT>(N), mask = (1u << bits) - 1u, scan_tiles = (uint32_t)scan_num_tiles(N);
     if (bits > 8)
-        BP_LAUNCH(K_SCAN_REDUCE, (plan_head_hist_kernel<9, IPT, ROUNDS>), dim3(ntiles), dim3(kSortBlock), 0, stream, skeys,
+        BP_LAUNCH(K_SCAN_REDUCE, (plan_head_hist_kernel<9, IPT, ROUNDS>), dim3(sort_grid(ntiles)), dim3(kSortBlock), 0, stream, skeys,
                   (uint32_t)N, pb, partials, scan_tiles, mask, counts, ntiles);
     else
-        BP_LAUNCH(K_SCAN_REDUCE, (plan_head_hist_kernel<8, IPT, ROUNDS>), dim3(ntiles), dim3(kSortBlock), 0, stream, skeys,
+        BP_LAUNCH(K_SCAN_REDUCE, (plan_head_hist_kernel<8, IPT, ROUNDS>), dim3(sort_grid(ntiles)), dim3(kSortBlock), 0, stream, skeys,
                   (uint32_t)N, pb, partials, scan_tiles, mask, counts, ntiles);
     return BP_OK;
 }
