@@ -642,7 +642,7 @@ def test_plan_medium_multi_tile(bp):
     plan_both(bp, tr.ids, tr.iter_offsets, cfg.total_rows, 60, 10 ** 6)         # lookahead beyond the trace
 
 
-@pytest.mark.parametrize("n", [1023, 1025, 4097, 1 << 18, (1 << 18) + 1, 1 << 21, (1 << 21) + 1, 1024 * 4096, 1024 * 4096 + 1, 2 * 1024 * 4096 + 4097])
+@pytest.mark.parametrize("n", [1023, 1025, 4097, 16 * 1024, 32 * 1024, 32 * 1024 + 1, 1 << 18, (1 << 18) + 1, 1 << 21, (1 << 21) + 1, 1024 * 4096, 1024 * 4096 + 1, 2 * 1024 * 4096 + 4097])
 def test_plan_sizes_around_the_sort_tiles(bp, n):
     """Lookups around one tile of the sort, around the sizes up to which tiles of sorts and scans are smaller, and around
     the number of tiles up to which a small workgroup scans a digit's counts; beyond it a large workgroup takes them in
