@@ -472,7 +472,7 @@ struct PairRecord {
 // its own pairs (kFlagsPerThread per thread), the one before them and the next kFlagsWindow into LDS, where a probe
 // costs a fraction of a trip to L2.  Only a lookahead beyond the window has probes outside it, and only then is a
 // probe's place tested: with the test in every probe the compiler picks the address instead and reads it with a flat
-// load, which waits for both kinds of memory (29 M pairs, lookahead 400: 129 -> 78 us).
+// load, which waits for both kinds of memory (the pairs of 85 M lookups, lookahead 400: 129 -> 78 us).
 constexpr int kFlagsWindow = 1024;
 constexpr int kFlagsPerThread = 4;
 constexpr int kFlagsTile = kBlock * kFlagsPerThread;
@@ -856,6 +856,10 @@ __global__ __launch_bounds__(kBlock) void plan_piece_partial_kernel(uint4* __res
 // their batch's stretch of the map (a few MB at most).  The same pass over the grouped words writes each lookup's
 // place to grouped_lookups and the row starts as bit masks (a wavefront holds 64 consecutive grouped positions
 // starting at a multiple of 64, lane = position % 64; positions outside [first, N) start no row).
+// Bound by the lines of the map where a batch's stretch outgrows an L2, else by memory: a thread's words are asked for
+// together, and what is read or written in order goes past the caches, which are left to the map (one word a thread:
+// 268 us on 85 M lookups without a map, 158 this way, 6.5 TB/s; 50 M with one in 17 MB stretches: 535 -> 486).
+constexpr int kSlotRounds = 4;
 __global__ __launch_bounds__(kBlock) void plan_lookup_slots_grouped_kernel(int64_t N, uint32_t per_xcd, GroupWord gw,
                                                                            int64_t first,
                                                                            const uint64_t* __restrict__ gkeys,
@@ -863,21 +867,36 @@ __global__ __launch_bounds__(kBlock) void plan_lookup_slots_grouped_kernel(int64
                                                                            int32_t* __restrict__ lookup_slots,
                                                                            int32_t* __restrict__ grouped_lookups,
                                                                            uint64_t* __restrict__ head_mask) {
-    const int64_t p = xcd_contiguous_block(per_xcd) * kBlock + threadIdx.x;
-    const bool real = p >= first && p < N;
-    const uint64_t k = real ? gkeys[p] : 0;
-    // the word before: the lane below holds it, only a wavefront's first lane has to load it
-    uint64_t before = __shfl_up(k, 1, kWave);
-    if (lane_id() == 0 && real && p > first) before = gkeys[p - 1];
-    bool head = false;
-    if (real) {
-        const uint32_t place = gw.place(k);
-        if (lookup_slots) lookup_slots[where.iter_off[gw.batch(k)] + place - first] = (int32_t)gw.slot(k);
-        grouped_lookups[p - first] = (int32_t)place;
-        head = p == first || (k >> gw.pb) != (before >> gw.pb);
+    const int lane = lane_id();
+    const int64_t stretch = xcd_contiguous_block(per_xcd) * (kBlock * kSlotRounds) + (threadIdx.x / kWave) * (kWave * kSlotRounds);
+    uint64_t k[kSlotRounds];
+#pragma unroll
+    for (int u = 0; u < kSlotRounds; ++u) {
+        const int64_t p = stretch + u * kWave + lane;
+        k[u] = p >= first && p < N ? __builtin_nontemporal_load(gkeys + p) : 0;
     }
-    const uint64_t m = __ballot(head);
-    if ((p & 63) == 0 && p < ((N + 63) & ~int64_t(63))) head_mask[p >> 6] = m;
+    // the word before: the lane below holds it, or the round before, or it is one word fetched per wavefront
+    uint64_t before = stretch > first && stretch < N ? gkeys[stretch - 1] : 0;
+    int64_t to[kSlotRounds];
+    if (lookup_slots) {
+#pragma unroll
+        for (int u = 0; u < kSlotRounds; ++u) to[u] = where.iter_off[gw.batch(k[u])] + gw.place(k[u]) - first;
+    }
+#pragma unroll
+    for (int u = 0; u < kSlotRounds; ++u) {
+        const int64_t p = stretch + u * kWave + lane;
+        uint64_t left = __shfl_up(k[u], 1, kWave);
+        if (lane == 0) left = before;
+        before = __shfl(k[u], kWave - 1, kWave);
+        bool head = false;
+        if (p >= first && p < N) {
+            if (lookup_slots) lookup_slots[to[u]] = (int32_t)gw.slot(k[u]);
+            __builtin_nontemporal_store((int32_t)gw.place(k[u]), grouped_lookups + (p - first));
+            head = p == first || (k[u] >> gw.pb) != (left >> gw.pb);
+        }
+        const uint64_t m = __ballot(head);
+        if (lane == 0 && p < N) head_mask[p >> 6] = m;
+    }
 }
 
 template <typename T>
@@ -1309,7 +1328,7 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
         // one pass over the grouped words: slot map, grouped_lookups, row starts as bit masks (the masks go to a
         // pair-level buffer that nobody reads any more); then the rows' first positions, into the buffer of the
         // sorted lookups' pair numbers, which is free as well
-        const uint32_t per_xcd = blocks_per_xcd(N);
+        const uint32_t per_xcd = blocks_per_xcd(ceil_div(N, (int64_t)kSlotRounds));
         uint64_t* head_mask = reinterpret_cast<uint64_t*>(w.par);
         uint32_t* row_pos = w.uq;
         const int64_t n_words = (N + 63) / 64;
