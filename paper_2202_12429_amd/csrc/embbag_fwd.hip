@@ -34,6 +34,7 @@ __global__ __launch_bounds__(kRowBlock) void embbag_fwd_kernel(const uint4* __re
         int64_t end = bag_off[bag + 1];
         if (k < 0) k = 0;                           // offsets that point outside the lookups read nothing there
         if (end > n) end = n;
+        if (k > end) k = end;                       // before anything is added to it: k + j cannot wrap
         uint32_t s[kBurst];
 #pragma unroll
         for (int j = 0; j < kBurst; ++j) s[j] = k + j < end ? (uint32_t)slots[k + j] : kNoSlot;

@@ -118,6 +118,17 @@ def test_forward_edge_cases(bp):
     bp.bp_embbag_fwd(cfg, w.cuda(), dev(slots), dev(np.array([0, 3, 5], np.int64)), 2, out)
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy(), np.stack([w[3].numpy(), w[5].numpy()]))
+    # offsets at the ends of their type: those bags are empty, the others are what they were
+    top, low = 2 ** 63 - 1, -2 ** 63
+    off = np.array([0, 1, top, top - 1, low, top - 7, 3, 5], np.int64)
+    out = torch.full((7, D), 7.0, device="cuda")
+    bp.bp_embbag_fwd(cfg, w.cuda(), dev(slots), dev(off), 7, out)
+    torch.cuda.synchronize()
+    want = np.zeros((7, D), np.float32)
+    want[0] = want[4] = w[3].numpy()                 # [0, 1) and [low, top - 7), which is all five lookups
+    want[1] = want[6] = w[5].numpy()                 # [1, top) and [3, 5)
+    want[4] += w[5].numpy()
+    assert np.array_equal(out.cpu().numpy(), want)
     # n_lookups != bags without offsets is an argument error
     with pytest.raises(bp.BagpipeError) as e:
         bp.bp_embbag_fwd(cfg, w.cuda(), dev(slots), None, 2, out)
