@@ -57,6 +57,7 @@ __global__ __launch_bounds__(256) void bwd_bag_of_lookup_kernel(const int64_t* _
     int64_t k = b < bags ? bag_off[b] : 0, end = b < bags ? bag_off[b + 1] : 0;
     if (k < 0) k = 0;
     if (end > n) end = n;
+    if (k > end) k = end;                                // before lanes are added to it: k + lane cannot wrap
     const int here = (int)(bags - b0 < kWave ? bags - b0 : kWave);
     for (int t = 0; t < here; ++t) {
         const int64_t first = __shfl(k, t, kWave), stop = __shfl(end, t, kWave);

@@ -320,6 +320,20 @@ def test_backward_degenerate(bp):
     assert e.value.status == -3
 
 
+def test_backward_grouped_offsets_at_the_ends_of_their_type(bp):
+    say("grouped backward: offsets near 2^63 are those of empty bags")
+    C, D, n = 64, 16, 700
+    w = random_cache(C, D, "f32", 5)
+    cfg = bp.make_config(1000, C, D, "f32", "sgd", lr=0.5)
+    rng = np.random.default_rng(5)
+    slots = rng.integers(0, C, size=n).astype(np.int32)
+    grad = rng.standard_normal((6, D)).astype(np.float32)
+    top, low = 2 ** 63 - 1, -2 ** 63
+    got, _ = run_bwd_grouped(bp, cfg, w, None, slots, np.array([0, 300, n, top, n, top - 5, low], np.int64), 6, grad, False)
+    want, _ = run_bwd_grouped(bp, cfg, w, None, slots, np.array([0, 300, n, n, n, n, n], np.int64), 6, grad, False)
+    assert np.array_equal(got.numpy(), want.numpy())
+
+
 @pytest.mark.parametrize("D,dtype,optimizer,pad", [(48, "f32", "adagrad", 0), (16, "f32", "adagrad", 64),
                                                    (128, "bf16", "adagrad_rowwise", 12), (32, "f32", "sgd", 32)])
 def test_strided_cache_equals_dense(bp, D, dtype, optimizer, pad):
