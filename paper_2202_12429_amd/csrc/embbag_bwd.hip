@@ -16,6 +16,8 @@
 // ONE launch does all of it: workgroups [0, piece_blocks) take pieces, the rest take rows.
 // Every order of addition is fixed by the records, never by timing: results are bit-identical run to run.
 // The summed gradient is rounded to fp32 once; the optimizer step itself is fp32 arithmetic.
+#include <algorithm>
+
 #include "bwd_records.h"
 #include "common.h"
 #include "device_prims.h"
@@ -503,7 +505,10 @@ BP_EXPORT size_t bp_embbag_bwd_ticket_bytes(int64_t n_lookups) { return partial_
 BP_EXPORT int bp_embbag_bwd_update_workspace_bytes(const bp_config* cfg, int64_t n_lookups, int64_t bags, size_t* bytes) {
     if (!bytes) return fail(BP_ERR_INVALID_ARG, "bytes is NULL");
     BP_TRY(check_bwd_args(cfg, n_lookups, bags));
+    // enough for fewer lookups as well, of which those just below kLargeSort need more than those from there on (the
+    // call itself asks for no more than its own batch needs)
     *bytes = carve_bwd(nullptr, 0, n_lookups, cfg->dim).bytes;
+    if (n_lookups >= kLargeSort) *bytes = std::max(*bytes, carve_bwd(nullptr, 0, kLargeSort - 1, cfg->dim).bytes);
     return BP_OK;
 }
 

@@ -85,3 +85,13 @@ def test_plan_workspace_for_more_lookups_is_enough_for_fewer(lib, around):
     for grouping in (False, True):
         need = [bp.bp_oracle_plan_workspace_bytes(cfg, n, 10, grouping) for n in sizes]
         assert need == sorted(need)
+
+
+def test_backward_workspace_for_more_lookups_is_enough_for_fewer(lib):
+    """The sort takes larger tiles, and so less scratch, from 2^21 lookups on; a caller that sizes its workspace once for
+    the largest batch passes it for the smaller ones too."""
+    import paper_2202_12429_amd as bp
+    cfg = bp.make_config(10_000, 512, 16)
+    sizes = sorted({max(0, around + d) for around in (1 << 10, 1 << 18, 1 << 21) for d in (-4097, -1, 0, 1, 4097)} | {2_200_000})
+    need = [bp.bp_embbag_bwd_update_workspace_bytes(cfg, n, n) for n in sizes]
+    assert need == sorted(need)
