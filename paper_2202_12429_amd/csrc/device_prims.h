@@ -419,6 +419,8 @@ __global__ __launch_bounds__(BLOCK) void sort_digit_scan_kernel(const uint32_t* 
     if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
+typedef uint32_t __attribute__((may_alias)) TwoCounters;      // two 16-bit counters, cleared with one store
+
 // What hides the loads' and the LDS's latency here is the number of workgroups a CU holds: 4 of keys alone (39 KB of LDS
 // each, 128 VGPRs), 3 of keys and values (2 at 9 bits), all at 4096 64-bit keys.  (With 32-bit wave counters and the
 // digits' starts beside them it was 3 of keys alone; 85 M words: 530 -> 478 us where the keys are made on the way, 314
@@ -444,7 +446,7 @@ __global__ __launch_bounds__(kSortBlock, !VALS ? 4 : RB > 8 ? 2 : 3) void sort_d
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
     const uint32_t tile = sort_tile_of_block(ntiles);
     if (tile >= ntiles) return;
-    for (int d = tid; d < WAVES * RADIX / 2; d += kSortBlock) reinterpret_cast<uint32_t*>(&wcnt[0][0])[d] = 0;
+    for (int d = tid; d < WAVES * RADIX / 2; d += kSortBlock) reinterpret_cast<TwoCounters*>(&wcnt[0][0])[d] = 0;
     // asked for now, used after the ranking
     uint32_t all[DPT], earlier[DPT];           // elements of the thread's digits: in all tiles, in the tiles before
     if (IPT > kSortSmallIPT || totals) {
