@@ -195,8 +195,10 @@ def _span(t, a: int, b: int):
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
-        if torch.cuda.is_initialized():      # the number alone: a Stream object costs the host more than the call itself
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+        # the number alone, where this torch has these calls: a Stream object costs the host more than the call itself
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is not None and device is not None and torch.cuda.is_initialized():
+            return raw(device()) or None
         return torch.cuda.current_stream().cuda_stream or None
     if isinstance(stream, int):
         return stream or None

@@ -95,3 +95,15 @@ def test_backward_workspace_for_more_lookups_is_enough_for_fewer(lib):
     sizes = sorted({max(0, around + d) for around in (1 << 10, 1 << 18, 1 << 21) for d in (-4097, -1, 0, 1, 4097)} | {2_200_000})
     need = [bp.bp_embbag_bwd_update_workspace_bytes(cfg, n, n) for n in sizes]
     assert need == sorted(need)
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_torch_internals(monkeypatch, missing):
+    """A torch that lacks one of the internal calls still tells its current stream, by the public one."""
+    import types
+    import torch
+    from paper_2202_12429_amd import binding
+    monkeypatch.delattr(torch._C, missing, raising=False)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert binding._stream(None) == 77
