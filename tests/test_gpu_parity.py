@@ -101,6 +101,35 @@ def test_forward_bags_around_the_bursts(bp, D, dtype):
     assert np.array_equal(out.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("D,dtype,bags,longest", [
+    # launches that leave the chip room: bursts of four for short bags, of eight from a mean of 7 lookups on
+    (4, "f32", 300, 12), (4, "f32", 300, 15), (64, "f32", 300, 3), (64, "f32", 300, 12), (64, "f32", 300, 15),
+    # 2^18 lanes, 16 a bag: long bags in bursts of eight below, of four from there on
+    (64, "f32", 16383, 20), (64, "f32", 16384, 20),
+    # 2^21 lanes and rows of 128 elements or more: fp32 with short bags, with long ones; bf16 with one, few and many lookups
+    (128, "f32", 65535, 15), (128, "f32", 65536, 12), (128, "f32", 65536, 15), (128, "bf16", 131072, 2), (128, "bf16", 131072, 4),
+    (128, "bf16", 131072, 15)])
+def test_forward_bags_in_every_form(bp, D, dtype, bags, longest):
+    """Bags of 0 to `longest` lookups in turn (mean longest / 2), around the sizes where another form of the pooled forward
+    pass is taken; fp32 sums in lookup order bit for bit."""
+    say(f"forward D={D} {dtype} {bags} bags of up to {longest}")
+    C = 300
+    w = random_cache(C, D, dtype, D)
+    rng = np.random.default_rng(D + bags)
+    lens = np.arange(bags) % (longest + 1)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    slots = rng.integers(-2, C + 3, size=int(off[-1])).astype(np.int32)
+    out = torch.full((bags, D), 3.0, device="cuda")
+    bp.bp_embbag_fwd(bp.make_config(1000, C, D, dtype), w.cuda(), dev(slots), dev(off), bags, out)
+    rows = np.concatenate([w.float().numpy(), np.zeros((1, D), np.float32)])        # row C: what an absent slot adds
+    slots = np.where((slots >= 0) & (slots < C), slots, C)
+    want = np.zeros((bags, D), np.float32)
+    for j in range(longest):
+        has = np.flatnonzero(lens > j)
+        want[has] += rows[slots[off[has] + j]]
+    assert np.array_equal(out.cpu().numpy(), want)
+
+
 def test_forward_edge_cases(bp):
     say("forward edge cases")
     C, D = 64, 16
