@@ -13,9 +13,10 @@
 namespace bp {
 namespace {
 
-// Bags of several lookups.  Where the launch leaves the chip room, bounded by the rows' latency: a burst's rows are in
-// flight together, the slots of the next burst come while they arrive, and a bag's last, short burst is one round trip
-// like the others.  How deep a burst pays is the rule in FwdLaunch.
+// Bags of several lookups, bounded by the rows' latency where the launch leaves the chip room, else by memory: a burst's
+// rows are in flight together, the slots of the next burst come while they arrive, and a bag's last, short burst is one
+// round trip like the others (4.2 M rows of 256 bytes in 163,840 bags: 129 us with the last rows one by one and no slots
+// fetched ahead, 118 this way, 9.1 TB/s of rows).  How deep a burst pays is the rule at FwdLaunch.
 constexpr uint32_t kNoSlot = 0xffffffffu;      // past the end of every cache
 template <int GW, bool BF16, int BURST>
 __global__ __launch_bounds__(kRowBlock) void embbag_fwd_kernel(const uint4* __restrict__ cache_w,
@@ -56,49 +57,6 @@ __global__ __launch_bounds__(kRowBlock) void embbag_fwd_kernel(const uint4* __re
         for (int j = 0; j < BURST; ++j) {       // in lookup order; a row that is not there adds zeros
             Piece<BF16> p;
             p.decode(raw[j]);
-            acc.add(p);
-        }
-    }
-    acc.store_f32_stream(out + bag * dim, c);
-}
-
-// The same sums where wide rows fill the chip many times over and memory is the bound: whole bursts of four, then row by
-// row.  Fewer rows in flight are then the better order for the caches and the pooled rows' stores (the rule in FwdLaunch).
-template <int GW, bool BF16>
-__global__ __launch_bounds__(kRowBlock) void embbag_fwd_saturated_kernel(const uint4* __restrict__ cache_w,
-                                                                         const int32_t* __restrict__ slots,
-                                                                         const int64_t* __restrict__ bag_off, int64_t bags,
-                                                                         int64_t n, int64_t C, int lpr, int64_t wst, int dim,
-                                                                         float* __restrict__ out) {
-    const int64_t bag = ((int64_t)blockIdx.x * kRowBlock + threadIdx.x) / GW;
-    const int c = threadIdx.x % GW;
-    if (bag >= bags || c >= lpr) return;
-    Piece<BF16> acc;
-    acc.zero();
-    int64_t k = bag_off[bag];
-    int64_t end = bag_off[bag + 1];
-    if (k < 0) k = 0;
-    if (end > n) end = n;
-    if (k > end) k = end;
-    for (; k + 4 <= end; k += 4) {              // four independent row loads in flight, added in order
-        uint32_t s[4];
-        uint4 raw[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) s[j] = (uint32_t)slots[k + j];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) raw[j] = s[j] < (uint64_t)C ? cache_w[(int64_t)s[j] * wst + c] : make_uint4(0, 0, 0, 0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            Piece<BF16> p;
-            p.decode(raw[j]);
-            acc.add(p);
-        }
-    }
-    for (; k < end; ++k) {
-        const uint32_t s = (uint32_t)slots[k];
-        if (s < (uint64_t)C) {
-            Piece<BF16> p;
-            p.decode(cache_w[(int64_t)s * wst + c]);
             acc.add(p);
         }
     }
@@ -242,21 +200,15 @@ struct FwdRowsLaunch {
     }
 };
 
-// How many rows of a bag to have in flight (times: whole bursts of four then row by row / bursts of four / of eight; us).
-//   long bags, few lanes     a burst of eight: nothing else hides the rows' latency (f32 dim 64, 4,096 bags of 25: 6.5 /
-//                            6.0 / 5.2).  The mean length has to be 7: at 6 the two bursts are even, and below the guards
-//                            of rows that are not there are the cost (32,768 bags of 1: 3.6 / 3.7 / 4.3).
-//   a launch of 2^18 lanes   bursts of four: from four wavefronts a SIMD on, others hide the latency, and eight rows cost
-//   or more                  registers (bf16 dim 64, 65,536 bags of 25: 28.7 / 27.8 / 29.3).
-//   2^21 lanes, wide rows    memory is the bound, and the row-by-row tail staggers the wavefronts (f32 dim 256, 163,840
-//                            bags of 0 to 16: 183 / 191 / 192; bf16 dim 256, bags of 0 to 4: 47 / 54 / 52).  Short f32 bags
-//                            lose nothing in bursts of four (dim 192, bags of 0 to 6: 66.5 / 64.9 / 65.4), and bf16
-//                            bags of about one lookup, which are all pooled stores, do best in the form with the fewest
-//                            wavefronts on a CU (bf16 dim 512, bags of 1: 95 / 92 / 86).
-constexpr int64_t kLongBag = 7;                             // mean lookups of a bag
-constexpr int64_t kFewThreads = int64_t(1) << 18;           // four wavefronts for every SIMD of the chip
-constexpr int64_t kSaturatedThreads = int64_t(1) << 21;     // 32 of them: four times what the chip holds
-constexpr int kWideDim = 128;
+// How many rows of a bag to have in flight (us in bursts of four / of eight; tables of 2 GB, Zipf rows, bags of 0 to twice
+// the mean, unless stated).  Long bags take eight: nothing else hides the rows' latency in small launches (f32 dim 64, 4,096
+// bags of 25, table in the caches: 6.0 / 5.2), and large ones gain a little (six batches of 163,840
+// bags of 1 to 50, the whole training pass: 2,688 / 2,673).  The mean has to be 6.5: the two are even about there, and below it the guards of rows that are not there are the cost
+// (f32, 32,768 bags of mean 1: dim 64 3.7 / 4.3, dim 256 8.3 / 9.1).  bf16 rows that fill a group of 8 lanes or more take
+// eight also in short bags from 2^20 lanes on, where the pooled stores are the bound and the fewer wavefronts a CU then holds
+// suit them (dim 256, 65,535 bags: 20.7 / 15.2 at a mean of 1, 18.5 / 17.6 at 2, even from there on); rows that leave lanes
+// idle do not (dim 192, mean 1: 11.0 / 13.0).
+constexpr int64_t kManyLanes = int64_t(1) << 20;            // twice what the chip holds
 struct FwdLaunch {
     const bp_config* cfg;
     const void* cache_w;
@@ -276,17 +228,8 @@ struct FwdLaunch {
             return BP_OK;
         }
         const dim3 grid((unsigned)ceil_div(bags * GW, kRowBlock));
-        const bool long_bags = n_lookups >= kLongBag * bags, single = 2 * n_lookups < 3 * bags;
-        bool deep = long_bags && bags * GW < kFewThreads;
-        if constexpr (GW >= 16) {               // narrower rows have dim < 128
-            const bool saturated = cfg->dim >= kWideDim && bags * GW >= kSaturatedThreads;
-            if (saturated && (long_bags || (BF16 && !single))) {
-                BP_LAUNCH(K_FWD, (embbag_fwd_saturated_kernel<GW, BF16>), grid, dim3(kRowBlock), 0, stream, (const uint4*)cache_w,
-                          slots, bag_off, bags, n_lookups, cfg->capacity, lpr, cache_w_stride16(cfg), cfg->dim, out);
-                return BP_OK;
-            }
-            deep = deep || (BF16 && saturated && single);
-        }
+        const bool long_bags = 2 * n_lookups >= 13 * bags;
+        const bool deep = long_bags || (BF16 && GW >= 8 && lpr == GW && bags * GW >= kManyLanes);
         if (deep)
             BP_LAUNCH(K_FWD, (embbag_fwd_kernel<GW, BF16, 8>), grid, dim3(kRowBlock), 0, stream, (const uint4*)cache_w, slots,
                       bag_off, bags, n_lookups, cfg->capacity, lpr, cache_w_stride16(cfg), cfg->dim, out);

@@ -102,13 +102,11 @@ def test_forward_bags_around_the_bursts(bp, D, dtype):
 
 
 @pytest.mark.parametrize("D,dtype,bags,longest", [
-    # launches that leave the chip room: bursts of four for short bags, of eight from a mean of 7 lookups on
-    (4, "f32", 300, 12), (4, "f32", 300, 15), (64, "f32", 300, 3), (64, "f32", 300, 12), (64, "f32", 300, 15),
-    # 2^18 lanes, 16 a bag: long bags in bursts of eight below, of four from there on
-    (64, "f32", 16383, 20), (64, "f32", 16384, 20),
-    # 2^21 lanes and rows of 128 elements or more: fp32 with short bags, with long ones; bf16 with one, few and many lookups
-    (128, "f32", 65535, 15), (128, "f32", 65536, 12), (128, "f32", 65536, 15), (128, "bf16", 131072, 2), (128, "bf16", 131072, 4),
-    (128, "bf16", 131072, 15)])
+    # bursts of four for short bags, of eight from a mean of 6.5 lookups on; rows of one lane, of 16 and of 64
+    (4, "f32", 300, 5), (4, "f32", 300, 12), (4, "f32", 300, 14), (4, "f32", 300, 25), (64, "f32", 300, 3), (64, "f32", 300, 12),
+    (64, "f32", 300, 14), (256, "f32", 300, 12), (512, "bf16", 300, 12), (64, "f32", 65537, 14),
+    # short bags of bf16 rows that fill their lanes: bursts of eight from 2^20 lanes on; rows that do not: of four
+    (64, "bf16", 131071, 4), (64, "bf16", 131072, 4), (512, "bf16", 16384, 2), (96, "bf16", 65536, 4)])
 def test_forward_bags_in_every_form(bp, D, dtype, bags, longest):
     """Bags of 0 to `longest` lookups in turn (mean longest / 2), around the sizes where another form of the pooled forward
     pass is taken; fp32 sums in lookup order bit for bit."""
