@@ -82,8 +82,8 @@ constexpr int kScanBlock = 256;
 // partials few.
 constexpr int64_t kScanSmall = int64_t(1) << 18, kScanMiddle = int64_t(1) << 21;
 inline int scan_rounds(int64_t n) { return n <= kScanSmall ? 1 : n <= kScanMiddle ? 4 : 8; }
-// Up to here pass 2 is left out: the partials are 8 KB at most, read from L2 by every workgroup at once, where the one
-// workgroup of pass 2 is a launch of its own (2.5 to 4 us, with the gaps on both sides).
+// Up to here pass 2 is left out: the partials are 8 KB at most, or 16 KB of 64-bit ones, read from L2 by every workgroup at
+// once, where the one workgroup of pass 2 is a launch of its own (2.5 to 4 us, with the gaps on both sides).
 constexpr int64_t kScanFewTiles = 2048;
 
 template <typename T, typename Op>

@@ -201,13 +201,15 @@ struct FwdRowsLaunch {
 };
 
 // How many rows of a bag to have in flight (us in bursts of four / of eight; tables of 2 GB, Zipf rows, bags of 0 to twice
-// the mean, unless stated).  Long bags take eight: nothing else hides the rows' latency in small launches (f32 dim 64, 4,096
-// bags of 25, table in the caches: 6.0 / 5.2), and large ones gain a little (six batches of 163,840
-// bags of 1 to 50, the whole training pass: 2,688 / 2,673).  The mean has to be 6.5: the two are even about there, and below it the guards of rows that are not there are the cost
-// (f32, 32,768 bags of mean 1: dim 64 3.7 / 4.3, dim 256 8.3 / 9.1).  bf16 rows that fill a group of 8 lanes or more take
-// eight also in short bags from 2^20 lanes on, where the pooled stores are the bound and the fewer wavefronts a CU then holds
-// suit them (dim 256, 65,535 bags: 20.7 / 15.2 at a mean of 1, 18.5 / 17.6 at 2, even from there on); rows that leave lanes
-// idle do not (dim 192, mean 1: 11.0 / 13.0).
+// the mean, unless stated):
+//   long bags take eight.  Nothing else hides the rows' latency in small launches (f32 dim 64, 4,096 bags of 25, table in
+//     the caches: 6.0 / 5.2), and large ones gain a little (a training pass over six batches of 163,840 bags of 1 to 50:
+//     2,688 / 2,673).
+//   short bags take four: at a mean of 6.5 the two are about even, and below it the guards of rows that are not there are
+//     the cost (f32, 32,768 bags of mean 1: dim 64 3.7 / 4.3, dim 256 8.3 / 9.1).
+//   but short bags of bf16 rows that fill a group of 8 lanes or more take eight from 2^20 lanes on (dim 256, 65,535 bags:
+//     20.7 / 15.2 at a mean of 1, 18.5 / 17.6 at 2, even from there on).  Such launches are nearly all pooled stores, and
+//     the deeper form holds fewer wavefronts on a CU; rows that leave lanes idle do not gain (dim 192, mean 1: 11.0 / 13.0).
 constexpr int64_t kManyLanes = int64_t(1) << 20;            // twice what the chip holds
 struct FwdLaunch {
     const bp_config* cfg;

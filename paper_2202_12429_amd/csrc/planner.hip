@@ -1196,9 +1196,11 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
         if (lds_gaps > Lcap - 2) lds_gaps = Lcap - 2;
         if (lds_gaps < 0) lds_gaps = 0;
         const size_t lds_cells = (size_t)(2 + lds_gaps) * T + v_cells;
-        // A workgroup's share of the pairs (about one lookup in four starts one) is large enough to amortise clearing
-        // and flushing its counters: 32 Ki pairs beside a full 48 KiB of them, fewer where the counters are few (a
-        // trace of 50 small batches: one workgroup took 55 us for 40 K pairs).
+        // A workgroup's share of the pairs (about one lookup in four starts one) amortises clearing and flushing its
+        // counters: twice as many pairs as it has counters, so 24 Ki beside a full 48 KiB of them, and 1 Ki at least (a
+        // trace of 50 small batches: one workgroup took 55 us for 40 K pairs).  Shares of 32 Ki whatever the counters:
+        // 30 M spread lookups in 100 batches 186 us for 94 this way, 4 M in 2,000 batches 128 for 100; 85 M skewed
+        // lookups, whose workgroups meet on few counters in memory, 73 for 77.
         const int64_t share = std::min<int64_t>(32 * 1024, std::max<int64_t>(1024, 2 * (int64_t)lds_cells));
         int64_t blocks = ceil_div(N, 4 * share);
         if (blocks > 1024) blocks = 1024;
