@@ -769,8 +769,8 @@ def test_plan_many_batches_wide_group_keys(bp):
 
 @pytest.mark.parametrize("lookahead", [1, 2, 3, 1024, 1025, 1026, 1500])
 def test_plan_lookaheads_around_the_probe_window(bp, lookahead):
-    """1,400 batches of a few rows each, popular ones in nearly every batch: the last use inside the lookahead lies up to
-    1,399 pairs ahead, within the LDS window of the flags kernel (1,024 pairs) and beyond it."""
+    """1,400 batches of a few rows each, popular ones in nearly every batch; lookaheads up to which the flags kernel
+    searches in LDS alone (1,025 at most) and beyond.  No row has enough pairs for a probe outside LDS: the next test."""
     say(f"plan with lookahead {lookahead}")
     rng = np.random.default_rng(lookahead)
     T, R = 1400, 40
@@ -778,6 +778,41 @@ def test_plan_lookaheads_around_the_probe_window(bp, lookahead):
     off[1:] = np.cumsum(rng.integers(1, 9, size=T))
     ids = np.minimum(rng.zipf(1.4, size=int(off[-1])) - 1, R - 1).astype(np.int64)
     plan_both(bp, ids, off, R, lookahead, 64)
+
+
+def probes_outside_the_window(ids, off, L_eff):
+    """The flags kernel's search for every pair's TTL, replayed: how many of its probes lie past the 2,049 words (the pair
+    before the workgroup's 1,024, those, and the 1,024 behind them) that the workgroup holds in LDS."""
+    batch = np.repeat(np.arange(len(off) - 1), np.diff(off))
+    pairs = np.unique(ids * len(off) + batch)
+    g, i = pairs // len(off), pairs % len(off)
+    q = np.arange(len(pairs))
+    keep = np.zeros(len(pairs), bool)
+    keep[:-1] = (g[1:] == g[:-1]) & (i[1:] - i[:-1] < L_eff)
+    bound = g * len(off) + np.minimum(i + L_eff - 1, len(off) - 1)
+    lo, hi, outside = q.copy(), np.minimum(q + L_eff - 1, len(pairs) - 1), 0
+    while True:
+        on = keep & (lo < hi)
+        if not on.any():
+            return outside
+        mid = (lo + hi + 1) // 2
+        outside += int((on & (mid - (q // 1024 * 1024 - 1) >= 2049)).sum())
+        up = pairs[mid] <= bound
+        lo, hi = np.where(on & up, mid, lo), np.where(on & ~up, mid - 1, hi)
+
+
+def test_plan_probes_outside_the_window(bp):
+    """Three rows in 2,600 batches, the most popular in nearly all of them, lookahead beyond the trace: the search for a
+    pair's last use probes up to 2,000 pairs ahead, past what the workgroup holds in LDS."""
+    say("plan with probes outside the LDS window")
+    rng = np.random.default_rng(2600)
+    T, R = 2600, 3
+    off = np.zeros(T + 1, dtype=np.int64)
+    off[1:] = np.cumsum(rng.integers(1, 9, size=T))
+    ids = np.minimum(rng.zipf(3.0, size=int(off[-1])) - 1, R - 1).astype(np.int64)
+    got, _ = plan_both(bp, ids, off, R, 2600, 64)
+    assert got.L_eff > 1025
+    assert probes_outside_the_window(ids, off, got.L_eff) > 5000
 
 
 def test_plan_errors(bp):
