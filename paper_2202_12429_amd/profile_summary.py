@@ -55,12 +55,12 @@ def stats_summary(directory: str, prefix: str) -> str:
         k = short_kernel_name(r["Kernel_Name"])
         if k:
             dur[k].append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
-    w = max([74] + [len(k) + 2 for k in dur])
+    wide = max([74] + [len(k) + 2 for k in dur])
     lines = [f"{DIGEST_TAG} {kernel_source_digest()}",
-             f"{'kernel':{w}s} {'calls':>7s} {'avg_us':>9s} {'median_us':>9s} {'min_us':>9s} {'max_us':>9s} {'total_ms':>9s}"]
+             f"{'kernel':{wide}s} {'calls':>7s} {'avg_us':>9s} {'median_us':>9s} {'min_us':>9s} {'max_us':>9s} {'total_ms':>9s}"]
     for k in sorted(dur, key=lambda k: -sum(dur[k])):
         d = dur[k]
-        lines.append(f"{k:{w}s} {len(d):7d} {statistics.mean(d):9.2f} {statistics.median(d):9.2f} {min(d):9.2f} "
+        lines.append(f"{k:{wide}s} {len(d):7d} {statistics.mean(d):9.2f} {statistics.median(d):9.2f} {min(d):9.2f} "
                      f"{max(d):9.2f} {sum(d) / 1e3:9.3f}")
     return "\n".join(lines)
 
@@ -79,7 +79,7 @@ def pmc_summary(directory: str) -> str:
                 out[k].append(float(r["Counter_Value"]))
         return out
     F, W = load("FETCH_SIZE"), load("WRITE_SIZE")
-    w = max([62] + [len(k) + 2 for k in F])
+    wide = max([62] + [len(k) + 2 for k in F])
     true_kib = 2 ** 30 / 1024
     cf, cw = statistics.mean(F["copy_calibration_kernel"]), statistics.mean(W["copy_calibration_kernel"])
     kf, kw = true_kib / cf, true_kib / cw
@@ -87,12 +87,12 @@ def pmc_summary(directory: str) -> str:
              f"copy_calibration_kernel (1 GiB read, 1 GiB written): FETCH_SIZE {cf:.1f}  WRITE_SIZE {cw:.1f}  "
              f"(true: {true_kib:.0f} KiB each)",
              f"scale factors: fetch x{kf:.4f}, write x{kw:.4f}",
-             f"{'kernel':{w}s} {'n':>5s} {'FETCH_SIZE':>12s} {'WRITE_SIZE':>12s} {'fetch MB':>10s} {'write MB':>10s} {'total MB':>10s}"]
+             f"{'kernel':{wide}s} {'n':>5s} {'FETCH_SIZE':>12s} {'WRITE_SIZE':>12s} {'fetch MB':>10s} {'write MB':>10s} {'total MB':>10s}"]
     traffic = []
     for k in sorted(F, key=lambda k: -sum(F[k])):
         f, w = statistics.mean(F[k]), statistics.mean(W.get(k, [0.0]))
         fm, wm = f * kf * 1024 / 1e6, w * kw * 1024 / 1e6
-        lines.append(f"{k:{w}s} {len(F[k]):5d} {f:12.1f} {w:12.1f} {fm:10.2f} {wm:10.2f} {fm + wm:10.2f}")
+        lines.append(f"{k:{wide}s} {len(F[k]):5d} {f:12.1f} {w:12.1f} {fm:10.2f} {wm:10.2f} {fm + wm:10.2f}")
         traffic.append(f"{TRAFFIC_TAG} {k.split('<')[0]} {(fm + wm) * 1e6:.0f}")
     return "\n".join(lines + [""] + traffic)
 

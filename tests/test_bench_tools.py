@@ -69,3 +69,19 @@ def test_stats_and_pmc_summaries(tmp_path):
     # fetch counts half the bytes (x2), write all of them: (2 * 60000 + 30000) KiB
     assert traffic["bwd_rows_kernel"] == (2 * 60000 + 30000) * 1024
     assert ps.read_traffic(str(tmp_path / "absent.txt")) == (None, {})
+
+
+def test_pmc_summary_keeps_names_and_scales_by_the_copy_kernel(tmp_path):
+    """Counters in KiB a dispatch, scaled by what they read for a copy of 1 GiB; kernel names whole."""
+    from paper_2202_12429_amd import profile_summary
+    long_name = "void bp::(anonymous namespace)::scan_apply_kernel<4, false, unsigned int, bp::AddOp, bp::RowMaskIn, bp::StoreExclusiveU32>(int)"
+    for counter, copied in (("FETCH_SIZE", 524288), ("WRITE_SIZE", 1048576)):
+        (tmp_path / f"pmc_{counter}_counter_collection.csv").write_text(
+            f'Kernel_Name,Counter_Value\n"void bp::copy_calibration_kernel(int)",{copied}\n"{long_name}",1000.5\n')
+    text = profile_summary.pmc_summary(str(tmp_path))
+    row = next(l for l in text.splitlines() if l.startswith("scan_apply_kernel"))
+    assert row.startswith("scan_apply_kernel<4, false, u32, AddOp, RowMaskIn, StoreExclusiveU32> ")
+    assert [float(x) for x in row.split()[-6:]] == [1, 1000.5, 1000.5, 2.05, 1.02, 3.07]
+    (tmp_path / "summary.txt").write_text(text)
+    digest, traffic = profile_summary.read_traffic(str(tmp_path / "summary.txt"))
+    assert digest == profile_summary.kernel_source_digest() and traffic["scan_apply_kernel"] == round(3 * 1000.5 * 1024)
