@@ -195,10 +195,11 @@ def _span(t, a: int, b: int):
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
-        # the number alone, where this torch has these calls: a Stream object costs the host more than the call itself
-        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
-        if raw is not None and device is not None and torch.cuda.is_initialized():
-            return raw(device()) or None
+        if torch.cuda.is_initialized():
+            try:                             # the number alone: a Stream object costs the host more than the call itself
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+            except AttributeError:           # a torch without these calls
+                pass
         return torch.cuda.current_stream().cuda_stream or None
     if isinstance(stream, int):
         return stream or None
