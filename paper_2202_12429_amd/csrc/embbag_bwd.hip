@@ -414,7 +414,6 @@ struct RowRecordOut {
 };
 
 // ---- workspace -------------------------------------------------------------------------------
-constexpr int kSmallIPT = 4, kLargeIPT = 16;
 constexpr int64_t kLargeSort = int64_t(1) << 21;
 
 struct ReduceScratch {      // what the reduce kernel itself needs, in both entry points
@@ -446,7 +445,7 @@ BwdWorkspace carve_bwd(void* base, size_t cap, int64_t n, int dim) {
     w.keys_b = c.take<uint32_t>(m);
     w.vals_a = c.take<uint32_t>(m);
     w.vals_b = c.take<uint32_t>(m);
-    w.sort_temp = c.take<uint32_t>(n >= kLargeSort ? sort_temp_words<kLargeIPT>(n) : sort_temp_words<kSmallIPT>(n));
+    w.sort_temp = c.take<uint32_t>(n >= kLargeSort ? sort_temp_words<LargeTiles>(n) : sort_temp_words<SmallTiles>(n));
     w.row_pos = c.take<uint32_t>(m);
     w.scan_partials32 = c.take<uint32_t>(scan_partials(n));
     w.scan_partials64 = c.take<uint64_t>(scan_partials(n));
@@ -537,10 +536,10 @@ BP_EXPORT int bp_embbag_bwd_update(const bp_config* cfg, void* cache_w, void* ca
     bool in_b = false;
     const int key_bits = bits_for(cfg->capacity + 1);
     if (n >= kLargeSort)
-        BP_TRY((radix_sort_pairs<uint32_t, kLargeIPT>(w.keys_a, w.keys_b, w.vals_a, w.vals_b, n, 0, key_bits, w.sort_temp,
+        BP_TRY((radix_sort_pairs<uint32_t, LargeTiles>(w.keys_a, w.keys_b, w.vals_a, w.vals_b, n, 0, key_bits, w.sort_temp,
                                                       stream, &in_b)));
     else
-        BP_TRY((radix_sort_pairs<uint32_t, kSmallIPT>(w.keys_a, w.keys_b, w.vals_a, w.vals_b, n, 0, key_bits, w.sort_temp,
+        BP_TRY((radix_sort_pairs<uint32_t, SmallTiles>(w.keys_a, w.keys_b, w.vals_a, w.vals_b, n, 0, key_bits, w.sort_temp,
                                                       stream, &in_b)));
     const uint32_t* skeys = in_b ? w.keys_b : w.keys_a;
     const uint32_t* sbags = in_b ? w.vals_b : w.vals_a;

@@ -10,10 +10,10 @@
 //   1. one 64-bit word per lookup, (id | batch | place inside the batch), made by the first pass of a stable LSD
 //      radix sort on the id bits as it reads the caller's ids (the input is batch-major, so equal ids stay in batch
 //      and lookup order)
-//   2. head flags + scan  -> unique pairs (sorted by id, then batch), pair index of every lookup
+//   2. pair starts as bit masks, numbered -> unique pairs (sorted by id, then batch)
 //   3. histogram H[gap][batch] and per-batch unique counts -> occupancy for every candidate lookahead
 //      -> L_eff = largest lookahead whose peak occupancy fits the capacity
-//   4. per-pair flags (miss / evict), TTL, and the pair that fetched the row (max-scan of miss indices)
+//   4. per-pair flags (miss / evict), TTL; the misses as bit masks, from which the pair that fetched a row is read
 //   5. regroup pairs by batch (stable sort on the batch bits) -> lists ascending in id inside a batch,
 //      miss / evict ordinals by one packed scan
 //   6. FIFO free ring without a walk over batches: the x-th miss takes ring position x; positions below
@@ -35,14 +35,16 @@
 namespace bp {
 namespace {
 
-// Elements per thread of the plan's sorts: tiles of 4096 keys, or of 1024 where 4096 would leave most of the CUs
-// without one (102,400 lookups: 25 tiles and 11 to 14 us a scatter, 100 tiles and 5 to 6 us).
-constexpr int kPlanSortIPT = 16, kPlanSmallIPT = 4;
-constexpr int64_t kPlanSmallSort = int64_t(1) << 18;
-template <typename F>
-int with_plan_ipt(int64_t n_lookups, F&& f) {
-    if (n_lookups <= kPlanSmallSort) return f(std::integral_constant<int, kPlanSmallIPT>{});
-    return f(std::integral_constant<int, kPlanSortIPT>{});
+// Tiles of the plan's sorts: of 4096 words, or of 1024 where 4096 would leave most of the CUs without one (102,400 lookups:
+// 25 tiles and 11 to 14 us a scatter, 100 tiles and 5 to 6 us), or, for words alone, of 8192 from 2^24 on
+// (whole plans, us in tiles of 4096 / 8192: 6.8 M lookups 534 / 540, 13.6 M 743 / 757, 20.4 M 1,009 / 979, 85 M 3,489 / 3,311).
+constexpr int64_t kPlanSmallSort = int64_t(1) << 18, kPlanWideSort = int64_t(1) << 24;
+template <bool VALS, typename F>
+int with_plan_tiles(int64_t n_lookups, F&& f) {
+    if (n_lookups <= kPlanSmallSort) return f(SmallTiles{});
+    if constexpr (!VALS)
+        if (n_lookups >= kPlanWideSort) return f(WideTiles{});
+    return f(LargeTiles{});
 }
 constexpr int kBlock = 256;
 constexpr uint32_t kGapInf = 0x7fffffffu;
@@ -103,137 +105,234 @@ struct PlanKeySource {
     int64_t R;
     PlanScalars* sc;
     typedef int64_t Raw;
-    __device__ __forceinline__ int64_t load(uint32_t i) const {
-        return *((int64_t)i < first ? resident_ids + i : ids + ((int64_t)i - first));
+    static constexpr bool kLate = false;
+    template <bool PLAIN>
+    __device__ __forceinline__ int64_t load(int64_t i) const {
+        return *(!PLAIN && i < first ? resident_ids + i : ids + (i - first));
     }
+    // Nearly every stretch lies in one batch, whose number and offset then are scalars.
     struct Cursor {
         const PlanKeySource& s;
-        int b;                     // batch of the last element asked for
-        int64_t lo, hi;            // its stretch
-        __device__ __forceinline__ Cursor(const PlanKeySource& src, uint32_t i) : s(src) {
-            b = s.where.find((int64_t)i);
-            lo = s.where.iter_off[b];
-            hi = s.where.iter_off[b + 1];
+        int b;                     // batch of the stretch's first element, or of the last element asked for
+        uint32_t lo, hi;           // its positions, which fit 32 bits like the number of lookups
+        bool one;                  // the stretch ends in it too, and none of it is a carried row
+        bool bad;                  // an id was out of range
+        __device__ __forceinline__ Cursor(const PlanKeySource& src, int64_t from, int64_t end) : s(src), bad(false) {
+            b = s.where.find(from);
+            lo = (uint32_t)s.where.iter_off[b];
+            hi = (uint32_t)s.where.iter_off[b + 1];
+            one = end <= (int64_t)hi && from >= s.first;
         }
-        __device__ __forceinline__ uint64_t key(uint32_t i, int64_t g) {
-            while ((int64_t)i >= hi && b + 1 < s.where.T) {      // elements are asked for in ascending order
-                ++b;
-                lo = hi;
-                hi = s.where.iter_off[b + 1];
+        __device__ __forceinline__ bool plain() const { return one; }
+        template <bool PLAIN>
+        __device__ __forceinline__ uint64_t key(int64_t i, int64_t g) {
+            const bool in = (uint64_t)g < (uint64_t)s.R;
+            bad |= !in;
+            g = in ? g : 0;
+            if constexpr (!PLAIN) {
+                while ((uint32_t)i >= hi && b + 1 < s.where.T) {           // elements are asked for in ascending order
+                    ++b;
+                    lo = hi;
+                    hi = (uint32_t)s.where.iter_off[b + 1];
+                }
             }
-            if (g < 0 || g >= s.R) {
-                atomicOr(&s.sc->error_flags, 1u);
-                g = 0;
-            }
-            return ((uint64_t)g << (s.ib + s.pb)) | ((uint64_t)b << s.pb) | (uint64_t)((int64_t)i - lo);
+            return ((uint64_t)g << (s.ib + s.pb)) | ((uint64_t)(uint32_t)b << s.pb) | (uint64_t)((uint32_t)i - lo);
         }
+        __device__ __forceinline__ void done() const {
+            if (bad) atomicOr(&s.sc->error_flags, 1u);
+        }
+    };
+};
+// The same for the first histogram, which counts id bits alone and asks nothing else of the word.
+struct PlanIdSource {
+    PlanKeySource of;
+    typedef int64_t Raw;
+    template <bool PLAIN>
+    __device__ __forceinline__ int64_t load(int64_t i) const { return of.load<PLAIN>(i); }
+    struct Cursor {
+        const PlanKeySource& s;
+        __device__ __forceinline__ Cursor(const PlanIdSource& src, int64_t, int64_t) : s(src.of) {}
+        __device__ __forceinline__ bool plain() const { return true; }
+        template <bool PLAIN>
+        __device__ __forceinline__ uint64_t key(int64_t, int64_t g) const {
+            return (uint64_t)((uint64_t)g < (uint64_t)s.R ? g : 0) << (s.ib + s.pb);
+        }
+        __device__ __forceinline__ void done() const {}
     };
 };
 
 // ---- 2. unique pairs -------------------------------------------------------------------------
-struct HeadFlagIn {
-    const uint64_t* keys;
-    int pb;
-    __device__ __forceinline__ uint32_t operator()(int64_t p) const {
-        return (p == 0 || (keys[p] >> pb) != (keys[p - 1] >> pb)) ? 1u : 0u;
-    }
+// A pair starts where (id, batch) changes among the sorted words.  These starts are kept as bit masks, 64 lookups a word,
+// and a scan over the words (population counts) leaves the pairs before every one of them.  Whoever walks the
+// sorted lookups 64 at a time has the pair of each from twelve bytes that all lanes share, where a pair number per lookup
+// would be 256 bytes to write and to read (85 M lookups: the pass that wrote them 283 us, the regrouping scatter that reads
+// them and the slots behind them 494; with the masks 87, and 330 in tiles of the same size).
+struct MaskCountIn {
+    const uint64_t* mask;
+    __device__ __forceinline__ uint32_t operator()(int64_t w) const { return (uint32_t)__popcll(mask[w]); }
 };
-struct PairOut {
-    const uint64_t* keys;
-    int pb;
-    uint64_t* ukey;           // (id << ib) | batch of every pair
-    uint32_t* uq;
-    uint32_t* pair_start;     // where the pair's lookups begin in the sorted order
-    __device__ __forceinline__ void operator()(int64_t p, uint32_t exc, uint32_t inc) const {
-        uq[p] = inc - 1u;
-        if (inc != exc) {
-            ukey[exc] = keys[p] >> pb;
-            pair_start[exc] = (uint32_t)p;
-        }
+struct StoreExclusiveU32 {
+    uint32_t* p;
+    __device__ __forceinline__ void operator()(int64_t i, uint32_t exc, uint32_t) const { p[i] = exc; }
+};
+struct PairOfLookup {
+    const uint64_t* head_mask;
+    const uint32_t* before;        // pairs that start before the word's first lookup
+    // pair of lookup 64 * word + lane; `word` is the same in every lane
+    __device__ __forceinline__ uint32_t operator()(int64_t word) const {
+        const uint64_t m = head_mask[word];
+        const uint32_t first = before[word] + ((uint32_t)m & 1u) - 1u;      // starts at or below a lane: bit 0, and bits 1 ..
+        return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 33), __builtin_amdgcn_mbcnt_lo((uint32_t)(m >> 1), first));
     }
 };
 
-// With the grouping asked for, the regrouping sort at the end of the plan reads these same sorted words for its first
-// histogram (the batch bits).  One kernel then makes both: a workgroup takes one tile of that sort, which is a whole
-// number of the scan's tiles, counts the heads of each of them (what scan_reduce_kernel would leave in `partials`)
-// and the tile's batch digits (what sort_upsweep_kernel would leave in `counts`).  Elements are dealt to lanes as in
-// the scan, so a lane's left neighbour is the lane below it, the round before, or one word fetched per wavefront.
-template <int RB, int IPT, int ROUNDS>
-__global__ __launch_bounds__(kSortBlock) void plan_head_hist_kernel(const uint64_t* __restrict__ keys, uint32_t n, int pb,
-                                                                    uint32_t* __restrict__ partials, uint32_t scan_tiles,
-                                                                    uint32_t mask, uint32_t* __restrict__ counts,
-                                                                    uint32_t ntiles) {
+// The start masks.  With the grouping asked for (HIST), the regrouping sort at the end of the plan reads these same words for
+// its first histogram (the batch bits), and this kernel makes that too: a workgroup takes one tile of that sort and counts
+// its digits as sort_upsweep_kernel would.
+template <int RB, typename Tiles, bool HIST>
+__global__ __launch_bounds__(Tiles::BLOCK) void plan_heads_kernel(const uint64_t* __restrict__ keys, uint32_t n, int pb,
+                                                                uint64_t* __restrict__ head_mask, uint32_t mask,
+                                                                uint32_t* __restrict__ counts, uint32_t ntiles) {
     constexpr int RADIX = 1 << RB;
-    constexpr int TILE = kSortBlock * IPT;
-    constexpr int SCAN_TILE = kScanBlock * ROUNDS;
-    constexpr int PARTS = TILE / SCAN_TILE;
-    constexpr int WAVES = kSortBlock / kWave;
-    static_assert(kSortBlock == kScanBlock && TILE % SCAN_TILE == 0, "a tile of the sort is a whole number of scan tiles");
-    __shared__ uint32_t hist[RADIX];
-    __shared__ uint32_t wave_tot[PARTS][WAVES];
+    constexpr int IPT = Tiles::IPT, BLOCK = Tiles::BLOCK, TILE = Tiles::TILE;
+    static_assert(IPT <= kWave, "a lane holds one of its wavefront's mask words");
+    __shared__ uint32_t hist[HIST ? RADIX : 1];
     const uint32_t tile = sort_tile_of_block(ntiles);
     if (tile >= ntiles) return;
-    const int w = threadIdx.x / kWave, lane = lane_id();
-    for (int d = threadIdx.x; d < RADIX; d += kSortBlock) hist[d] = 0;
-    __syncthreads();
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
+    if constexpr (HIST) {
+        for (int d = threadIdx.x; d < RADIX; d += BLOCK) hist[d] = 0;
+        __syncthreads();
+    }
+    const int64_t first = (int64_t)tile * TILE + w * (kWave * IPT);          // of this wavefront
+    if (first < (int64_t)n) {                                                // uniform
+        uint64_t k[IPT];
 #pragma unroll
-    for (int h = 0; h < PARTS; ++h) {
-        const int64_t first = (int64_t)tile * TILE + h * SCAN_TILE + w * (kWave * ROUNDS);      // of this wavefront
-        uint64_t k[ROUNDS];
-#pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) {
+        for (int r = 0; r < IPT; ++r) {
             const int64_t i = first + r * kWave + lane;
-            k[r] = i < (int64_t)n ? keys[i] : 0;
+            k[r] = keys[i < (int64_t)n ? i : (int64_t)n - 1];
         }
-        uint64_t before = first > 0 && first <= (int64_t)n ? keys[first - 1] : 0;               // left of lane 0, round 0
-        uint32_t heads = 0;
+        uint64_t before = first > 0 ? keys[first - 1] : ~keys[0];            // left of lane 0, round 0
+        uint64_t starts = 0;
 #pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) {
-            const int64_t i = first + r * kWave + lane;
-            uint64_t left = __shfl_up(k[r], 1, kWave);
-            if (lane == 0) left = before;
-            before = __shfl(k[r], kWave - 1, kWave);
-            if (i < (int64_t)n) {
-                heads += (i == 0 || (k[r] >> pb) != (left >> pb)) ? 1u : 0u;
-                // as in sort_upsweep_kernel: the lanes that share the first active lane's digit count themselves at once
-                const uint32_t d = (uint32_t)(k[r] >> pb) & mask;
-                const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
-                const uint64_t same = __ballot(d == d0);
-                if (d != d0) atomicAdd(&hist[d], 1u);
-                else if ((same & lanemask_lt()) == 0) atomicAdd(&hist[d0], (uint32_t)__popcll(same));
+        for (int r = 0; r < IPT; ++r) {
+            const bool in = first + r * kWave + lane < (int64_t)n;
+            const uint64_t left = lane_below(k[r], before);
+            before = lane_value(k[r], kWave - 1);
+            const uint64_t m = __ballot(in && ((k[r] ^ left) >> pb) != 0);
+            if (lane == r) starts = m;
+            if constexpr (HIST) {
+                if (in) count_digit(hist, (uint32_t)(k[r] >> pb) & mask);
             }
         }
-        heads = wave_reduce(heads, AddOp());
-        if (lane == 0) wave_tot[h][w] = heads;
+        if (lane < IPT && first + lane * kWave < (int64_t)n) head_mask[first / kWave + lane] = starts;
     }
-    __syncthreads();
-    if (threadIdx.x < PARTS) {
-        const uint32_t st = tile * PARTS + threadIdx.x;
-        uint32_t total = 0;
-#pragma unroll
-        for (int i = 0; i < WAVES; ++i) total += wave_tot[threadIdx.x][i];
-        if (st < scan_tiles) partials[st] = total;
+    if constexpr (HIST) {
+        __syncthreads();
+        for (int d = threadIdx.x; d < RADIX; d += BLOCK) counts[(size_t)d * ntiles + tile] = hist[d];
     }
-    for (int d = threadIdx.x; d < RADIX; d += kSortBlock) counts[(size_t)d * ntiles + tile] = hist[d];
 }
 
-template <int IPT, int ROUNDS>
-int launch_head_hist(const uint64_t* skeys, int64_t N, int pb, uint32_t* partials, int bits, uint32_t* counts, hipStream_t stream) {
-    const uint32_t ntiles = sort_num_tiles<IPT>(N), mask = (1u << bits) - 1u, scan_tiles = (uint32_t)scan_num_tiles(N);
-    if (bits > 8)
-        BP_LAUNCH(K_SCAN_REDUCE, (plan_head_hist_kernel<9, IPT, ROUNDS>), dim3(sort_grid(ntiles)), dim3(kSortBlock), 0, stream, skeys,
-                  (uint32_t)N, pb, partials, scan_tiles, mask, counts, ntiles);
+template <typename Tiles>
+int plan_heads(const uint64_t* skeys, int64_t N, int pb, uint64_t* head_mask, int bits, uint32_t* counts, hipStream_t stream) {
+    const uint32_t ntiles = sort_num_tiles<Tiles>(N), mask = (1u << bits) - 1u;
+    const dim3 grid(sort_grid(ntiles)), block(Tiles::BLOCK);
+    if (!counts)
+        BP_LAUNCH(K_PLAN_PAIRS, (plan_heads_kernel<8, Tiles, false>), grid, block, 0, stream, skeys, (uint32_t)N, pb, head_mask, 0u,
+                  (uint32_t*)nullptr, ntiles);
+    else if (bits > 8)
+        BP_LAUNCH(K_PLAN_PAIRS, (plan_heads_kernel<9, Tiles, true>), grid, block, 0, stream, skeys, (uint32_t)N, pb, head_mask, mask,
+                  counts, ntiles);
     else
-        BP_LAUNCH(K_SCAN_REDUCE, (plan_head_hist_kernel<8, IPT, ROUNDS>), dim3(sort_grid(ntiles)), dim3(kSortBlock), 0, stream, skeys,
-                  (uint32_t)N, pb, partials, scan_tiles, mask, counts, ntiles);
+        BP_LAUNCH(K_PLAN_PAIRS, (plan_heads_kernel<8, Tiles, true>), grid, block, 0, stream, skeys, (uint32_t)N, pb, head_mask, mask,
+                  counts, ntiles);
     return BP_OK;
 }
-int plan_head_hist(const uint64_t* skeys, int64_t N, int pb, uint32_t* partials, int bits, uint32_t* counts, hipStream_t stream) {
-    static_assert(kPlanSmallSort == kScanSmall, "one length of input decides both tiles");
-    if (N <= kPlanSmallSort) return launch_head_hist<kPlanSmallIPT, 1>(skeys, N, pb, partials, bits, counts, stream);
-    if (scan_rounds(N) == 4) return launch_head_hist<kPlanSortIPT, 4>(skeys, N, pb, partials, bits, counts, stream);
-    return launch_head_hist<kPlanSortIPT, 8>(skeys, N, pb, partials, bits, counts, stream);
+
+// Set bits of such masks, numbered: a wavefront takes kExpandWords words, asks for what the set bits need, all of it together,
+// and writes it side by side behind the bits before.  emit.load(at) for set bit `at`, then emit.store(number, at, loaded).
+// SELF: no scan has run; every workgroup adds up the words before its own, leaves the sums in `before`, and the last one the
+// grand total in *total.  That is for few words, where the scan's two launches cost more (a plan of
+// 102,400 lookups, both uses: 325 -> 299 us).
+constexpr int kExpandWords = 8;
+constexpr int64_t kExpandSelf = 4096;      // words: 32 KB, read from L2 by up to 128 workgroups
+template <typename Emit, bool SELF>
+__global__ __launch_bounds__(kBlock) void expand_masks_kernel(const uint64_t* __restrict__ mask, uint32_t* before, int64_t n_words,
+                                                              uint32_t* __restrict__ total, Emit emit) {
+    constexpr int WAVES = kBlock / kWave;
+    const int lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t w0 = ((int64_t)blockIdx.x * WAVES + w) * kExpandWords;
+    uint64_t m[kExpandWords];
+#pragma unroll
+    for (int u = 0; u < kExpandWords; ++u) m[u] = w0 + u < n_words ? mask[w0 + u] : 0;
+    typename Emit::Loaded got[kExpandWords];
+#pragma unroll
+    for (int u = 0; u < kExpandWords; ++u)
+        if ((m[u] >> lane) & 1u) got[u] = emit.load((w0 + u) * kWave + lane);
+    uint32_t at[kExpandWords];
+    if constexpr (SELF) {
+        __shared__ uint32_t sums[2][WAVES];
+        uint32_t ahead = 0, mine = 0;
+        for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x * (WAVES * kExpandWords); t += kBlock) ahead += (uint32_t)__popcll(mask[t]);
+#pragma unroll
+        for (int u = 0; u < kExpandWords; ++u) mine += (uint32_t)__popcll(m[u]);
+        ahead = wave_reduce(ahead, AddOp());
+        if (lane == 0) {
+            sums[0][w] = ahead;
+            sums[1][w] = mine;
+        }
+        __syncthreads();
+        uint32_t run = 0;
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) run += sums[0][k] + (k < w ? sums[1][k] : 0u);
+#pragma unroll
+        for (int u = 0; u < kExpandWords; ++u) {
+            at[u] = run;
+            if (lane == 0 && w0 + u < n_words) before[w0 + u] = run;
+            run += (uint32_t)__popcll(m[u]);
+        }
+        if (lane == 0 && w == WAVES - 1 && blockIdx.x == gridDim.x - 1) *total = run;
+    } else {
+#pragma unroll
+        for (int u = 0; u < kExpandWords; ++u) at[u] = w0 + u < n_words ? before[w0 + u] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < kExpandWords; ++u)
+        if ((m[u] >> lane) & 1u)
+            emit.store(__builtin_amdgcn_mbcnt_hi((uint32_t)(m[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[u], at[u])),
+                       (w0 + u) * kWave + lane, got[u]);
 }
+// *total: where the number of set bits is found afterwards.
+template <typename Emit>
+int expand_masks(KernelId id, const uint64_t* mask, uint32_t* before, int64_t n_words, uint32_t* partials, const uint32_t** total,
+                 const Emit& emit, hipStream_t stream) {
+    const dim3 grid((unsigned)ceil_div(n_words, (int64_t)kExpandWords * (kBlock / kWave)));
+    if (n_words <= kExpandSelf) {
+        *total = partials;
+        BP_LAUNCH(id, (expand_masks_kernel<Emit, true>), grid, dim3(kBlock), 0, stream, mask, before, n_words, partials, emit);
+        return BP_OK;
+    }
+    BP_TRY((device_scan<uint32_t, AddOp, MaskCountIn, StoreExclusiveU32>(MaskCountIn{mask}, StoreExclusiveU32{before}, n_words,
+                                                                         partials, AddOp(), 0u, stream)));
+    *total = partials + scan_num_tiles(n_words);
+    BP_LAUNCH(id, (expand_masks_kernel<Emit, false>), grid, dim3(kBlock), 0, stream, mask, before, n_words, (uint32_t*)nullptr, emit);
+    return BP_OK;
+}
+
+// The pairs themselves.  Lines of sorted words without a start are not read.
+struct EmitPair {
+    const uint64_t* keys;
+    int pb;
+    uint64_t* ukey;            // (id << ib) | batch of every pair
+    uint32_t* pair_start;      // where its lookups begin in the sorted order, or NULL
+    typedef uint64_t Loaded;
+    __device__ __forceinline__ uint64_t load(int64_t at) const { return keys[at]; }
+    __device__ __forceinline__ void store(uint32_t q, int64_t at, uint64_t k) const {
+        ukey[q] = k >> pb;
+        if (pair_start) pair_start[q] = (uint32_t)at;
+    }
+};
 
 // ---- 3. gaps, histogram, occupancy -----------------------------------------------------------
 __device__ __forceinline__ uint32_t pair_gap(const uint64_t* ukey, uint32_t q, uint32_t M, int ib, uint64_t imask) {
@@ -242,12 +341,15 @@ __device__ __forceinline__ uint32_t pair_gap(const uint64_t* ukey, uint32_t q, u
     return (a >> ib) == (b >> ib) ? (uint32_t)((b & imask) - (a & imask)) : kGapInf;
 }
 
+// The counters of a workgroup fill a third of a CU's LDS: eight wavefronts on them, not four, and the neighbours' keys from the lanes
+// beside instead of two more loads (19.5 M pairs: 125 -> 104 us).
+constexpr int kHistBlock = 512;
 // Each workgroup walks a contiguous stretch of pairs and keeps its counts in LDS: the per-batch unique counts and
 // the histogram rows of the small gaps [2, 2 + lds_gaps), which take nearly all the hits; larger gaps go to global
 // atomics.  Integer atomics only: the sums do not depend on the order.
 // The number of pairs is read from the device (the host has not fetched it yet: it comes back together with the
 // lookahead, in one synchronisation instead of two); the grid is sized for the lookups, an upper bound.
-__global__ __launch_bounds__(kBlock) void plan_hist_kernel(const uint64_t* __restrict__ ukey,
+__global__ __launch_bounds__(kHistBlock) void plan_hist_kernel(const uint64_t* __restrict__ ukey,
                                                            const uint32_t* __restrict__ n_pairs, int ib, int T,
                                                            int Lcap, int lds_gaps,
                                                            uint32_t* __restrict__ H, uint32_t* __restrict__ ucount,
@@ -265,26 +367,33 @@ __global__ __launch_bounds__(kBlock) void plan_hist_kernel(const uint64_t* __res
     uint32_t* v_count = v_in_lds ? lds + 2 * T : V;
     uint32_t* lds_h = lds + 2 * T + v_cells;
     const int cells = (2 + lds_gaps) * T + v_cells;
-    for (int i = threadIdx.x; i < cells; i += kBlock) lds[i] = 0;
+    for (int i = threadIdx.x; i < cells; i += kHistBlock) lds[i] = 0;
     __syncthreads();
     const uint64_t imask = (uint64_t(1) << ib) - 1;
     const uint64_t begin = (uint64_t)blockIdx.x * per_block;
     const uint64_t end = begin + per_block < M ? begin + per_block : M;
-    // four pairs per thread and round, their keys and both neighbours' requested before any of them is counted
+    // four pairs per thread and round, requested before any of them is counted; the neighbours' keys come from the lanes
+    // beside, and for a wavefront's outer lanes from two more words
     constexpr int kPairsInFlight = 4;
-    for (uint64_t q0 = begin + threadIdx.x; q0 < end; q0 += kBlock * kPairsInFlight) {
+    const int lane = lane_id();
+    const uint64_t of_wave = begin + (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave) * kWave;
+    for (uint64_t q0 = of_wave + lane, w0 = of_wave; w0 < end; q0 += kHistBlock * kPairsInFlight, w0 += kHistBlock * kPairsInFlight) {
         uint64_t key[kPairsInFlight], prev[kPairsInFlight], next[kPairsInFlight];
 #pragma unroll
         for (int r = 0; r < kPairsInFlight; ++r) {
-            const uint64_t q = q0 + (uint64_t)r * kBlock;
-            const bool in = q < end;
-            key[r] = in ? ukey[q] : 0;
-            prev[r] = in && q > 0 ? ukey[q - 1] : ~uint64_t(0);        // no id has all bits set
-            next[r] = in && q + 1 < M ? ukey[q + 1] : ~uint64_t(0);
+            const uint64_t q = q0 + (uint64_t)r * kHistBlock, first = w0 + (uint64_t)r * kHistBlock;
+            key[r] = q < M ? ukey[q] : ~uint64_t(0);                                            // no id has all bits set
+            prev[r] = first > 0 && first <= M ? ukey[first - 1] : ~uint64_t(0);
+            next[r] = first + kWave < M ? ukey[first + kWave] : ~uint64_t(0);
         }
 #pragma unroll
         for (int r = 0; r < kPairsInFlight; ++r) {
-            if (q0 + (uint64_t)r * kBlock >= end) break;
+            prev[r] = lane_below(key[r], prev[r]);
+            next[r] = lane_above(key[r], next[r]);
+        }
+#pragma unroll
+        for (int r = 0; r < kPairsInFlight; ++r) {
+            if (q0 + (uint64_t)r * kHistBlock >= end) break;
             const uint64_t a = key[r];
             const uint32_t i = (uint32_t)(a & imask);
             const uint32_t gap = (a >> ib) == (next[r] >> ib) ? (uint32_t)((next[r] & imask) - i) : kGapInf;
@@ -315,14 +424,14 @@ __global__ __launch_bounds__(kBlock) void plan_hist_kernel(const uint64_t* __res
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < T; i += kBlock) {
+    for (int i = threadIdx.x; i < T; i += kHistBlock) {
         if (lds_u[i]) atomicAdd(&ucount[i], lds_u[i]);
         if (lds_f[i]) atomicAdd(&first_use[i], lds_f[i]);
     }
     if (v_in_lds)
-        for (int i = threadIdx.x; i <= T; i += kBlock)
+        for (int i = threadIdx.x; i <= T; i += kHistBlock)
             if (v_count[i]) atomicAdd(&V[i], v_count[i]);
-    for (int x = threadIdx.x; x < lds_gaps * T; x += kBlock)
+    for (int x = threadIdx.x; x < lds_gaps * T; x += kHistBlock)
         if (lds_h[x]) atomicAdd(&H[(size_t)2 * T + x], lds_h[x]);      // row (2 + x / T), column x % T
 }
 
@@ -336,7 +445,7 @@ __global__ __launch_bounds__(kBlock) void plan_occ_prefix_kernel(uint32_t* H, in
         const int i = base + lane_id();
         const uint32_t inc = wave_inclusive_scan(i < T ? row[i] : 0u, AddOp());
         if (i < T) row[i] = run + inc;
-        run += __shfl(inc, kWave - 1);
+        run += lane_value(inc, kWave - 1);
     }
 }
 
@@ -411,7 +520,7 @@ __global__ __launch_bounds__(kWave) void plan_choose_kernel(const uint32_t* __re
             const int i = i0 + lane;
             const int64_t inc = held + wave_inclusive_scan<int64_t>(i < T ? (int64_t)first_use[i] : 0, AddOp());
             k += (int)__popcll(__ballot(i < T && inc <= budget));
-            held = __shfl(inc, kWave - 1, kWave);
+            held = lane_value(inc, kWave - 1);
             if (held > budget) break;
         }
         requested = k - carried_batches;             // a chunk's batch 0 holds the carried residents, not lookups
@@ -430,7 +539,7 @@ __global__ __launch_bounds__(kWave) void plan_choose_kernel(const uint32_t* __re
         const uint32_t x = i < T ? ucount[i] : 0u;
         const uint32_t inc = run + wave_inclusive_scan<uint32_t>(x, AddOp());
         if (i <= T) pair_off[i] = inc - x;
-        run = __shfl(inc, kWave - 1, kWave);
+        run = lane_value(inc, kWave - 1);
     }
     if (lane == 0) {
         sc->n_pairs = *n_pairs;          // comes back to the host with the lookahead, in one copy
@@ -477,7 +586,8 @@ constexpr int kFlagsWindow = 1024;
 constexpr int kFlagsPerThread = 4;
 constexpr int kFlagsTile = kBlock * kFlagsPerThread;
 __global__ __launch_bounds__(kBlock) void plan_flags_kernel(const uint64_t* __restrict__ ukey, uint32_t M, int ib,
-                                                            const PlanScalars* sc, int chunk, uint64_t* __restrict__ rec) {
+                                                            const PlanScalars* sc, int chunk, uint64_t* __restrict__ rec,
+                                                            uint64_t* __restrict__ miss_mask) {
     __shared__ uint64_t win[kFlagsTile + 1 + kFlagsWindow];
     const uint64_t imask = (uint64_t(1) << ib) - 1;
     const int64_t Leff = sc->L_eff;
@@ -538,19 +648,49 @@ __global__ __launch_bounds__(kBlock) void plan_flags_kernel(const uint64_t* __re
             }
         }
         rec[q] = PairRecord{ib}.pack(g, t, (miss ? kMiss : 0) | (keep ? 0 : kEvict), (uint32_t)i);
+        const uint64_t m = __ballot(miss);
+        if (lane_id() == 0) miss_mask[q / kWave] = m;
     }
 }
 
-struct MissIndexIn {
-    const uint64_t* rec;
-    int ib;
-    __device__ __forceinline__ uint32_t operator()(int64_t q) const {
-        return (PairRecord{ib}.flags(rec[q]) & kMiss) ? (uint32_t)q : 0u;
+// The pair that fetched a pair's row: the last miss at or before it in (id, batch) order.  Kept as bit masks like the pairs'
+// starts.  An id's first pair is a miss, so the words without one that a pair looks back over are its own id's: none as a
+// rule, and never more than a 64th of the batches.
+struct FetchingPair {
+    const uint64_t* miss_mask;
+    struct Words {                 // the pair's word and the one before, which nearly always hold the miss
+        uint64_t own, before;
+    };
+    __device__ __forceinline__ Words load(int64_t word) const { return Words{miss_mask[word], miss_mask[word > 0 ? word - 1 : 0]}; }
+    __device__ __forceinline__ uint32_t in_word(int64_t word, int lane, Words w) const {
+        uint64_t m = w.own & (~uint64_t(0) >> (kWave - 1 - lane));
+        if (m == 0 && word > 0) {
+            m = w.before;
+            --word;
+        }
+        while (m == 0 && word > 0) m = miss_mask[--word];
+        return (uint32_t)(word * kWave) + (kWave - 1) - (uint32_t)__clzll((long long)m);
     }
+    __device__ __forceinline__ uint32_t of(uint32_t q) const { return in_word(q / kWave, (int)(q % kWave), load(q / kWave)); }
 };
-struct StoreInclusiveU32 {
-    uint32_t* p;
-    __device__ __forceinline__ void operator()(int64_t i, uint32_t, uint32_t inc) const { p[i] = inc; }
+// The pairs' records for the sort by batch, each with the pair that fetched its row.
+struct FetchedRecords {
+    const uint64_t* rec;
+    FetchingPair fetched_by;
+    typedef uint64_t Raw;
+    static constexpr bool kLate = false;
+    template <bool PLAIN>
+    __device__ __forceinline__ uint64_t load(int64_t i) const { return rec[i]; }
+    typedef FetchingPair::Words RawVal;
+    __device__ __forceinline__ RawVal load_val(int64_t, int64_t at) const { return fetched_by.load(at / kWave); }
+    __device__ __forceinline__ uint32_t val(RawVal raw, int64_t at) const { return fetched_by.in_word(at / kWave, lane_id(), raw); }
+    struct Cursor {
+        __device__ __forceinline__ Cursor(const FetchedRecords&, int64_t, int64_t) {}
+        __device__ __forceinline__ bool plain() const { return true; }
+        template <bool PLAIN>
+        __device__ __forceinline__ uint64_t key(int64_t, uint64_t raw) const { return raw; }
+        __device__ __forceinline__ void done() const {}
+    };
 };
 
 // ---- 5. lists in (batch, id) order -----------------------------------------------------------
@@ -587,7 +727,7 @@ struct ListOut {
     int pb;
     const int64_t* cuts;      // device [real batches][P + 1]
     int P;
-    const uint32_t* chain;    // the pair that fetched the row a pair uses
+    FetchingPair fetched_by;
     bool numbered;
     __device__ __forceinline__ int trainer_of(const int64_t* c, int64_t rel) const {
         int lo = 0, hi = P;                               // largest t < P with c[t] <= rel
@@ -609,24 +749,22 @@ struct ListOut {
         const bool next = q + 1 < M && (ukey[q + 1] >> ib) == (ukey[q] >> ib) && (ukey[q + 1] & imask) == (uint64_t)i + 1;
         return next ? -2 : -1;
     }
-    __device__ __forceinline__ void operator()(int64_t k, uint64_t exc, uint64_t) const {
+    // entry k: its record, what travelled with it, the misses and evictions before it
+    __device__ __forceinline__ void write(int64_t k, uint64_t r, uint32_t q, uint32_t x, uint32_t e) const {
         const PairRecord pr{ib};
-        const uint64_t r = srec[k];
-        const uint32_t q = ord[k];           // not numbered: the pair's own number only where the pair is a miss
         const int64_t g = pr.id(r);
         const uint32_t i = pr.batch(r);
-        const uint32_t x = (uint32_t)exc, e = (uint32_t)(exc >> 32);
         const uint64_t f = pr.flags(r);
         keep_ids[k] = g;
         keep_ttl[k] = (int32_t)pr.ttl(r) - ttl_shift;
         if (keep_owner) keep_owner[k] = owner_of(q, i);
         if (f & kMiss) {
             prefetch_ids[x] = g;
-            missord[q] = x;
+            missord[q] = x;                  // not numbered: the pair's own number only where the pair is a miss
         }
         if (f & kEvict) {
             evict_ids[e] = g;
-            evict_pair[e] = numbered ? chain[q] : q;       // the pair that fetched the row: same residency, same slot
+            evict_pair[e] = numbered ? fetched_by.of(q) : q;       // the pair that fetched the row: same residency, same slot
         }
         if ((uint32_t)k == pair_off[i]) {
             prefetch_off[i] = x;
@@ -634,6 +772,46 @@ struct ListOut {
         }
     }
 };
+// The last pass of the scan over ListCountIn, written out: the counts are flags, so a ballot and a population count place an
+// entry where a scan would take six additions of 64 bits, and every round's records are here before the first is written (the
+// compiler moves no load across the stores of the round before: 19.5 M pairs 258 us, 149 this way).
+template <int ROUNDS, bool SPINE>
+__global__ __launch_bounds__(kScanBlock) void plan_lists_kernel(ListOut out, int64_t M, uint64_t* partials) {
+    __shared__ ScanShared<uint64_t> sh;
+    const int w = threadIdx.x / kWave, lane = lane_id();
+    const int64_t base = (int64_t)blockIdx.x * (kScanBlock * ROUNDS) + w * (kWave * ROUNDS) + lane;
+    uint64_t rec[ROUNDS];
+    uint32_t with[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int64_t k = base + r * kWave;
+        rec[r] = k < M ? out.srec[k] : 0;
+        with[r] = k < M ? out.ord[k] : 0u;
+    }
+    const uint64_t before = scan_tiles_before<SPINE>(partials, AddOp(), uint64_t(0));
+    uint64_t missed[ROUNDS], evicted[ROUNDS];
+    uint32_t misses = 0, evictions = 0;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint64_t f = PairRecord{out.ib}.flags(rec[r]);
+        missed[r] = __ballot((f & kMiss) != 0);
+        evicted[r] = __ballot((f & kEvict) != 0);
+        misses += (uint32_t)__popcll(missed[r]);
+        evictions += (uint32_t)__popcll(evicted[r]);
+    }
+    const uint64_t carry = scan_carry<SPINE>((uint64_t)misses | ((uint64_t)evictions << 32), before, partials, AddOp(), uint64_t(0), sh);
+    uint32_t x = (uint32_t)carry, e = (uint32_t)(carry >> 32);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int64_t k = base + r * kWave;
+        if (k < M)
+            out.write(k, rec[r], with[r],
+                      __builtin_amdgcn_mbcnt_hi((uint32_t)(missed[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)missed[r], x)),
+                      __builtin_amdgcn_mbcnt_hi((uint32_t)(evicted[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)evicted[r], e)));
+        x += (uint32_t)__popcll(missed[r]);
+        e += (uint32_t)__popcll(evicted[r]);
+    }
+}
 
 // ---- 6. FIFO ring: chains of links ------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void plan_ring_init_kernel(const uint64_t* __restrict__ totals, int64_t C,
@@ -690,14 +868,15 @@ __device__ __forceinline__ int32_t resolved_slot(uint32_t p0, const int32_t* __r
     return ring0 ? ring0[p0] : (int32_t)p0;
 }
 
-__global__ __launch_bounds__(kBlock) void plan_pair_slots_kernel(uint32_t M, const uint32_t* __restrict__ chain,
+__global__ __launch_bounds__(kBlock) void plan_pair_slots_kernel(uint32_t M, FetchingPair fetched_by,
                                                                  const uint32_t* __restrict__ missord,
                                                                  const uint32_t* __restrict__ par,
                                                                  const int32_t* __restrict__ ring0, int64_t C,
                                                                  int32_t* __restrict__ slot_of_pair) {
     const uint32_t q = blockIdx.x * kBlock + threadIdx.x;
     if (q >= M) return;
-    slot_of_pair[q] = resolved_slot(par[missord[chain[q]]], ring0, C);
+    const int64_t word = (int64_t)blockIdx.x * (kBlock / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    slot_of_pair[q] = resolved_slot(par[missord[fetched_by.in_word(word, lane_id(), fetched_by.load(word))]], ring0, C);
 }
 
 __global__ __launch_bounds__(kBlock) void plan_list_slots_kernel(const uint64_t* __restrict__ totals,
@@ -733,14 +912,17 @@ inline uint32_t blocks_per_xcd(int64_t n) { return (uint32_t)ceil_div(n > 0 ? ce
 __global__ __launch_bounds__(kBlock) void plan_lookup_slots_kernel(int64_t N, int64_t first, int ib, int pb,
                                                                    const uint64_t* __restrict__ skeys,
                                                                    const int64_t* __restrict__ iter_off,
-                                                                   const uint32_t* __restrict__ uq,
+                                                                   PairOfLookup pair_of,
                                                                    const int32_t* __restrict__ slot_of_pair,
                                                                    int32_t* __restrict__ lookup_slots) {
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t word = (int64_t)blockIdx.x * (kBlock / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (word * kWave >= N) return;                               // uniform
+    const uint32_t q = pair_of(word);
     if (p >= N) return;
     const uint64_t k = skeys[p];
     const int64_t pos = iter_off[(k >> pb) & ((uint64_t(1) << ib) - 1)] + (int64_t)(k & ((uint64_t(1) << pb) - 1));
-    if (pos >= first) lookup_slots[pos - first] = slot_of_pair[uq[p]];   // below first: carried rows
+    if (pos >= first) lookup_slots[pos - first] = slot_of_pair[q];   // below first: carried rows
 }
 
 // ---- 8. lookups of every batch grouped by row (optional) ---------------------------------------
@@ -758,52 +940,35 @@ struct GroupWord {
 // which the sorted words already hold).
 struct GroupWordSource {
     const uint64_t* skeys;
-    const uint32_t* uq;
+    PairOfLookup pair_of;
     const int32_t* slot_of_pair;
     int low;                                  // ib + pb: the bits kept from the sorted word
-    struct Raw {
-        uint64_t k;
-        uint32_t q;
-    };
-    __device__ __forceinline__ Raw load(uint32_t i) const { return Raw{skeys[i], uq[i]}; }
+    typedef uint64_t Raw;
+    static constexpr bool kLate = true;       // the slot plays no part in the ranking
+    template <bool PLAIN>
+    __device__ __forceinline__ uint64_t load(int64_t i) const { return skeys[i]; }
+    __device__ __forceinline__ uint32_t late(int64_t at) const { return (uint32_t)slot_of_pair[pair_of(at / kWave)]; }
+    __device__ __forceinline__ uint64_t merge(uint64_t k, uint32_t slot) const {
+        return ((uint64_t)slot << low) | (k & ((uint64_t(1) << low) - 1));
+    }
     struct Cursor {
-        const GroupWordSource& s;
-        __device__ __forceinline__ Cursor(const GroupWordSource& src, uint32_t) : s(src) {}
-        __device__ __forceinline__ uint64_t key(uint32_t, Raw raw) {
-            return ((uint64_t)(uint32_t)s.slot_of_pair[raw.q] << s.low) | (raw.k & ((uint64_t(1) << s.low) - 1));
-        }
+        __device__ __forceinline__ Cursor(const GroupWordSource&, int64_t, int64_t) {}
+        __device__ __forceinline__ bool plain() const { return true; }
+        template <bool PLAIN>
+        __device__ __forceinline__ uint64_t key(int64_t, uint64_t raw) const { return raw; }
+        __device__ __forceinline__ void done() const {}
     };
 };
 
 // Rows of the grouped order.  A row starts where (slot, batch) changes; the kernel that scatters the slot map reads
-// every grouped word anyway and leaves these starts as bit masks, 64 lookups a word.  A scan over the words
-// (population counts) then numbers the rows, and every word writes the first grouped positions of its rows to row_pos.
-struct RowMaskIn {
-    const uint64_t* head_mask;
-    __device__ __forceinline__ uint32_t operator()(int64_t w) const { return (uint32_t)__popcll(head_mask[w]); }
+// every grouped word anyway and leaves these starts as bit masks, 64 lookups a word; numbered like the pairs', they give
+// the rows' first grouped positions.
+struct EmitRowStart {
+    uint32_t* row_pos;
+    struct Loaded {};
+    __device__ __forceinline__ Loaded load(int64_t) const { return Loaded{}; }
+    __device__ __forceinline__ void store(uint32_t r, int64_t at, Loaded) const { row_pos[r] = (uint32_t)at; }
 };
-// A wavefront takes 64 mask words and goes through them one by one: lane b owns bit b of the word in hand, and the
-// lanes whose bit is set write their positions side by side, behind the rows that the scan counted before the word.
-// (Every word writing its own rows from one lane, inside the scan's last pass, scatters 64 short runs per store.)
-__global__ __launch_bounds__(kBlock) void plan_row_starts_kernel(const uint64_t* __restrict__ head_mask,
-                                                                 const uint32_t* __restrict__ rows_before, int64_t n_words,
-                                                                 uint32_t* __restrict__ row_pos) {
-    const int lane = lane_id();
-    const int64_t w0 = ((int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave) * kWave;    // wave-uniform
-    if (w0 >= n_words) return;
-    const int64_t mine = w0 + lane;
-    const uint64_t m = mine < n_words ? head_mask[mine] : 0;
-    const uint32_t before = mine < n_words ? rows_before[mine] : 0u;
-    uint64_t left = __ballot(m != 0);                                // words of this wavefront that hold a row start
-    while (left) {
-        const int t = __ffsll((unsigned long long)left) - 1;
-        left &= left - 1;
-        const uint64_t word = __shfl(m, t, kWave);
-        const uint32_t base = __shfl(before, t, kWave);
-        if ((word >> lane) & 1u)
-            row_pos[base + (uint32_t)__popcll(word & lanemask_lt())] = (uint32_t)((w0 + t) * 64 + lane);
-    }
-}
 
 // Second scan, over the rows (RowPiecesIn counts the pieces): every row writes its record beside its keep-list
 // entry (the carried residents of a chunk own the first `first` entries), a long row its piece records, and the
@@ -821,24 +986,59 @@ struct GroupRecordOut {
     uint4* piece_recs;
     int64_t* piece_off;    // device copies of the CSR offsets, [T+1] each, pre-filled with -1
     int64_t* multi_off;
-    __device__ __forceinline__ void operator()(int64_t r, uint64_t exc, uint64_t inc) const {
-        const uint32_t R = *n_rows;
-        if (r >= (int64_t)R) return;
-        const uint32_t p = row_pos[r];
-        const uint32_t count = (r + 1 < (int64_t)R ? row_pos[r + 1] : n) - p;
-        const uint64_t k = gkeys[p];
-        const uint32_t b = gw.batch(k), slot = gw.slot(k);
-        const int64_t base = iter_off[b];
-        const uint32_t rel = (uint32_t)((int64_t)p - base);
-        const uint32_t pc = pieces_of(count);
-        row_recs[first + r] = make_uint4(rel | (pc ? kLongRow : 0u), count, slot, gw.place(k));
-        if (pc) write_pieces(piece_recs, (uint32_t)exc, pc, rel, count, slot, (uint32_t)(exc >> 32), b);
-        if ((int64_t)p == base) {
-            piece_off[b] = (int64_t)(uint32_t)exc;
-            multi_off[b] = (int64_t)(exc >> 32);
+};
+// Written out like plan_lists_kernel: everything a tile's rows ask for is asked for before the first record is written, and
+// the pieces are scanned only where a round of 64 rows has any.  Bound by memory: 19.5 M rows 172 us in the general scan, 131
+// this way with six wavefronts a SIMD, 196 with four (108 registers, the scans of all rounds kept).
+template <int ROUNDS, bool SPINE>
+__global__ __launch_bounds__(kScanBlock, 6) void plan_records_kernel(GroupRecordOut o, int64_t bound, uint64_t* partials) {
+    __shared__ ScanShared<uint64_t> sh;
+    const int w = threadIdx.x / kWave, lane = lane_id();
+    const int64_t base = (int64_t)blockIdx.x * (kScanBlock * ROUNDS) + w * (kWave * ROUNDS) + lane;
+    const int64_t R = min((int64_t)*o.n_rows, bound);
+    uint32_t p[ROUNDS], count[ROUNDS];
+    uint64_t key[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int64_t row = base + r * kWave;
+        p[r] = row < R ? o.row_pos[row] : 0u;
+        count[r] = row < R ? (row + 1 < R ? o.row_pos[row + 1] : o.n) - p[r] : 0u;
+    }
+    const uint64_t before = scan_tiles_before<SPINE>(partials, AddOp(), uint64_t(0));
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) key[r] = base + r * kWave < R ? o.gkeys[p[r]] : 0;
+    const auto pieces = [&](int r) {
+        const uint32_t pc = pieces_of(count[r]);
+        return (uint64_t)pc | ((uint64_t)(pc > 1 ? pc : 0u) << 32);
+    };
+    uint64_t mine = 0;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)
+        if (__ballot(count[r] > kRowMax)) mine += wave_reduce(pieces(r), AddOp());
+    uint64_t carry = scan_carry<SPINE>(mine, before, partials, AddOp(), uint64_t(0), sh);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int64_t row = base + r * kWave;
+        uint64_t exc = carry;
+        if (__ballot(count[r] > kRowMax)) {
+            const uint64_t inc = wave_inclusive_scan(pieces(r), AddOp());
+            exc = lane_below(inc, uint64_t(0)) + carry;
+            carry += lane_value(inc, kWave - 1);
+        }
+        if (row < R) {
+            const uint32_t b = o.gw.batch(key[r]), slot = o.gw.slot(key[r]);
+            const int64_t start = o.iter_off[b];
+            const uint32_t rel = (uint32_t)((int64_t)p[r] - start);
+            const uint32_t pc = pieces_of(count[r]);
+            o.row_recs[o.first + row] = make_uint4(rel | (pc ? kLongRow : 0u), count[r], slot, o.gw.place(key[r]));
+            if (pc) write_pieces(o.piece_recs, (uint32_t)exc, pc, rel, count[r], slot, (uint32_t)(exc >> 32), b);
+            if ((int64_t)p[r] == start) {
+                o.piece_off[b] = (int64_t)(uint32_t)exc;
+                o.multi_off[b] = (int64_t)(exc >> 32);
+            }
         }
     }
-};
+}
 __global__ __launch_bounds__(kBlock) void plan_piece_partial_kernel(uint4* __restrict__ piece_recs,
                                                                     const uint32_t* __restrict__ n_pieces, int T,
                                                                     const int64_t* __restrict__ multi_off,
@@ -885,9 +1085,8 @@ __global__ __launch_bounds__(kBlock) void plan_lookup_slots_grouped_kernel(int64
 #pragma unroll
     for (int u = 0; u < kSlotRounds; ++u) {
         const int64_t p = stretch + u * kWave + lane;
-        uint64_t left = __shfl_up(k[u], 1, kWave);
-        if (lane == 0) left = before;
-        before = __shfl(k[u], kWave - 1, kWave);
+        const uint64_t left = lane_below(k[u], before);
+        before = lane_value(k[u], kWave - 1);
         bool head = false;
         if (p >= first && p < N) {
             if (lookup_slots) lookup_slots[to[u]] = (int32_t)gw.slot(k[u]);
@@ -955,7 +1154,8 @@ __global__ __launch_bounds__(kBlock) void plan_state_queue_kernel(int64_t n_miss
 // ---- workspace layout ------------------------------------------------------------------------
 struct PlanWorkspace {
     uint64_t *keys_a, *keys_b;
-    uint32_t* uq;            // pair of every sorted lookup
+    uint64_t* head_mask;     // where a pair starts among the sorted lookups, 64 a word
+    uint32_t* pairs_before;  // pairs that start before every word
     int32_t* tile_batch;     // batch of every 4096-th position
     uint32_t* sort_temp;
     uint32_t* scan_partials32;   // head scan, chain scan
@@ -964,11 +1164,13 @@ struct PlanWorkspace {
     PlanScalars* scalars;
     int64_t *occ, *offsets, *prefetch_off, *evict_off, *iter_off;
     uint64_t *rec_a, *rec_b;
-    uint32_t *chain, *val2_a, *val2_b, *missord, *evict_pair, *par, *pair_start;
+    uint64_t* miss_mask;     // misses among the pairs, 64 a word
+    uint32_t *val2_a, *val2_b, *missord, *evict_pair, *par, *pair_start;
     int64_t* cuts;           // trainer cuts of every batch, [T][kMaxTrainers + 1] at most
     int32_t* slot_of_pair;
     uint64_t* keys_c;      // grouping only: the other half of the regrouping sort's ping-pong
-    uint32_t* group_counts;   // grouping only: the regrouping sort's first histogram, made by the head scan's first pass
+    uint32_t* group_counts;   // grouping only: the regrouping sort's first histogram, made with the start masks
+    uint32_t* row_pos;        // grouping only: the rows' first positions, at most one row a pair
     int64_t* piece_off;
     int64_t* multi_off;
     size_t bytes;
@@ -980,11 +1182,12 @@ PlanWorkspace carve_plan(void* base, size_t cap, int64_t N, int T, int Lcap, boo
     const size_t n = (size_t)(N > 0 ? N : 1);
     w.keys_a = c.take<uint64_t>(n);
     w.keys_b = c.take<uint64_t>(n);
-    w.uq = c.take<uint32_t>(n < 64 ? 64 : n);      // later the rows' first positions of the grouping step
+    w.head_mask = c.take<uint64_t>((n + 63) / 64);
+    w.pairs_before = c.take<uint32_t>((n + 63) / 64);
     w.tile_batch = c.take<int32_t>((n >> kPosTileShift) + 2);
     // a workspace that is large enough for N lookups is so for fewer, which may have more tiles
     const int64_t in_small_tiles = std::min(N, kPlanSmallSort);
-    w.sort_temp = c.take<uint32_t>(std::max(sort_temp_words<kPlanSortIPT>(N), sort_temp_words<kPlanSmallIPT>(in_small_tiles)));
+    w.sort_temp = c.take<uint32_t>(std::max(sort_temp_words<LargeTiles>(N), sort_temp_words<SmallTiles>(in_small_tiles)));
     w.scan_partials32 = c.take<uint32_t>(scan_partials(N));
     w.scan_partials64 = c.take<uint64_t>(scan_partials(N));
     w.H = c.take<uint32_t>((size_t)(Lcap + 1) * T);
@@ -1005,7 +1208,7 @@ PlanWorkspace carve_plan(void* base, size_t cap, int64_t N, int T, int Lcap, boo
     w.iter_off = c.take<int64_t>(T + 1);
     w.rec_a = c.take<uint64_t>(n);
     w.rec_b = c.take<uint64_t>(n);
-    w.chain = c.take<uint32_t>(n);
+    w.miss_mask = c.take<uint64_t>((n + 63) / 64);
     w.val2_a = c.take<uint32_t>(n);
     w.val2_b = c.take<uint32_t>(n);
     w.missord = c.take<uint32_t>(n);
@@ -1016,8 +1219,9 @@ PlanWorkspace carve_plan(void* base, size_t cap, int64_t N, int T, int Lcap, boo
     w.slot_of_pair = c.take<int32_t>(n);
     if (grouping) {
         w.keys_c = c.take<uint64_t>(n);
-        w.group_counts = c.take<uint32_t>((size_t)kMaxRadix * std::max(sort_num_tiles<kPlanSortIPT>(N),
-                                                                        sort_num_tiles<kPlanSmallIPT>(in_small_tiles)));
+        w.row_pos = c.take<uint32_t>(n);
+        w.group_counts = c.take<uint32_t>((size_t)kMaxRadix * std::max(sort_num_tiles<LargeTiles>(N),
+                                                                        sort_num_tiles<SmallTiles>(in_small_tiles)));
     }
     w.bytes = c.used();
     return w;
@@ -1167,25 +1371,23 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
     uint64_t* const kbuf[2] = {w.keys_a, w.keys_b};
     uint32_t* const no_vals[2] = {nullptr, nullptr};
     int sorted_in = -1;
-    BP_TRY(with_plan_ipt(N, [&](auto ipt) {
-        return radix_sort_from<uint64_t, ipt(), PlanKeySource, PlanKeySource, false>(
-            source, source, kbuf, no_vals, N, ib + pb, ib + pb + gb, w.sort_temp, stream, &sorted_in);
+    BP_TRY(with_plan_tiles<false>(N, [&](auto tiles) {
+        return radix_sort_from<uint64_t, decltype(tiles), PlanIdSource, PlanKeySource, false>(
+            PlanIdSource{source}, source, kbuf, no_vals, N, ib + pb, ib + pb + gb, w.sort_temp, stream, &sorted_in);
     }));
     const uint64_t* skeys = kbuf[sorted_in];
     uint64_t* ukey = kbuf[sorted_in ^ 1];          // the other ping-pong buffer is free now
-    uint32_t* uq = w.uq;
 
     // ---- 2. unique pairs
     const int group_bits = grouping ? radix_first_pass_bits(pb, pb + ib) : 0;     // of the regrouping sort's first pass
-    if (grouping) {
-        BP_TRY(plan_head_hist(skeys, N, pb, w.scan_partials32, group_bits, w.group_counts, stream));
-        BP_TRY((device_scan_reduced<uint32_t, AddOp, HeadFlagIn, PairOut>(
-            HeadFlagIn{skeys, pb}, PairOut{skeys, pb, ukey, uq, w.pair_start}, N, w.scan_partials32, AddOp(), 0u, stream)));
-    } else {
-        BP_TRY((device_scan<uint32_t, AddOp, HeadFlagIn, PairOut>(HeadFlagIn{skeys, pb}, PairOut{skeys, pb, ukey, uq, w.pair_start},
-                                                                  N, w.scan_partials32, AddOp(), 0u, stream)));
-    }
-    const uint32_t* n_pairs_dev = w.scan_partials32 + scan_num_tiles(N);     // stays valid until the next 32-bit scan
+    const int64_t n_words = (N + kWave - 1) / kWave;
+    BP_TRY(with_plan_tiles<false>(N, [&](auto tiles) {
+        return plan_heads<decltype(tiles)>(skeys, N, pb, w.head_mask, group_bits, grouping ? w.group_counts : nullptr, stream);
+    }));
+    const uint32_t* n_pairs_dev = nullptr;               // stays valid until the next 32-bit scan
+    BP_TRY(expand_masks(K_PLAN_PAIRS, w.head_mask, w.pairs_before, n_words, w.scan_partials32, &n_pairs_dev,
+                        EmitPair{skeys, pb, ukey, owners ? w.pair_start : nullptr}, stream));
+    const PairOfLookup pair_of{w.head_mask, w.pairs_before};
 
     // ---- 3. occupancy for every candidate lookahead, L_eff
     // H, ucount, first_use, V, vcover and peak lie one after the other in the workspace: one clear for all of them
@@ -1205,7 +1407,7 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
         int64_t blocks = ceil_div(N, 4 * share);
         if (blocks > 1024) blocks = 1024;
         if (blocks < 1) blocks = 1;
-        BP_LAUNCH(K_PLAN_HIST, plan_hist_kernel, dim3((unsigned)blocks), dim3(kBlock),
+        BP_LAUNCH(K_PLAN_HIST, plan_hist_kernel, dim3((unsigned)blocks), dim3(kHistBlock),
                   sizeof(uint32_t) * lds_cells, stream, (const uint64_t*)ukey, n_pairs_dev, ib, T, Lcap,
                   lds_gaps, w.H, w.ucount, w.first_use, (int)chunk, w.V, (int)(v_cells > 0));
     }
@@ -1251,9 +1453,8 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
     // ---- 4. flags, TTL, fetching pair of every pair
     BP_LAUNCH(K_PLAN_FLAGS, plan_flags_kernel, dim3((unsigned)(M > 0 ? ceil_div((int64_t)M, kFlagsTile) : 1)), dim3(kBlock), 0,
               stream, (const uint64_t*)ukey, M, ib,
-              (const PlanScalars*)w.scalars, (int)chunk, w.rec_a);
-    BP_TRY((device_scan<uint32_t, MaxOp, MissIndexIn, StoreInclusiveU32>(MissIndexIn{w.rec_a, ib}, StoreInclusiveU32{w.chain},
-                                                                         M, w.scan_partials32, MaxOp(), 0u, stream)));
+              (const PlanScalars*)w.scalars, (int)chunk, w.rec_a, w.miss_mask);
+    const FetchingPair fetched_by{w.miss_mask};
 
     // ---- 5. regroup by batch (the records travel as keys), lists
     // What travels with a record: the number of the pair that fetched its row (for a miss that is the pair itself,
@@ -1261,17 +1462,18 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
     // pass then looks the fetching pair up.
     bool ord_in_b = false;
     if (owners) {
-        BP_TRY(with_plan_ipt(N, [&](auto ipt) {
-            return radix_sort_numbered<uint64_t, ipt()>(w.rec_a, w.rec_b, w.val2_a, w.val2_b, M, 0, ib, w.sort_temp, stream,
+        BP_TRY(with_plan_tiles<true>(N, [&](auto tiles) {
+            return radix_sort_numbered<uint64_t, decltype(tiles)>(w.rec_a, w.rec_b, w.val2_a, w.val2_b, M, 0, ib, w.sort_temp, stream,
                                                         &ord_in_b);
         }));
     } else {
         uint64_t* const rbuf[2] = {w.rec_b, w.rec_a};
         uint32_t* const vbuf[2] = {w.val2_b, w.val2_a};
-        const SortArrays<uint64_t> rup{w.rec_a, nullptr}, rsrc{w.rec_a, w.chain};
+        const SortArrays<uint64_t> rup{w.rec_a, nullptr};
+        const FetchedRecords rsrc{w.rec_a, fetched_by};
         int r_in = -1;
-        BP_TRY(with_plan_ipt(N, [&](auto ipt) {
-            return radix_sort_from<uint64_t, ipt(), SortArrays<uint64_t>, SortArrays<uint64_t>, true>(
+        BP_TRY(with_plan_tiles<true>(N, [&](auto tiles) {
+            return radix_sort_from<uint64_t, decltype(tiles), SortArrays<uint64_t>, FetchedRecords, true>(
                 rup, rsrc, rbuf, vbuf, M, 0, ib, w.sort_temp, stream, &r_in);
         }));
         ord_in_b = r_in == 0;
@@ -1281,12 +1483,15 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
     // prefetch, evict, piece and several-piece offsets start at -1 ("this batch owns no entry")
     BP_LAUNCH(K_FILL, fill_kernel<int64_t>, grid_for(4 * (T + 1)), dim3(kBlock), 0, stream, w.offsets, (int64_t)(4 * (T + 1)),
               (int64_t)-1);
-    BP_TRY((device_scan<uint64_t, AddOp, ListCountIn, ListOut>(
-        ListCountIn{srec, ib},
-        ListOut{srec, ord, w.pair_off, ib, plan->keep_ids, plan->keep_ttl, plan->prefetch_ids, plan->evict_ids, w.missord,
-                w.evict_pair, w.prefetch_off, w.evict_off, shift, owners ? plan->keep_owner : nullptr, ukey, M,
-                w.pair_start, (uint32_t)N, skeys, pb, w.cuts, P, w.chain, owners},
-        M, w.scan_partials64, AddOp(), uint64_t(0), stream)));
+    const ListOut lists{srec, ord, w.pair_off, ib, plan->keep_ids, plan->keep_ttl, plan->prefetch_ids, plan->evict_ids, w.missord,
+                        w.evict_pair, w.prefetch_off, w.evict_off, shift, owners ? plan->keep_owner : nullptr, ukey, M,
+                        w.pair_start, (uint32_t)N, skeys, pb, w.cuts, P, fetched_by, owners};
+    BP_TRY((scan_reduce<uint64_t, AddOp, ListCountIn>(ListCountIn{srec, ib}, M, w.scan_partials64, AddOp(), uint64_t(0), stream)));
+    BP_TRY(scan_finish(M, w.scan_partials64, AddOp(), uint64_t(0), stream, [&](auto rounds, auto spine, dim3 grid) {
+        BP_LAUNCH(K_PLAN_LISTS, (plan_lists_kernel<rounds(), spine()>), grid, dim3(kScanBlock), 0, stream, lists, (int64_t)M,
+                  w.scan_partials64);
+        return (int)BP_OK;
+    }));
     const uint64_t* totals = w.scan_partials64 + scan_num_tiles(M);
 
     // ---- 6. ring
@@ -1304,52 +1509,51 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
     }
 
     // ---- 7. slots
-    BP_LAUNCH(K_PLAN_SLOTS, plan_pair_slots_kernel, grid_for(M), dim3(kBlock), 0, stream, M, (const uint32_t*)w.chain,
+    BP_LAUNCH(K_PLAN_SLOTS, plan_pair_slots_kernel, grid_for(M), dim3(kBlock), 0, stream, M, fetched_by,
               (const uint32_t*)w.missord, (const uint32_t*)w.par, ring0, C, w.slot_of_pair);
     BP_LAUNCH(K_PLAN_SLOTS, plan_list_slots_kernel, grid_for(M), dim3(kBlock), 0, stream, totals, (const uint32_t*)w.par,
               (const uint32_t*)w.evict_pair, (const int32_t*)w.slot_of_pair, ring0, C, plan->prefetch_slots,
               plan->evict_slots, reinterpret_cast<uint64_t*>(w.offsets + 5 * (size_t)(T + 1)));
     if (!grouping && N_real)      // with grouping the slot map is written from the batch-grouped order (step 8)
         BP_LAUNCH(K_PLAN_SLOTS, plan_lookup_slots_kernel, grid_for(N), dim3(kBlock), 0, stream, N, R0, ib, pb, skeys,
-                  (const int64_t*)w.iter_off, (const uint32_t*)uq, (const int32_t*)w.slot_of_pair, plan->lookup_slots);
+                  (const int64_t*)w.iter_off, pair_of, (const int32_t*)w.slot_of_pair, plan->lookup_slots);
 
     // ---- 8. grouping for the backward pass
     if (grouping) {
         // one pass as a rule (batch bits <= 9): out of the sorted words into the spare buffer; a second pass would
         // come back into the sorted words' own buffer, which nobody reads any more by then
-        const GroupWordSource gsrc{skeys, uq, w.slot_of_pair, ib + pb};
+        const GroupWordSource gsrc{skeys, pair_of, w.slot_of_pair, ib + pb};
         const SortArrays<uint64_t> gup{skeys, nullptr};
         uint64_t* const gbuf[2] = {w.keys_c, const_cast<uint64_t*>(skeys)};
         int g_in = -1;
-        BP_TRY(with_plan_ipt(N, [&](auto ipt) {
-            return radix_sort_from<uint64_t, ipt(), SortArrays<uint64_t>, GroupWordSource, false>(
+        BP_TRY(with_plan_tiles<false>(N, [&](auto tiles) {
+            return radix_sort_from<uint64_t, decltype(tiles), SortArrays<uint64_t>, GroupWordSource, false>(
                 gup, gsrc, gbuf, no_vals, N, pb, pb + ib, w.sort_temp, stream, &g_in, w.group_counts);
         }));
         const uint64_t* gkeys = gbuf[g_in];
         const GroupWord gw{ib, pb};
         // one pass over the grouped words: slot map, grouped_lookups, row starts as bit masks (the masks go to a
-        // pair-level buffer that nobody reads any more); then the rows' first positions, into the buffer of the
-        // sorted lookups' pair numbers, which is free as well
+        // pair-level buffer that nobody reads any more); then the rows' first positions
         const uint32_t per_xcd = blocks_per_xcd(ceil_div(N, (int64_t)kSlotRounds));
         uint64_t* head_mask = reinterpret_cast<uint64_t*>(w.par);
-        uint32_t* row_pos = w.uq;
-        const int64_t n_words = (N + 63) / 64;
+        uint32_t* row_pos = w.row_pos;
         BP_LAUNCH(K_PLAN_SLOTS, plan_lookup_slots_grouped_kernel, dim3(per_xcd * kXcds), dim3(kBlock), 0, stream, N, per_xcd,
                   gw, R0, gkeys, where, plan->lookup_slots, plan->grouped_lookups, head_mask);
         uint32_t* rows_before = w.val2_a;                      // free since the lists were written
-        BP_TRY((device_scan<uint32_t, AddOp, RowMaskIn, StoreExclusiveU32>(RowMaskIn{head_mask}, StoreExclusiveU32{rows_before},
-                                                                          n_words, w.scan_partials32, AddOp(), 0u, stream)));
-        BP_LAUNCH(K_PLAN_GROUP, plan_row_starts_kernel, dim3((unsigned)ceil_div(n_words, (int64_t)kBlock)), dim3(kBlock), 0,
-                  stream, (const uint64_t*)head_mask, (const uint32_t*)rows_before, n_words, row_pos);
-        const uint32_t* n_rows = w.scan_partials32 + scan_num_tiles(n_words);
+        const uint32_t* n_rows = nullptr;
+        BP_TRY(expand_masks(K_PLAN_GROUP, head_mask, rows_before, n_words, w.scan_partials32, &n_rows, EmitRowStart{row_pos}, stream));
         // at most one row per pair (fewer only where the look-ahead batches of a chunk hold rows without a slot)
         const int64_t rows_bound = (int64_t)M - R0 > 0 ? (int64_t)M - R0 : 1;
-        BP_TRY((device_scan<uint64_t, AddOp, RowPiecesIn, GroupRecordOut>(
-            RowPiecesIn{row_pos, n_rows, (uint32_t)N},
-            GroupRecordOut{row_pos, n_rows, (uint32_t)N, gkeys, gw, (const int64_t*)w.iter_off, R0,
-                           reinterpret_cast<uint4*>(plan->row_recs), reinterpret_cast<uint4*>(plan->piece_recs),
-                           w.piece_off, w.multi_off},
-            rows_bound, w.scan_partials64, AddOp(), uint64_t(0), stream)));
+        const GroupRecordOut records{row_pos, n_rows, (uint32_t)N, gkeys, gw, (const int64_t*)w.iter_off, R0,
+                                     reinterpret_cast<uint4*>(plan->row_recs), reinterpret_cast<uint4*>(plan->piece_recs),
+                                     w.piece_off, w.multi_off};
+        BP_TRY((scan_reduce<uint64_t, AddOp, RowPiecesIn>(RowPiecesIn{row_pos, n_rows, (uint32_t)N}, rows_bound, w.scan_partials64,
+                                                          AddOp(), uint64_t(0), stream)));
+        BP_TRY(scan_finish(rows_bound, w.scan_partials64, AddOp(), uint64_t(0), stream, [&](auto rounds, auto spine, dim3 grid) {
+            BP_LAUNCH(K_PLAN_GROUP, (plan_records_kernel<rounds(), spine()>), grid, dim3(kScanBlock), 0, stream, records, rows_bound,
+                      w.scan_partials64);
+            return (int)BP_OK;
+        }));
         const uint32_t* n_pieces_dev = reinterpret_cast<const uint32_t*>(w.scan_partials64 + scan_num_tiles(rows_bound));
         BP_LAUNCH(K_PLAN_GROUP, plan_piece_partial_kernel, grid_for((int64_t)piece_capacity_for(N_real)), dim3(kBlock), 0,
                   stream, reinterpret_cast<uint4*>(plan->piece_recs), n_pieces_dev, T, (const int64_t*)w.multi_off,

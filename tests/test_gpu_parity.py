@@ -711,6 +711,25 @@ def test_plan_sizes_around_the_sort_tiles(bp, n):
     assert_grouping_valid(got, want, ids, off)
 
 
+@pytest.mark.parametrize("n", [(1 << 24) - 1, 1 << 24, (1 << 24) + 8193])
+def test_plan_sizes_around_the_wide_tiles(bp, n):
+    """Lookups around the size from which the plan's sorts take tiles of 8,192: batches that fill many tiles, and a run
+    of ragged and empty ones several of which meet in one tile."""
+    say(f"plan of {n} lookups in wide tiles")
+    rng = np.random.default_rng(n)
+    R = 1_000_003
+    lens = rng.integers(0, 9000, size=200)
+    lens[rng.integers(0, 200, size=20)] = 0
+    lens = np.concatenate([[3_000_000], lens, [5_000_001]])
+    off = np.concatenate([[0], np.cumsum(lens), [n]]).astype(np.int64)
+    ids = ((rng.pareto(0.4, size=n) + 1).clip(max=R).astype(np.int64) * 7919 % R).astype(np.int64)
+    umax = max(len(np.unique(ids[off[i]:off[i + 1]])) for i in range(len(off) - 1))
+    got = bp.bp_oracle_plan(bp.make_config(R, umax + 7, 16, lookahead=9), dev(ids), off, grouping=True)
+    want = oracle.plan(ids, off, R, 9, umax + 7)
+    assert_plan_equal(got, want, n)
+    assert_grouping_valid(got, want, ids, off)
+
+
 @pytest.mark.parametrize("largest", [1, 2, 255, 256, 257, 4096, 4097])
 def test_plan_word_field_boundaries(bp, largest):
     """The place field of a lookup's word has as many bits as the largest batch needs: sizes at and around powers of
