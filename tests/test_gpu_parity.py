@@ -361,6 +361,28 @@ def test_backward_grouped_offsets_at_the_ends_of_their_type(bp):
     assert np.array_equal(got.numpy(), want.numpy())
 
 
+@pytest.mark.parametrize("lens", [
+    [64] * 9, [63, 65, 1, 127, 128, 129, 64], [1] * 63 + [700], [700] + [1] * 70, [64, 0, 64, 0, 0, 1, 63, 0] * 3, [0] * 200 + [640],
+    [40, *[0] * 130, 40, *[1] * 20] * 2, [1, 2, 0, 3] * 50, [5000], [257, 0, 3000, 1, 1, 0, 900, *[0] * 70, 20], [1, 0] * 40 + [4000], [30] * 300],
+    ids=lambda x: f"{len(x)}bags{sum(x)}")
+def test_backward_grouped_bags_of_positions(bp, lens):
+    """Bags whose starts lie on and around the 64 lookups one entry of the bag list tells of, runs of empty bags inside and
+    across it, bags of many entries: sums of small whole numbers, exact in every order."""
+    say(f"grouped backward, {len(lens)} bags of {sum(lens)} lookups")
+    C, D, bags = 37, 8, len(lens)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    n = int(off[-1])
+    rng = np.random.default_rng(n + bags)
+    w = torch.zeros((C, D))
+    cfg = bp.make_config(1000, C, D, "f32", "sgd", lr=1.0)
+    slots = rng.integers(0, C, size=n).astype(np.int32)
+    grad = rng.integers(-8, 9, size=(bags, D)).astype(np.float32)
+    got, _ = run_bwd_grouped(bp, cfg, w, None, slots, off, bags, grad, False)
+    want = np.zeros((C, D), np.float32)
+    np.subtract.at(want, slots, grad[np.repeat(np.arange(bags), lens)])
+    assert np.array_equal(got.numpy(), want)
+
+
 @pytest.mark.parametrize("D,dtype,optimizer,pad", [(48, "f32", "adagrad", 0), (16, "f32", "adagrad", 64),
                                                    (128, "bf16", "adagrad_rowwise", 12), (32, "f32", "sgd", 32)])
 def test_strided_cache_equals_dense(bp, D, dtype, optimizer, pad):
