@@ -9,10 +9,10 @@
 //                  slot, its first lookup.  A row of up to BP_BWD_ROW_MAX lookups is summed (fp64) and updated by
 //                  one lane group, which needs nothing but its record to ask for the cache row and the first
 //                  gradient row.
-//   piece records  a row with more lookups is cut into pieces of BP_BWD_PIECE lookups; one workgroup takes a piece,
-//                  its lane groups add their shares and meet in LDS.  A one-piece row is updated at once.  For a
-//                  row of several pieces the workgroup stores the piece's sum, and the one that finds, by a counter,
-//                  that all the others have stored theirs adds the sums in piece order and updates the row.
+//   piece records  a row with more lookups is cut into pieces of BP_BWD_PIECE lookups; one workgroup (narrow rows: one
+//                  wavefront) takes a piece, its lane groups add their shares and meet.  A one-piece row is updated
+//                  at once.  For a row of several pieces the piece's sum is stored, and whoever finds, by a counter,
+//                  that all the others have stored theirs adds the sums and updates the row.
 // ONE launch does all of it: workgroups [0, piece_blocks) take pieces, the rest take rows.
 // Every order of addition is fixed by the records, never by timing: results are bit-identical run to run.
 // The summed gradient is rounded to fp32 once; the optimizer step itself is fp32 arithmetic.
@@ -333,21 +333,38 @@ __device__ __forceinline__ void add_gradient_rows(SumPiece<N>& acc, uint32_t (&i
     }
 }
 
-// Sum over the lane groups of a workgroup, in group order: every group leaves its sum in LDS, group 0 adds them up.
-// Two barriers; `red` may be reused after the call.
-template <int G, int GW, int N>
-__device__ __forceinline__ void workgroup_sum(SumPiece<N>& acc, double (*red)[N][GW], int j, int c) {
+// Who takes a piece.  Rows of up to four lanes: one wavefront, whose 16 or more lane groups have a piece's lookups in flight
+// in a burst or four; its groups' sums meet by lane shuffles, without LDS or barriers, and four pieces are under way a
+// workgroup.  Wider rows: the workgroup.  (64-byte rows, a Criteo-shaped batch: 22.0 us with a workgroup a piece, whose 64 sums
+// four lanes added one after the other, 14.2 this way.)
+template <int GW>
+constexpr bool kWavePieces = GW <= 4;
+template <int GW>
+constexpr int kPieceThreads = kWavePieces<GW> ? kWave : kRowBlock;
+
+// Sum over the lane groups that took a piece, in an order of its own that nothing but GW decides.  The whole sum is in the
+// first group.  By workgroup: every group leaves its sum in LDS, group 0 adds them up in group order; two barriers, and
+// `red` may be reused after the call.  By wavefront: in pairs, then pairs of pairs.
+template <int GW, int N>
+__device__ __forceinline__ void piece_sum(SumPiece<N>& acc, double (*red)[N][GW], int j, int c) {
+    if constexpr (kWavePieces<GW>) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) red[j][i][c] = acc.v[i];
-    __syncthreads();
-    if (j == 0) {
-        acc.zero();
-        for (int g = 0; g < G; ++g) {
+        for (int off = GW; off < kWave; off <<= 1)
 #pragma unroll
-            for (int i = 0; i < N; ++i) acc.v[i] += red[g][i][c];
+            for (int i = 0; i < N; ++i) acc.v[i] += __shfl_xor(acc.v[i], off, kWave);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) red[j][i][c] = acc.v[i];
+        __syncthreads();
+        if (j == 0) {
+            acc.zero();
+            for (int g = 0; g < kRowBlock / GW; ++g) {
+#pragma unroll
+                for (int i = 0; i < N; ++i) acc.v[i] += red[g][i][c];
+            }
         }
+        __syncthreads();
     }
-    __syncthreads();
 }
 
 // counts: the numbers of row and piece records when they were made on the device (bp_embbag_bwd_update), else NULL
@@ -409,64 +426,79 @@ __global__ __launch_bounds__(kRowBlock, BF16 ? 4 : 8) void bwd_rows_kernel(const
         return;
     }
 
-    // ---- pieces of longer rows: one workgroup each
-    __shared__ double red[G][N][GW];
+    // ---- pieces of longer rows: a wavefront or a workgroup each (kWavePieces)
+    constexpr bool WAVE = kWavePieces<GW>;
+    constexpr int PG = kPieceThreads<GW> / GW;           // lane groups that share a piece
+    constexpr int PER_BLOCK = kRowBlock / kPieceThreads<GW>;
+    __shared__ double red[WAVE ? 1 : G][N][GW];
     __shared__ uint32_t s_last;
+    const int pj = WAVE ? j % PG : j;
     const uint32_t P = n_pieces_ptr ? *n_pieces_ptr : n_pieces_host;
-    const bool writer = active && j == 0;
-    for (uint32_t pi = blockIdx.x; pi < P; pi += piece_blocks) {
+    const bool writer = active && pj == 0;
+    for (uint32_t pi = blockIdx.x * PER_BLOCK + (WAVE ? threadIdx.x / kWave : 0u); pi < P; pi += piece_blocks * PER_BLOCK) {
         const uint4 r0 = piece_recs[2 * (size_t)pi], r1 = piece_recs[2 * (size_t)pi + 1];
         const uint32_t start = r0.x, count = r0.y, slot = r0.z, index = r0.w, pieces = r1.x, pbase = r1.y;
         // a record that points outside the batch or the workspace does nothing (the test is the same in every lane)
         if ((int64_t)slot >= C || count == 0 || start >= n || count > n - start || pieces == 0 || index >= pieces) continue;
         const bool direct = pieces == 1;
         if (!direct && (pbase >= partial_rows || pieces > partial_rows - pbase)) continue;
-        // lane group j takes the j-th stretch of the piece
-        const uint32_t per = (count + G - 1) / G;
-        const uint32_t p0 = start + min((uint32_t)j * per, count), p1 = start + min((uint32_t)(j + 1) * per, count);
+        // lane group pj takes the pj-th stretch of the piece
+        const uint32_t per = (count + PG - 1) / PG;
+        const uint32_t p0 = start + min((uint32_t)pj * per, count), p1 = start + min((uint32_t)(pj + 1) * per, count);
         uint32_t idx[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) idx[k] = p0 + k < p1 ? bag_of[p0 + k] : 0u;
         SumPiece<N> acc;
         acc.zero();
         if (active) add_gradient_rows<BF16, N>(acc, idx, p0, p1, bag_of, grad, u, c);
-        workgroup_sum<G, GW, N>(acc, red, j, c);
+        piece_sum<GW, N>(acc, red, pj, c);
         if (direct) {      // the row is asked for only now: one more round trip after a few hundred gradient rows
-            if (j == 0) {
+            if (pj == 0) {
                 const RowPiece<BF16> row = load_row<BF16>(u, cache_w, cache_s, (int64_t)slot, c, writer);
                 finish_update<GW, BF16>(u, cache_w, cache_s, (int64_t)slot, c, row, acc.template rounded<BF16>(), writer);
             }
             continue;
         }
-        // one of several pieces: leave the sum where the last workgroup of the row will find it, then take a ticket
-        // (device-coherent stores, complete before the barrier lets thread 0 count this piece; the workgroup that
-        // counts the last piece then reads all the sums with device-coherent loads)
+        // one of several pieces: leave the sum where whoever takes the row's last piece will find it, then take a ticket
+        // (device-coherent stores, complete before this piece is counted; whoever counts the last piece then reads
+        // all the sums with device-coherent loads)
+        // The writers and the lane that draws the ticket are of one wavefront, which waits for its stores here by itself: a
+        // fence for the workgroup leaves them on their way, its barrier too.
+        static_assert(GW <= kWave, "the writers are lanes of the workgroup's, or the piece's, first wavefront");
         if (writer) acc.store_device(partial + (size_t)(pbase + index) * u.dim, c);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __syncthreads();
-        if (threadIdx.x == 0)
-            s_last = __hip_atomic_fetch_add(&tickets[pbase], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == pieces ? 1u : 0u;
-        __syncthreads();
-        const bool last = s_last != 0u;
-        __syncthreads();                               // everybody has read s_last before a later piece rewrites it
+        bool last;
+        if constexpr (WAVE) {
+            uint32_t drawn = 0;
+            if (threadIdx.x % kWave == 0) drawn = __hip_atomic_fetch_add(&tickets[pbase], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last = __builtin_amdgcn_readfirstlane(drawn) + 1u == pieces;
+        } else {
+            __syncthreads();
+            if (threadIdx.x == 0)
+                s_last = __hip_atomic_fetch_add(&tickets[pbase], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == pieces ? 1u : 0u;
+            __syncthreads();
+            last = s_last != 0u;
+            __syncthreads();                           // everybody has read s_last before a later piece rewrites it
+        }
         if (!last) continue;
         acc.zero();
-        for (uint32_t b = (uint32_t)j; b < pieces; b += 2 * G) {      // lane groups take the pieces round-robin
+        for (uint32_t b = (uint32_t)pj; b < pieces; b += 2 * PG) {      // lane groups take the pieces round-robin
             SumPiece<N> t[2];
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 t[k].zero();
-                if (active && b + (uint32_t)k * G < pieces) t[k].load_device(partial + (size_t)(pbase + b + k * G) * u.dim, c);
+                if (active && b + (uint32_t)k * PG < pieces) t[k].load_device(partial + (size_t)(pbase + b + k * PG) * u.dim, c);
             }
 #pragma unroll
             for (int k = 0; k < 2; ++k) acc.add(t[k]);
         }
-        workgroup_sum<G, GW, N>(acc, red, j, c);
-        if (j == 0) {
+        piece_sum<GW, N>(acc, red, pj, c);
+        if (pj == 0) {
             const RowPiece<BF16> row = load_row<BF16>(u, cache_w, cache_s, (int64_t)slot, c, writer);
             finish_update<GW, BF16>(u, cache_w, cache_s, (int64_t)slot, c, row, acc.template rounded<BF16>(), writer);
         }
-        if (threadIdx.x == 0)                          // the counter is zero again for the next call
+        if (threadIdx.x % kPieceThreads<GW> == 0)      // the counter is zero again for the next call
             __hip_atomic_store(&tickets[pbase], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
@@ -567,7 +599,7 @@ struct BwdLaunch {
         UpdateParams u{cfg->optimizer, cfg->lr, cfg->eps, (int)(row_bytes(cfg) / 16), cfg->dim,
                        (uint32_t)(bags > 0 ? bags : 1), cache_w_stride16(cfg), (int64_t)(sbytes / 4)};
         const int groups_per_block = kRowBlock / GW;
-        int64_t piece_blocks = n_pieces, row_blocks = ceil_div((int64_t)n_rows, (int64_t)groups_per_block * kBwdRows);
+        int64_t piece_blocks = ceil_div((int64_t)n_pieces, kRowBlock / kPieceThreads<GW>), row_blocks = ceil_div((int64_t)n_rows, (int64_t)groups_per_block * kBwdRows);
         if (piece_blocks > kMaxGridBlocks / 4) piece_blocks = kMaxGridBlocks / 4;
         if (row_blocks > kMaxGridBlocks) row_blocks = kMaxGridBlocks;
         if (row_blocks < 1) row_blocks = 1;

@@ -361,6 +361,28 @@ def test_backward_grouped_offsets_at_the_ends_of_their_type(bp):
     assert np.array_equal(got.numpy(), want.numpy())
 
 
+@pytest.mark.parametrize("D,dtype", [(4, "f32"), (8, "f32"), (12, "f32"), (16, "f32"), (20, "f32"), (64, "f32"), (256, "f32"),
+                                     (8, "bf16"), (16, "bf16"), (24, "bf16"), (128, "bf16"), (264, "bf16"), (512, "bf16")])
+def test_backward_pieces_around_their_edges(bp, D, dtype):
+    """Rows of lookups around the length up to which they are not cut, and of one to seventeen pieces, by the wavefront (rows of
+    up to four lanes) and by the workgroup: sums of small whole numbers, exact in every order."""
+    say(f"backward pieces D={D} {dtype}")
+    counts = [1, 2, 4, 5, 15, 16, 17, 18, 63, 64, 65, 255, 256, 257, 511, 512, 513, 4096, 4097]
+    C = len(counts)
+    rng = np.random.default_rng(D)
+    slots = rng.permutation(np.repeat(np.arange(C), counts)).astype(np.int32)
+    n = len(slots)
+    grad = rng.integers(-2, 3, size=(n, D)).astype(np.float32)
+    w = torch.zeros((C, D), dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    cfg = bp.make_config(1000, C, D, dtype, "sgd", lr=1.0)
+    want = np.zeros((C, D), np.float32)
+    np.subtract.at(want, slots, grad)
+    want = torch.from_numpy(want).to(w.dtype).float().numpy()
+    for run in (run_bwd, run_bwd_grouped):
+        got, _ = run(bp, cfg, w, None, slots, np.arange(n + 1), n, grad, True)
+        assert np.array_equal(got.float().numpy(), want), run.__name__
+
+
 @pytest.mark.parametrize("lens", [
     [64] * 9, [63, 65, 1, 127, 128, 129, 64], [1] * 63 + [700], [700] + [1] * 70, [64, 0, 64, 0, 0, 1, 63, 0] * 3, [0] * 200 + [640],
     [40, *[0] * 130, 40, *[1] * 20] * 2, [1, 2, 0, 3] * 50, [5000], [257, 0, 3000, 1, 1, 0, 900, *[0] * 70, 20], [1, 0] * 40 + [4000], [30] * 300],
