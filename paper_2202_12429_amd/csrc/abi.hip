@@ -155,7 +155,7 @@ struct GatherLaunch {
                   (const uint4*)table, (uint32_t)table_rows, lpr, rows, (uint32_t)n, (uint4*)sink);
         return BP_OK;
     }
-    template <int GW, bool BF16>
+    template <int GW>
     int run() {
         switch (in_flight) {
             case 1: return launch<GW, 1>();
@@ -204,7 +204,7 @@ struct ScatterLaunch {
                   (uint32_t)table_rows, lpr, rows, (uint32_t)n);
         return BP_OK;
     }
-    template <int GW, bool BF16>
+    template <int GW>
     int run() {
         switch (in_flight) {
             case 1: return launch<GW, 1>();
@@ -287,7 +287,7 @@ BP_EXPORT int bp_gather_calibration(void* sink, const void* table, int64_t table
     if (rows_in_flight != 1 && rows_in_flight != 2 && rows_in_flight != 4 && rows_in_flight != 8)
         return fail(BP_ERR_INVALID_ARG, "rows_in_flight %d: 1, 2, 4 or 8", rows_in_flight);
     GatherLaunch l{table, table_rows, row_bytes / 16, rows, n, sink, (hipStream_t)stream, rows_in_flight};
-    return dispatch_row(row_bytes / 16, false, l);
+    return dispatch_row(row_bytes / 16, l);
 }
 
 BP_EXPORT int bp_scatter_calibration(void* table, int64_t table_rows, int32_t row_bytes, const uint32_t* rows, int64_t n,
@@ -302,7 +302,7 @@ BP_EXPORT int bp_scatter_calibration(void* table, int64_t table_rows, int32_t ro
     if (rows_in_flight != 1 && rows_in_flight != 2 && rows_in_flight != 4)
         return fail(BP_ERR_INVALID_ARG, "rows_in_flight %d: 1, 2 or 4", rows_in_flight);
     ScatterLaunch l{table, table_rows, row_bytes / 16, rows, n, (hipStream_t)stream, rows_in_flight};
-    return dispatch_row(row_bytes / 16, false, l);
+    return dispatch_row(row_bytes / 16, l);
 }
 
 BP_EXPORT int bp_profile_enable(int on) {

@@ -173,7 +173,7 @@ struct DuplexLaunch {
     hipStream_t stream;
     bool stage, apply;     // which of the two steps to launch
     int64_t max_blocks;    // 0: one lane group per entry; otherwise the grid is capped and the lane groups stride
-    template <int GW, bool BF16>
+    template <int GW>
     int run() {
         const int lpr = (int)(row_bytes(cfg) / 16);
         const int slpr = cfg->optimizer == BP_ADAGRAD ? cfg->dim / 4 : 0;
@@ -207,7 +207,7 @@ struct CopyLaunch {
     bool to_backing;
     hipStream_t stream;
     int64_t max_blocks;
-    template <int GW, bool BF16>
+    template <int GW>
     int run() {
         const int lpr = (int)(row_bytes(cfg) / 16);
         const int slpr = cfg->optimizer == BP_ADAGRAD ? cfg->dim / 4 : 0;
@@ -249,12 +249,12 @@ int cache_apply_impl(const bp_config* cfg, void* cache_w, void* cache_state, voi
     if (n_evict) {
         CopyLaunch l{cfg, cache_w, cache_state, backing_w, backing_state, evict_ids, evict_slots, n_evict, true,
                      (hipStream_t)stream, grid_cap};
-        BP_TRY(dispatch_row(lpr, false, l));
+        BP_TRY(dispatch_row(lpr, l));
     }
     if (n_prefetch) {
         CopyLaunch l{cfg, cache_w, cache_state, backing_w, backing_state, prefetch_ids, prefetch_slots, n_prefetch, false,
                      (hipStream_t)stream, grid_cap};
-        BP_TRY(dispatch_row(lpr, false, l));
+        BP_TRY(dispatch_row(lpr, l));
     }
     return BP_OK;
 }
@@ -298,7 +298,7 @@ BP_EXPORT int bp_cache_apply_duplex(const bp_config* cfg, void* cache_w, void* c
     DuplexLaunch l{cfg, cache_w, cache_state, backing_w, backing_state, workspace,
                    workspace ? (char*)workspace + stage_w_bytes(cfg, n_evict) : nullptr, evict_ids, evict_slots, n_evict,
                    prefetch_ids, prefetch_slots, n_prefetch, (hipStream_t)stream, true, true, 0};
-    return dispatch_row((int)(row_bytes(cfg) / 16), false, l);
+    return dispatch_row((int)(row_bytes(cfg) / 16), l);
 }
 
 namespace bp {
@@ -327,7 +327,7 @@ int cache_stage_impl(const bp_config* cfg, const void* cache_w, const void* cach
     DuplexLaunch l{cfg, const_cast<void*>(cache_w), const_cast<void*>(cache_state), nullptr, nullptr, staging,
                    (char*)staging + stage_w_bytes(cfg, n_evict), nullptr, evict_slots, n_evict, nullptr, nullptr, 0,
                    (hipStream_t)stream, true, false, grid_cap};
-    return dispatch_row((int)(row_bytes(cfg) / 16), false, l);
+    return dispatch_row((int)(row_bytes(cfg) / 16), l);
 }
 }  // namespace bp
 
@@ -356,7 +356,7 @@ int cache_apply_staged_impl(const bp_config* cfg, void* cache_w, void* cache_sta
     DuplexLaunch l{cfg, cache_w, cache_state, backing_w, backing_state, st,
                    st ? (char*)st + stage_w_bytes(cfg, n_evict) : nullptr, evict_ids, evict_slots, n_evict, prefetch_ids,
                    prefetch_slots, n_prefetch, (hipStream_t)stream, false, true, grid_cap};
-    return dispatch_row((int)(row_bytes(cfg) / 16), false, l);
+    return dispatch_row((int)(row_bytes(cfg) / 16), l);
 }
 }  // namespace bp
 
@@ -382,7 +382,7 @@ struct HandoffLaunch {
     uint32_t* mismatch;
     hipStream_t stream;
     int64_t grid_cap;
-    template <int GW, bool BF16>
+    template <int GW>
     int run() {
         const int lpr = (int)(row_bytes(cfg) / 16);
         const int slpr = cfg->optimizer == BP_ADAGRAD ? cfg->dim / 4 : 0;
@@ -417,7 +417,7 @@ int cache_apply_handoff_impl(const bp_config* cfg, void* cache_w, void* cache_st
         return fail(BP_ERR_INVALID_ARG, "a list pointer is NULL");
     HandoffLaunch l{cfg, cache_w, cache_state, backing_w, backing_state, evict_ids, evict_slots, n_evict, prefetch_ids,
                     prefetch_slots, n_prefetch, n_early, mismatch_flag, (hipStream_t)stream, grid_cap};
-    return dispatch_row((int)(row_bytes(cfg) / 16), false, l);
+    return dispatch_row((int)(row_bytes(cfg) / 16), l);
 }
 }  // namespace bp
 

@@ -176,11 +176,11 @@ struct UpdateParams {
     int lpr;
     int dim;
     uint32_t bags;      // rows of the upstream gradient: a bag number beyond them reads row 0 instead
-    int64_t wst;        // stride of a cache row, in 16-byte pieces
+    int64_t wst;        // stride of a cache row, in pieces
     int64_t sst;        // stride of a row's optimizer state, in floats
 };
 
-// Running sum of one 16-byte piece of gradient rows.  Sums are carried in fp64 and rounded to fp32 once,
+// Running sum of one lane's piece of gradient rows.  Sums are carried in fp64 and rounded to fp32 once,
 // which makes the result independent of how a slot's lookups were cut into items (fp64 addition of
 // fp32 values is exact until the partial sums outgrow 53 bits); everything after the sum is fp32.
 template <int N>
@@ -190,8 +190,8 @@ struct SumPiece {
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] = 0.0;
     }
-    template <bool BF16>
-    __device__ __forceinline__ void add(const Piece<BF16>& p) {
+    template <bool BF16, bool SPLIT>
+    __device__ __forceinline__ void add(const Piece<BF16, N, SPLIT>& p) {
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] += (double)p.v[i];
     }
@@ -228,9 +228,9 @@ struct SumPiece {
         for (int i = 0; i < N; ++i)
             v[i] = __longlong_as_double((long long)__hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     }
-    template <bool BF16>
-    __device__ __forceinline__ Piece<BF16> rounded() const {
-        Piece<BF16> p;
+    template <typename P>
+    __device__ __forceinline__ P rounded() const {
+        P p;
 #pragma unroll
         for (int i = 0; i < N; ++i) p.v[i] = (float)v[i];
         return p;
@@ -246,23 +246,23 @@ __device__ __forceinline__ double group_sum(double x) {
 
 // The piece of lane c of row `slot` and of its optimizer state, loaded ahead of the gradient sum so that the row's
 // latency hides behind the gradient loads.
-template <bool BF16>
+template <typename P>
 struct RowPiece {
-    uint4 w_raw;
-    Piece<BF16> s;       // element-wise Adagrad state
+    typename P::Raw w_raw;
+    P s;       // element-wise Adagrad state
     float s_row;         // row-wise Adagrad state
 };
 
-template <bool BF16>
-__device__ __forceinline__ RowPiece<BF16> load_row(const UpdateParams& u, const uint4* cache_w, const float* cache_s,
+template <typename P>
+__device__ __forceinline__ RowPiece<P> load_row(const UpdateParams& u, const typename P::Unit* cache_w, const float* cache_s,
                                                    int64_t slot, int c, bool active) {
-    RowPiece<BF16> r;
-    r.w_raw = make_uint4(0, 0, 0, 0);
+    RowPiece<P> r;
+    r.w_raw = P::none();
     r.s.zero();
     r.s_row = 0.f;
     if (active) {
-        r.w_raw = cache_w[slot * u.wst + c];
-        if (u.optimizer == BP_ADAGRAD) r.s.load_f32(cache_s + slot * u.sst, c);
+        r.w_raw = P::fetch(cache_w + slot * u.wst, c, u.lpr);
+        if (u.optimizer == BP_ADAGRAD) r.s.load_f32(cache_s + slot * u.sst, c, u.lpr);
     }
     if (u.optimizer == BP_ADAGRAD_ROWWISE) r.s_row = cache_s[slot * u.sst];
     return r;
@@ -273,11 +273,11 @@ __device__ __forceinline__ RowPiece<BF16> load_row(const UpdateParams& u, const 
 // with c >= lpr carry zeros and touch no memory, and neither do the lanes of a group that is not the writer.
 // One fp32 operation per statement: step = lr*g, then for Adagrad s += g*g, den = sqrt(s) + eps, step /= den,
 // and w -= step.
-template <int GW, bool BF16>
-__device__ __forceinline__ void finish_update(const UpdateParams& u, uint4* cache_w, float* cache_s, int64_t slot, int c,
-                                              const RowPiece<BF16>& r, const Piece<BF16>& g, bool active) {
-    constexpr int N = Piece<BF16>::N;
-    Piece<BF16> w;
+template <int GW, typename P>
+__device__ __forceinline__ void finish_update(const UpdateParams& u, typename P::Unit* cache_w, float* cache_s, int64_t slot, int c,
+                                              const RowPiece<P>& r, const P& g, bool active) {
+    constexpr int N = P::N;
+    P w;
     w.decode(r.w_raw);
     if (u.optimizer == BP_SGD) {
 #pragma unroll
@@ -286,7 +286,7 @@ __device__ __forceinline__ void finish_update(const UpdateParams& u, uint4* cach
             w.v[i] = w.v[i] - step;
         }
     } else if (u.optimizer == BP_ADAGRAD) {
-        Piece<BF16> s = r.s;
+        P s = r.s;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const float gg = g.v[i] * g.v[i];
@@ -295,7 +295,7 @@ __device__ __forceinline__ void finish_update(const UpdateParams& u, uint4* cach
             const float step = (u.lr * g.v[i]) / den;
             w.v[i] = w.v[i] - step;
         }
-        if (active) s.store_f32(cache_s + slot * u.sst, c);
+        if (active) s.store_f32(cache_s + slot * u.sst, c, u.lpr);
     } else {
         double ss = 0.0;                       // mean of squares over the row: an fp64 sum, rounded once
 #pragma unroll
@@ -311,20 +311,20 @@ __device__ __forceinline__ void finish_update(const UpdateParams& u, uint4* cach
         }
         if (c == 0 && active) cache_s[slot * u.sst] = s;
     }
-    if (active) cache_w[slot * u.wst + c] = w.encode();
+    if (active) P::put(cache_w + slot * u.wst, w.encode(), c, u.lpr);
 }
 
 // Adds the gradient rows of the grouped lookups [p0, p1) into acc: bursts of four rows, the indices of the next
 // burst loaded while the rows of this one arrive.  idx holds the bag numbers of the first four lookups.
-template <bool BF16, int N>
+template <typename P, int N>
 __device__ __forceinline__ void add_gradient_rows(SumPiece<N>& acc, uint32_t (&idx)[4], uint32_t p0, uint32_t p1,
                                                   const uint32_t* __restrict__ bag_of, const float* __restrict__ grad,
                                                   const UpdateParams& u, int c) {
     for (uint32_t p = p0; p < p1; p += 4) {
-        Piece<BF16> t[4];
+        P t[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)     // the bag number is clamped where it is used: its load stays in flight until then
-            if (p + j < p1) t[j].load_f32(grad + (size_t)min(idx[j], u.bags - 1u) * u.dim, c);
+            if (p + j < p1) t[j].load_f32(grad + (size_t)min(idx[j], u.bags - 1u) * u.dim, c, u.lpr);
 #pragma unroll
         for (int j = 0; j < 4; ++j) idx[j] = p + 4 + j < p1 ? bag_of[p + 4 + j] : 0u;
 #pragma unroll
@@ -339,13 +339,17 @@ __device__ __forceinline__ void add_gradient_rows(SumPiece<N>& acc, uint32_t (&i
 // four lanes added one after the other, 14.2 this way.)
 template <int GW>
 constexpr bool kWavePieces = GW <= 4;
+// A workgroup of 256 threads, or one of sixteen lane groups, where a group's share of a piece is sixteen lookups at most: four
+// bursts one behind the other where 64-lane rows have sixteen in 256 threads (BwdLaunch has the rule).
 template <int GW>
-constexpr int kPieceThreads = kWavePieces<GW> ? kWave : kRowBlock;
+constexpr int kBwdWideBlock = GW <= 16 ? 256 : 16 * GW;
+template <int GW, int BLOCK>
+constexpr int kPieceThreads = kWavePieces<GW> ? kWave : BLOCK;
 
 // Sum over the lane groups that took a piece, in an order of its own that nothing but GW decides.  The whole sum is in the
 // first group.  By workgroup: every group leaves its sum in LDS, group 0 adds them up in group order; two barriers, and
 // `red` may be reused after the call.  By wavefront: in pairs, then pairs of pairs.
-template <int GW, int N>
+template <int GW, int BLOCK, int N>
 __device__ __forceinline__ void piece_sum(SumPiece<N>& acc, double (*red)[N][GW], int j, int c) {
     if constexpr (kWavePieces<GW>) {
 #pragma unroll
@@ -358,7 +362,7 @@ __device__ __forceinline__ void piece_sum(SumPiece<N>& acc, double (*red)[N][GW]
         __syncthreads();
         if (j == 0) {
             acc.zero();
-            for (int g = 0; g < kRowBlock / GW; ++g) {
+            for (int g = 0; g < BLOCK / GW; ++g) {
 #pragma unroll
                 for (int i = 0; i < N; ++i) acc.v[i] += red[g][i][c];
             }
@@ -373,19 +377,19 @@ __device__ __forceinline__ void piece_sum(SumPiece<N>& acc, double (*red)[N][GW]
 // Rows a lane group takes per round.  Two would have their requests in flight together, but at eight wavefronts per
 // SIMD their state spills (50.7 us), and with the registers for it only six wavefronts fit (40.8 us).
 constexpr int kBwdRows = 1;
-template <int GW, bool BF16>
-__global__ __launch_bounds__(kRowBlock, BF16 ? 4 : 8) void bwd_rows_kernel(const uint4* __restrict__ row_recs,
+template <int GW, typename P, int BLOCK>
+__global__ __launch_bounds__(BLOCK, P::N == 8 ? 4 : 8) void bwd_rows_kernel(const uint4* __restrict__ row_recs,
                                                             const uint4* __restrict__ piece_recs,
                                                             const uint32_t* __restrict__ n_rows_ptr,
                                                             const uint32_t* __restrict__ n_pieces_ptr,
                                                             uint32_t n_rows_host, uint32_t n_pieces_host,
                                                             uint32_t piece_blocks, const uint32_t* __restrict__ bag_of,
                                                             int use_first, uint32_t n, int64_t C,
-                                                            const float* __restrict__ grad, uint4* cache_w, float* cache_s,
+                                                            const float* __restrict__ grad, typename P::Unit* cache_w, float* cache_s,
                                                             double* partial, uint32_t partial_rows, uint32_t* tickets,
                                                             UpdateParams u) {
-    constexpr int N = Piece<BF16>::N;
-    constexpr int G = kRowBlock / GW;                 // lane groups per workgroup
+    constexpr int N = P::N;
+    constexpr int G = BLOCK / GW;                     // lane groups per workgroup
     const int c = threadIdx.x % GW, j = threadIdx.x / GW;
     const bool active = c < u.lpr;
 
@@ -400,7 +404,7 @@ __global__ __launch_bounds__(kRowBlock, BF16 ? 4 : 8) void bwd_rows_kernel(const
         for (uint32_t w0 = ((blockIdx.x - piece_blocks) * G + j) * kBwdRows; w0 < R; w0 += groups * kBwdRows) {
             uint4 rec[kBwdRows];
             bool ok[kBwdRows];
-            RowPiece<BF16> row[kBwdRows];
+            RowPiece<P> row[kBwdRows];
             uint32_t idx[kBwdRows][4];
 #pragma unroll
             for (int r = 0; r < kBwdRows; ++r) rec[r] = w0 + r < R ? row_recs[w0 + r] : make_uint4(0, 0, 0, 0);
@@ -408,7 +412,7 @@ __global__ __launch_bounds__(kRowBlock, BF16 ? 4 : 8) void bwd_rows_kernel(const
             for (int r = 0; r < kBwdRows; ++r) {
                 const uint32_t start = rec[r].x & kPosMask, count = rec[r].y, slot = rec[r].z;
                 ok[r] = !(rec[r].x & kLongRow) && (int64_t)slot < C && count != 0 && start < n && count <= n - start;
-                row[r] = load_row<BF16>(u, cache_w, cache_s, ok[r] ? (int64_t)slot : 0, c, active && ok[r]);
+                row[r] = load_row<P>(u, cache_w, cache_s, ok[r] ? (int64_t)slot : 0, c, active && ok[r]);
                 idx[r][0] = use_first ? rec[r].w : (ok[r] ? bag_of[start] : 0u);
 #pragma unroll
                 for (int k = 1; k < 4; ++k) idx[r][k] = ok[r] && (uint32_t)k < count ? bag_of[start + k] : 0u;
@@ -419,8 +423,8 @@ __global__ __launch_bounds__(kRowBlock, BF16 ? 4 : 8) void bwd_rows_kernel(const
                 const uint32_t start = rec[r].x & kPosMask, count = rec[r].y;
                 SumPiece<N> acc;
                 acc.zero();
-                if (active) add_gradient_rows<BF16, N>(acc, idx[r], start, start + count, bag_of, grad, u, c);
-                finish_update<GW, BF16>(u, cache_w, cache_s, (int64_t)rec[r].z, c, row[r], acc.template rounded<BF16>(), active);
+                if (active) add_gradient_rows<P, N>(acc, idx[r], start, start + count, bag_of, grad, u, c);
+                finish_update<GW, P>(u, cache_w, cache_s, (int64_t)rec[r].z, c, row[r], acc.template rounded<P>(), active);
             }
         }
         return;
@@ -428,14 +432,14 @@ __global__ __launch_bounds__(kRowBlock, BF16 ? 4 : 8) void bwd_rows_kernel(const
 
     // ---- pieces of longer rows: a wavefront or a workgroup each (kWavePieces)
     constexpr bool WAVE = kWavePieces<GW>;
-    constexpr int PG = kPieceThreads<GW> / GW;           // lane groups that share a piece
-    constexpr int PER_BLOCK = kRowBlock / kPieceThreads<GW>;
+    constexpr int PG = kPieceThreads<GW, BLOCK> / GW;           // lane groups that share a piece
+    constexpr int PER_BLOCK = BLOCK / kPieceThreads<GW, BLOCK>;
     __shared__ double red[WAVE ? 1 : G][N][GW];
     __shared__ uint32_t s_last;
     const int pj = WAVE ? j % PG : j;
-    const uint32_t P = n_pieces_ptr ? *n_pieces_ptr : n_pieces_host;
+    const uint32_t n_pieces = n_pieces_ptr ? *n_pieces_ptr : n_pieces_host;
     const bool writer = active && pj == 0;
-    for (uint32_t pi = blockIdx.x * PER_BLOCK + (WAVE ? threadIdx.x / kWave : 0u); pi < P; pi += piece_blocks * PER_BLOCK) {
+    for (uint32_t pi = blockIdx.x * PER_BLOCK + (WAVE ? threadIdx.x / kWave : 0u); pi < n_pieces; pi += piece_blocks * PER_BLOCK) {
         const uint4 r0 = piece_recs[2 * (size_t)pi], r1 = piece_recs[2 * (size_t)pi + 1];
         const uint32_t start = r0.x, count = r0.y, slot = r0.z, index = r0.w, pieces = r1.x, pbase = r1.y;
         // a record that points outside the batch or the workspace does nothing (the test is the same in every lane)
@@ -450,12 +454,12 @@ __global__ __launch_bounds__(kRowBlock, BF16 ? 4 : 8) void bwd_rows_kernel(const
         for (int k = 0; k < 4; ++k) idx[k] = p0 + k < p1 ? bag_of[p0 + k] : 0u;
         SumPiece<N> acc;
         acc.zero();
-        if (active) add_gradient_rows<BF16, N>(acc, idx, p0, p1, bag_of, grad, u, c);
-        piece_sum<GW, N>(acc, red, pj, c);
+        if (active) add_gradient_rows<P, N>(acc, idx, p0, p1, bag_of, grad, u, c);
+        piece_sum<GW, BLOCK, N>(acc, red, pj, c);
         if (direct) {      // the row is asked for only now: one more round trip after a few hundred gradient rows
             if (pj == 0) {
-                const RowPiece<BF16> row = load_row<BF16>(u, cache_w, cache_s, (int64_t)slot, c, writer);
-                finish_update<GW, BF16>(u, cache_w, cache_s, (int64_t)slot, c, row, acc.template rounded<BF16>(), writer);
+                const RowPiece<P> row = load_row<P>(u, cache_w, cache_s, (int64_t)slot, c, writer);
+                finish_update<GW, P>(u, cache_w, cache_s, (int64_t)slot, c, row, acc.template rounded<P>(), writer);
             }
             continue;
         }
@@ -493,12 +497,12 @@ __global__ __launch_bounds__(kRowBlock, BF16 ? 4 : 8) void bwd_rows_kernel(const
 #pragma unroll
             for (int k = 0; k < 2; ++k) acc.add(t[k]);
         }
-        piece_sum<GW, N>(acc, red, pj, c);
+        piece_sum<GW, BLOCK, N>(acc, red, pj, c);
         if (pj == 0) {
-            const RowPiece<BF16> row = load_row<BF16>(u, cache_w, cache_s, (int64_t)slot, c, writer);
-            finish_update<GW, BF16>(u, cache_w, cache_s, (int64_t)slot, c, row, acc.template rounded<BF16>(), writer);
+            const RowPiece<P> row = load_row<P>(u, cache_w, cache_s, (int64_t)slot, c, writer);
+            finish_update<GW, P>(u, cache_w, cache_s, (int64_t)slot, c, row, acc.template rounded<P>(), writer);
         }
-        if (threadIdx.x % kPieceThreads<GW> == 0)      // the counter is zero again for the next call
+        if (threadIdx.x % kPieceThreads<GW, BLOCK> == 0)      // the counter is zero again for the next call
             __hip_atomic_store(&tickets[pbase], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
@@ -579,6 +583,15 @@ BwdWorkspace carve_bwd(void* base, size_t cap, int64_t n, int dim) {
     return w;
 }
 
+// Two choices that change no result, us of the kernel on tables of hundreds of MB, ids uniform / skewed (of
+// 200,000 lookups 181,000 / 86,000 rows distinct):
+//   bf16 rows by fours or by eights a lane (dispatch_values).  By fours pieces are quicker in a launch that the chip holds at once
+//     (20,000 lookups, dim 64: 8.5 by fours, 11.5 by eights; without pieces 5.6, 5.2); a larger one has the more bytes in flight
+//     by eights (200,000, dim 128: 48.2 / 33.2 by fours, 42.9 / 33.5 by eights; 1.3 M: 276 / 206, 258 / 204).
+//   256 threads or sixteen lane groups, for rows of 32 and 64 lanes: the wide workgroup has a piece done sooner, which small
+//     launches wait for (fp32, dim 256, row-wise Adagrad, 20,000 lookups: 18.5 / 19.5 with 256 threads, 12.9 / 14.1 wide); large ones
+//     lose, whose rows hold a workgroup's place until its last one ends (200,000: 92 / 70, 99 / 77).  32-lane rows that leave
+//     lanes idle do not gain (dim 100, 20,000: 13.3, 13.4 either way).
 struct BwdLaunch {
     const bp_config* cfg;
     ReduceScratch red;
@@ -593,20 +606,29 @@ struct BwdLaunch {
     void* cache_s;
     hipStream_t stream;
     int64_t bags;
-    template <int GW, bool BF16>
-    int run() {
+    int64_t chips(int lanes) const { return ceil_div((int64_t)n_rows * lanes, int64_t(256) * 2048); }      // that the rows fill
+    int launch() { return dispatch_values<true>(cfg, n_pieces == 0 || chips(group_width(cfg->dim / 4)) > 1, *this); }
+    template <int GW, typename P>
+    int run(int lpr) {
+        if constexpr (kBwdWideBlock<GW> != 256) {
+            const bool wide = n_pieces > 0 && chips(GW) <= 4 && (GW == 64 || lpr == GW);
+            if (wide) return run_block<GW, P, kBwdWideBlock<GW>>(lpr);
+        }
+        return run_block<GW, P, 256>(lpr);
+    }
+    template <int GW, typename P, int BLOCK>
+    int run_block(int lpr) {
         const size_t sbytes = cfg->cache_state_stride ? (size_t)cfg->cache_state_stride : state_row_bytes(cfg);
-        UpdateParams u{cfg->optimizer, cfg->lr, cfg->eps, (int)(row_bytes(cfg) / 16), cfg->dim,
-                       (uint32_t)(bags > 0 ? bags : 1), cache_w_stride16(cfg), (int64_t)(sbytes / 4)};
-        const int groups_per_block = kRowBlock / GW;
-        int64_t piece_blocks = ceil_div((int64_t)n_pieces, kRowBlock / kPieceThreads<GW>), row_blocks = ceil_div((int64_t)n_rows, (int64_t)groups_per_block * kBwdRows);
+        UpdateParams u{cfg->optimizer, cfg->lr, cfg->eps, lpr, cfg->dim,
+                       (uint32_t)(bags > 0 ? bags : 1), cache_w_stride16(cfg) * P::kPerVec, (int64_t)(sbytes / 4)};
+        int64_t piece_blocks = ceil_div((int64_t)n_pieces, BLOCK / kPieceThreads<GW, BLOCK>), row_blocks = ceil_div((int64_t)n_rows, BLOCK / GW);
         if (piece_blocks > kMaxGridBlocks / 4) piece_blocks = kMaxGridBlocks / 4;
         if (row_blocks > kMaxGridBlocks) row_blocks = kMaxGridBlocks;
         if (row_blocks < 1) row_blocks = 1;
-        BP_LAUNCH(K_BWD_REDUCE_UPDATE, (bwd_rows_kernel<GW, BF16>), dim3((unsigned)(piece_blocks + row_blocks)),
-                  dim3(kRowBlock), 0, stream, row_recs, piece_recs, n_rows_ptr, n_pieces_ptr, n_rows, n_pieces,
-                  (uint32_t)piece_blocks, bag_of, use_first, (uint32_t)n, cfg->capacity, grad, (uint4*)cache_w,
-                  (float*)cache_s, red.partial, red.partial_rows, red.tickets, u);
+        BP_LAUNCH(K_BWD_REDUCE_UPDATE, (bwd_rows_kernel<GW, P, BLOCK>), dim3((unsigned)(piece_blocks + row_blocks)), dim3(BLOCK), 0,
+                  stream, row_recs, piece_recs, n_rows_ptr, n_pieces_ptr, n_rows, n_pieces, (uint32_t)piece_blocks, bag_of,
+                  use_first, (uint32_t)n, cfg->capacity, grad, (typename P::Unit*)cache_w, (float*)cache_s, red.partial,
+                  red.partial_rows, red.tickets, u);
         return BP_OK;
     }
 };
@@ -680,7 +702,7 @@ BP_EXPORT int bp_embbag_bwd_update(const bp_config* cfg, void* cache_w, void* ca
 
     BwdLaunch l{cfg, w.red, w.row_recs, w.piece_recs, n_rows, n_pieces, (uint32_t)n, (uint32_t)piece_capacity_for(n), sbags,
                 1, n, grad_out, cache_w, cache_state, stream, bags};
-    return dispatch_row((int)(row_bytes(cfg) / 16), cfg->weight_dtype == BP_BF16, l);
+    return l.launch();
 }
 
 // ---- grouped variant: the plan already lists the batch's lookups grouped by row ---------------------------------
@@ -756,7 +778,7 @@ BP_EXPORT int bp_embbag_bwd_update_grouped(const bp_config* cfg, void* cache_w, 
     BwdLaunch l{cfg, w.red, reinterpret_cast<const uint4*>(row_recs), reinterpret_cast<const uint4*>(piece_recs), nullptr,
                 nullptr, (uint32_t)n_rows, (uint32_t)n_pieces, bag_of, bag_offsets == nullptr, n, grad_out, cache_w,
                 cache_state, stream, bags};
-    return dispatch_row((int)(row_bytes(cfg) / 16), cfg->weight_dtype == BP_BF16, l);
+    return l.launch();
 }
 
 // ---- the grouped variant for callers that cannot allocate ---------------------------------------------------------

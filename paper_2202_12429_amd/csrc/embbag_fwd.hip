@@ -18,8 +18,8 @@ namespace {
 // round trip like the others (4.2 M rows of 256 bytes in 163,840 bags: 129 us with the last rows one by one and no slots
 // fetched ahead, 118 this way, 9.1 TB/s of rows).  How deep a burst pays is the rule at FwdLaunch.
 constexpr uint32_t kNoSlot = 0xffffffffu;      // past the end of every cache
-template <int GW, bool BF16, int BURST>
-__global__ __launch_bounds__(kRowBlock) void embbag_fwd_kernel(const uint4* __restrict__ cache_w,
+template <int GW, typename P, int BURST>
+__global__ __launch_bounds__(kRowBlock) void embbag_fwd_kernel(const typename P::Raw* __restrict__ cache_w,
                                                                const int32_t* __restrict__ slots,
                                                                const int64_t* __restrict__ bag_off, int64_t bags,
                                                                int64_t n, int64_t C, int lpr, int64_t wst, int dim,
@@ -27,7 +27,7 @@ __global__ __launch_bounds__(kRowBlock) void embbag_fwd_kernel(const uint4* __re
     const int64_t bag = ((int64_t)blockIdx.x * kRowBlock + threadIdx.x) / GW;
     const int c = threadIdx.x % GW;
     if (bag >= bags || c >= lpr) return;
-    Piece<BF16> acc;
+    P acc;
     acc.zero();
     int64_t k = bag_off[bag];
     int64_t end = bag_off[bag + 1];
@@ -48,14 +48,14 @@ __global__ __launch_bounds__(kRowBlock) void embbag_fwd_kernel(const uint4* __re
     };
     fetch_slots(k);
     for (; k < end; k += BURST) {
-        uint4 raw[BURST];
+        typename P::Raw raw[BURST];
 #pragma unroll
         for (int j = 0; j < BURST; ++j)
-            raw[j] = s[j] < (uint64_t)C ? cache_w[(int64_t)s[j] * wst + c] : make_uint4(0, 0, 0, 0);
+            raw[j] = s[j] < (uint64_t)C ? cache_w[(int64_t)s[j] * wst + c] : P::none();
         if (k + BURST < end) fetch_slots(k + BURST);      // one test: bags of a single burst pass it by
 #pragma unroll
         for (int j = 0; j < BURST; ++j) {       // in lookup order; a row that is not there adds zeros
-            Piece<BF16> p;
+            P p;
             p.decode(raw[j]);
             acc.add(p);
         }
@@ -67,8 +67,8 @@ __global__ __launch_bounds__(kRowBlock) void embbag_fwd_kernel(const uint4* __re
 // kRowBlock * U consecutive pieces; the division by lpr uses inv = floor(2^32 / lpr) + 1, exact for the dividends
 // that occur here (below 2^32 / lpr).
 constexpr int kFlatPieces = 4;
-template <bool BF16, int U>
-__global__ __launch_bounds__(kRowBlock) void embbag_fwd_onehot_kernel(const uint4* __restrict__ cache_w,
+template <typename P, int U>
+__global__ __launch_bounds__(kRowBlock) void embbag_fwd_onehot_kernel(const typename P::Raw* __restrict__ cache_w,
                                                                       const int32_t* __restrict__ slots, int64_t bags,
                                                                       int64_t C, uint32_t lpr, uint32_t inv, int64_t wst,
                                                                       int dim, float* __restrict__ out) {
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(kRowBlock) void embbag_fwd_onehot_kernel(const uint
     const uint32_t r0 = (uint32_t)(base - bag0 * lpr);
     int64_t bag[U];
     uint32_t c[U], s[U];
-    uint4 raw[U];
+    typename P::Raw raw[U];
 #pragma unroll
     for (int j = 0; j < U; ++j) {
         const uint32_t q = r0 + j * kRowBlock + threadIdx.x;
@@ -88,11 +88,11 @@ __global__ __launch_bounds__(kRowBlock) void embbag_fwd_onehot_kernel(const uint
     }
 #pragma unroll
     for (int j = 0; j < U; ++j)
-        raw[j] = s[j] < (uint64_t)C ? cache_w[(int64_t)s[j] * wst + c[j]] : make_uint4(0, 0, 0, 0);
+        raw[j] = s[j] < (uint64_t)C ? cache_w[(int64_t)s[j] * wst + c[j]] : P::none();
 #pragma unroll
     for (int j = 0; j < U; ++j) {
         if (bag[j] >= bags) continue;
-        Piece<BF16> p;
+        P p;
         p.decode(raw[j]);
         p.store_f32_stream(out + bag[j] * dim, (int)c[j]);
     }
@@ -105,12 +105,12 @@ __global__ __launch_bounds__(kRowBlock) void embbag_fwd_onehot_kernel(const uint
 // [0, piece_blocks) take the pieces of long rows (every lane group fetches the row and writes it to its share of the
 // piece's bags), the others take one row of up to kRowMax lookups per lane group.
 constexpr int kFwdRows = 2;
-template <int GW, bool BF16>
+template <int GW, typename P>
 __global__ __launch_bounds__(kRowBlock) void embbag_fwd_rows_kernel(const uint4* __restrict__ row_recs,
                                                                     const uint4* __restrict__ piece_recs, uint32_t n_rows,
                                                                     uint32_t n_pieces, uint32_t piece_blocks,
                                                                     const uint32_t* __restrict__ grouped, uint32_t n,
-                                                                    int64_t C, const uint4* __restrict__ cache_w, int lpr,
+                                                                    int64_t C, const typename P::Raw* __restrict__ cache_w, int lpr,
                                                                     int64_t wst, int dim, float* __restrict__ out) {
     constexpr int G = kRowBlock / GW;
     static_assert(kPiece <= (uint32_t)kRowBlock, "a lane group's share of a piece is at most one lookup per lane");
@@ -122,7 +122,8 @@ __global__ __launch_bounds__(kRowBlock) void embbag_fwd_rows_kernel(const uint4*
         // their first lookups, all in flight together, then the stores
         const uint32_t groups = (gridDim.x - piece_blocks) * G;
         for (uint32_t w0 = ((blockIdx.x - piece_blocks) * G + j) * kFwdRows; w0 < n_rows; w0 += groups * kFwdRows) {
-            uint4 rec[kFwdRows], raw[kFwdRows];
+            uint4 rec[kFwdRows];
+            typename P::Raw raw[kFwdRows];
             uint32_t start[kFwdRows], count[kFwdRows], bag[kFwdRows][4];
 #pragma unroll
             for (int r = 0; r < kFwdRows; ++r) rec[r] = w0 + r < n_rows ? row_recs[w0 + r] : make_uint4(0, 0, 0, 0);
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(kRowBlock) void embbag_fwd_rows_kernel(const uint4*
                 count[r] = rec[r].y;
                 const uint32_t slot = rec[r].z;
                 if ((rec[r].x & kLongRow) || (int64_t)slot >= C || start[r] >= n || count[r] > n - start[r]) count[r] = 0;
-                raw[r] = count[r] ? cache_w[(int64_t)slot * wst + c] : make_uint4(0, 0, 0, 0);
+                raw[r] = count[r] ? cache_w[(int64_t)slot * wst + c] : P::none();
                 bag[r][0] = rec[r].w;                     // the row's first lookup: its position is its bag
 #pragma unroll
                 for (int k = 1; k < 4; ++k) bag[r][k] = (uint32_t)k < count[r] ? grouped[start[r] + k] : n;
@@ -140,18 +141,18 @@ __global__ __launch_bounds__(kRowBlock) void embbag_fwd_rows_kernel(const uint4*
 #pragma unroll
             for (int r = 0; r < kFwdRows; ++r) {
                 if (count[r] == 0) continue;
-                Piece<BF16> p;
+                P p;
                 p.decode(raw[r]);
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    if ((uint32_t)k < count[r] && bag[r][k] < n) p.store_f32(out + (size_t)bag[r][k] * dim, c);
+                    if ((uint32_t)k < count[r] && bag[r][k] < n) p.store_f32(out + (size_t)bag[r][k] * dim, c, lpr);
                 for (uint32_t k = 4; k < count[r]; k += 4) {      // the few rows of 5 .. kRowMax lookups
                     uint32_t more[4];
 #pragma unroll
                     for (int q = 0; q < 4; ++q) more[q] = k + q < count[r] ? grouped[start[r] + k + q] : n;
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
-                        if (more[q] < n) p.store_f32(out + (size_t)more[q] * dim, c);
+                        if (more[q] < n) p.store_f32(out + (size_t)more[q] * dim, c, lpr);
                 }
             }
         }
@@ -167,12 +168,17 @@ __global__ __launch_bounds__(kRowBlock) void embbag_fwd_rows_kernel(const uint4*
         const uint32_t per = (count + G - 1) / G;
         const uint32_t p0 = min((uint32_t)j * per, count), share = min(per, count - p0);
         const uint32_t mine = (uint32_t)c < share ? grouped[start + p0 + c] : n;
-        Piece<BF16> p;
+        P p;
         if (active) p.decode(cache_w[(int64_t)slot * wst + c]);
+        constexpr int STEP = GW < 16 ? GW : 16;
 #pragma unroll
-        for (int t = 0; t < GW; ++t) {
-            const uint32_t bag = __shfl(mine, t, GW);
-            if (active && bag < n) p.store_f32(out + (size_t)bag * dim, c);
+        for (int t0 = 0; t0 < GW; t0 += STEP) {
+            if ((uint32_t)t0 >= per) break;              // per <= GW, and the same in the whole workgroup
+#pragma unroll
+            for (int t = t0; t < t0 + STEP; ++t) {
+                const uint32_t bag = __shfl(mine, t, GW);
+                if (active && bag < n) p.store_f32(out + (size_t)bag * dim, c, lpr);
+            }
         }
     }
 }
@@ -186,15 +192,15 @@ struct FwdRowsLaunch {
     int64_t n_rows, n_pieces, bags;
     float* out;
     hipStream_t stream;
-    template <int GW, bool BF16>
-    int run() {
+    template <int GW, typename P>
+    int run(int lpr) {
         int64_t piece_blocks = n_pieces, row_blocks = ceil_div(n_rows, (int64_t)(kRowBlock / GW) * kFwdRows);
         if (piece_blocks > kMaxGridBlocks / 4) piece_blocks = kMaxGridBlocks / 4;
         if (row_blocks > kMaxGridBlocks) row_blocks = kMaxGridBlocks;
         if (row_blocks < 1) row_blocks = 1;
-        BP_LAUNCH(K_FWD, (embbag_fwd_rows_kernel<GW, BF16>), dim3((unsigned)(piece_blocks + row_blocks)), dim3(kRowBlock), 0,
+        BP_LAUNCH(K_FWD, (embbag_fwd_rows_kernel<GW, P>), dim3((unsigned)(piece_blocks + row_blocks)), dim3(kRowBlock), 0,
                   stream, row_recs, piece_recs, (uint32_t)n_rows, (uint32_t)n_pieces, (uint32_t)piece_blocks, grouped,
-                  (uint32_t)bags, cfg->capacity, (const uint4*)cache_w, (int)(row_bytes(cfg) / 16), cache_w_stride16(cfg),
+                  (uint32_t)bags, cfg->capacity, (const typename P::Raw*)cache_w, lpr, cache_w_stride16(cfg) * P::kPerVec,
                   cfg->dim, out);
         return BP_OK;
     }
@@ -207,10 +213,6 @@ struct FwdRowsLaunch {
 //     2,688 / 2,673).
 //   short bags take four: at a mean of 6.5 the two are about even, and below it the guards of rows that are not there are
 //     the cost (f32, 32,768 bags of mean 1: dim 64 3.7 / 4.3, dim 256 8.3 / 9.1).
-//   but short bags of bf16 rows that fill a group of 8 lanes or more take eight from 2^20 lanes on (dim 256, 65,535 bags:
-//     20.7 / 15.2 at a mean of 1, 18.5 / 17.6 at 2, even from there on).  Such launches are nearly all pooled stores, and
-//     the deeper form holds fewer wavefronts on a CU; rows that leave lanes idle do not gain (dim 192, mean 1: 11.0 / 13.0).
-constexpr int64_t kManyLanes = int64_t(1) << 20;            // twice what the chip holds
 struct FwdLaunch {
     const bp_config* cfg;
     const void* cache_w;
@@ -219,25 +221,23 @@ struct FwdLaunch {
     int64_t bags, n_lookups;
     float* out;
     hipStream_t stream;
-    template <int GW, bool BF16>
-    int run() {
-        const int lpr = (int)(row_bytes(cfg) / 16);
+    template <int GW, typename P>
+    int run(int lpr) {
         if (bag_off == nullptr) {
             const uint32_t inv = lpr == 1 ? 0u : (uint32_t)((uint64_t(1) << 32) / (uint32_t)lpr + 1);
             const dim3 flat((unsigned)ceil_div(bags * lpr, (int64_t)kRowBlock * kFlatPieces));
-            BP_LAUNCH(K_FWD, (embbag_fwd_onehot_kernel<BF16, kFlatPieces>), flat, dim3(kRowBlock), 0, stream,
-                      (const uint4*)cache_w, slots, bags, cfg->capacity, (uint32_t)lpr, inv, cache_w_stride16(cfg), cfg->dim, out);
+            BP_LAUNCH(K_FWD, (embbag_fwd_onehot_kernel<P, kFlatPieces>), flat, dim3(kRowBlock), 0, stream,
+                      (const typename P::Raw*)cache_w, slots, bags, cfg->capacity, (uint32_t)lpr, inv, cache_w_stride16(cfg) * P::kPerVec, cfg->dim, out);
             return BP_OK;
         }
         const dim3 grid((unsigned)ceil_div(bags * GW, kRowBlock));
         const bool long_bags = 2 * n_lookups >= 13 * bags;
-        const bool deep = long_bags || (BF16 && GW >= 8 && lpr == GW && bags * GW >= kManyLanes);
-        if (deep)
-            BP_LAUNCH(K_FWD, (embbag_fwd_kernel<GW, BF16, 8>), grid, dim3(kRowBlock), 0, stream, (const uint4*)cache_w, slots,
-                      bag_off, bags, n_lookups, cfg->capacity, lpr, cache_w_stride16(cfg), cfg->dim, out);
+        if (long_bags)
+            BP_LAUNCH(K_FWD, (embbag_fwd_kernel<GW, P, 8>), grid, dim3(kRowBlock), 0, stream, (const typename P::Raw*)cache_w, slots,
+                      bag_off, bags, n_lookups, cfg->capacity, lpr, cache_w_stride16(cfg) * P::kPerVec, cfg->dim, out);
         else
-            BP_LAUNCH(K_FWD, (embbag_fwd_kernel<GW, BF16, 4>), grid, dim3(kRowBlock), 0, stream, (const uint4*)cache_w, slots,
-                      bag_off, bags, n_lookups, cfg->capacity, lpr, cache_w_stride16(cfg), cfg->dim, out);
+            BP_LAUNCH(K_FWD, (embbag_fwd_kernel<GW, P, 4>), grid, dim3(kRowBlock), 0, stream, (const typename P::Raw*)cache_w, slots,
+                      bag_off, bags, n_lookups, cfg->capacity, lpr, cache_w_stride16(cfg) * P::kPerVec, cfg->dim, out);
         return BP_OK;
     }
 };
@@ -258,7 +258,7 @@ BP_EXPORT int bp_embbag_fwd(const bp_config* cfg, const void* cache_w, const int
     if (!cache_w || !out || (n_lookups && !lookup_slots)) return fail(BP_ERR_INVALID_ARG, "NULL pointer");
     if (((uintptr_t)cache_w | (uintptr_t)out) & 15) return fail(BP_ERR_INVALID_ARG, "cache_w and out must be 16-byte aligned");
     FwdLaunch l{cfg, cache_w, lookup_slots, bag_offsets, bags, n_lookups, out, (hipStream_t)stream};
-    return dispatch_row((int)(row_bytes(cfg) / 16), cfg->weight_dtype == BP_BF16, l);
+    return dispatch_values<false>(cfg, bag_offsets && 2 * n_lookups >= 5 * bags, l);      // pooling by eights from a mean of 2.5
 }
 
 BP_EXPORT int bp_embbag_fwd_grouped(const bp_config* cfg, const void* cache_w, const int32_t* grouped_lookups,
@@ -275,5 +275,5 @@ BP_EXPORT int bp_embbag_fwd_grouped(const bp_config* cfg, const void* cache_w, c
         return fail(BP_ERR_INVALID_ARG, "cache_w, out, row_recs and piece_recs must be 16-byte aligned");
     FwdRowsLaunch l{cfg, cache_w, reinterpret_cast<const uint32_t*>(grouped_lookups), reinterpret_cast<const uint4*>(row_recs),
                     reinterpret_cast<const uint4*>(piece_recs), n_rows, n_pieces, bags, out, (hipStream_t)stream};
-    return dispatch_row((int)(row_bytes(cfg) / 16), cfg->weight_dtype == BP_BF16, l);
+    return dispatch_values<false>(cfg, false, l);
 }

@@ -59,7 +59,7 @@ def random_bags(rng, bags, max_len, C, allow_empty=True):
 
 
 @pytest.mark.parametrize("D,dtype", [(16, "f32"), (48, "f32"), (64, "f32"), (128, "bf16"), (8, "bf16"), (4, "f32"),
-                                     (256, "f32")])
+                                     (256, "f32"), (256, "bf16"), (264, "bf16"), (512, "bf16"), (24, "bf16")])
 @pytest.mark.parametrize("max_len", [1, 50])
 def test_forward(bp, D, dtype, max_len):
     say(f"forward D={D} {dtype} max_len={max_len}")
@@ -105,7 +105,8 @@ def test_forward_bags_around_the_bursts(bp, D, dtype):
     # bursts of four for short bags, of eight from a mean of 6.5 lookups on; rows of one lane, of 16 and of 64
     (4, "f32", 300, 5), (4, "f32", 300, 12), (4, "f32", 300, 14), (4, "f32", 300, 25), (64, "f32", 300, 3), (64, "f32", 300, 12),
     (64, "f32", 300, 14), (256, "f32", 300, 12), (512, "bf16", 300, 12), (64, "f32", 65537, 14),
-    # short bags of bf16 rows that fill their lanes: bursts of eight from 2^20 lanes on; rows that do not: of four
+    # bf16 rows: four elements a lane for bags of less than 2.5 lookups in the mean, eight from there on
+    (64, "bf16", 300, 4), (64, "bf16", 300, 5), (64, "bf16", 300, 6), (8, "bf16", 300, 2), (8, "bf16", 300, 14), (264, "bf16", 300, 2),
     (64, "bf16", 131071, 4), (64, "bf16", 131072, 4), (512, "bf16", 16384, 2), (96, "bf16", 65536, 4)])
 def test_forward_bags_in_every_form(bp, D, dtype, bags, longest):
     """Bags of 0 to `longest` lookups in turn (mean longest / 2), around the sizes where another form of the pooled forward
@@ -381,6 +382,36 @@ def test_backward_pieces_around_their_edges(bp, D, dtype):
     for run in (run_bwd, run_bwd_grouped):
         got, _ = run(bp, cfg, w, None, slots, np.arange(n + 1), n, grad, True)
         assert np.array_equal(got.float().numpy(), want), run.__name__
+
+
+@pytest.mark.parametrize("D,dtype,optimizer", [(64, "bf16", "adagrad_rowwise"), (264, "bf16", "adagrad"), (256, "bf16", "sgd"),
+                                               (512, "bf16", "adagrad_rowwise"), (100, "f32", "adagrad_rowwise"), (256, "f32", "adagrad")])
+@pytest.mark.parametrize("rows,hot", [(700, 0), (700, 40), (33000, 0), (33000, 40)])
+def test_backward_in_every_form(bp, D, dtype, optimizer, rows, hot):
+    """Batches without long rows and with some, of few rows and of more than the chip holds lanes for: bf16 rows by fours and
+    by eights a lane, workgroups of 256 threads and wide ones, to the same bits (gradients of small whole numbers, whose
+    sums are exact in every order) as the oracle."""
+    say(f"backward D={D} {dtype} {optimizer} rows={rows} hot={hot}")
+    rng = np.random.default_rng(rows + hot + D)
+    counts = np.ones(rows, np.int64)
+    counts[rng.integers(0, rows, size=hot)] = rng.integers(17, 400, size=hot)
+    slots = rng.permutation(np.repeat(np.arange(rows), counts)).astype(np.int32)
+    n = len(slots)
+    grad = rng.integers(-2, 3, size=(n, D)).astype(np.float32)
+    w = random_cache(rows, D, dtype, D)
+    op = oracle.OPTIMIZERS[optimizer]
+    state = rng.uniform(0.5, 2.0, size=oracle.state_shape(rows, D, op)).astype(np.float32) if op != oracle.SGD else None
+    cfg = bp.make_config(10 * rows, rows, D, dtype, optimizer, lr=0.01, eps=1e-8)
+    got_w, got_s = run_bwd_grouped(bp, cfg, w, state, slots, np.arange(n + 1), n, grad, True)
+    want_w = cache_numpy(w)
+    want_s = None if state is None else state.copy()
+    oracle.train_iter(want_w, want_s, D, oracle.DTYPES[dtype], op, 0.01, 1e-8, slots, np.arange(n + 1), grad, want_out=False)
+    if dtype == "bf16":
+        assert np.array_equal(cache_numpy(got_w), want_w)
+        assert want_s is None or np.array_equal(got_s, want_s)
+    else:
+        helpers.assert_weights_close(got_w.numpy(), want_w)
+        np.testing.assert_allclose(got_s, want_s, rtol=1e-4, atol=1e-9)
 
 
 @pytest.mark.parametrize("lens", [
