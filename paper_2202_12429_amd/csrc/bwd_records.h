@@ -1,5 +1,5 @@
 // Row and piece records of a batch grouped by row (bp_row_rec / bp_piece_rec of the C header): what both makers of
-// them, the planner's grouping step and bp_embbag_bwd_update's own scans, and the kernels that walk them share.
+// them, the planner's grouping step and bp_embbag_bwd_update itself, and the kernels that walk them share.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -710,13 +710,16 @@ inline size_t sort_temp_words(int64_t n) {
 
 // One pass.  The histogram reads `up`, the scatter reads `src`: the same elements, but a source that has to fetch
 // more than the digit needs may leave that to the scatter alone.
-// `ready`: the pass's histogram (counts[digit][tile], as the upsweep writes it) made by a kernel of the caller's that
-// read the same elements anyway; NULL: the upsweep makes it.
+// `ready`: the pass's histogram made by a kernel of the caller's that read the same elements anyway, counts[digit][tile], or
+// in `counts` itself, laid out as the upsweep would; NULL: the upsweep makes it.
+template <typename Tiles>
+inline bool sort_counts_by_tile(uint32_t ntiles) { return Tiles::IPT <= SmallTiles::IPT && ntiles <= kSortFewTiles; }
+
 template <typename K, int RB, typename Tiles, typename Up, typename Src, bool VALS>
 int radix_sort_pass(const Up& up, const Src& src, K* kout, uint32_t* vout, int64_t n, int bit, int nb, uint32_t* counts,
                     uint32_t* totals, uint32_t ntiles, hipStream_t stream, const uint32_t* ready) {
     const uint32_t mask = (1u << nb) - 1u;
-    const bool few = Tiles::IPT <= SmallTiles::IPT && ntiles <= kSortFewTiles && !ready;
+    const bool few = sort_counts_by_tile<Tiles>(ntiles) && (!ready || ready == counts);
     if (!ready)
         BP_LAUNCH(K_SORT_UPSWEEP, (sort_upsweep_kernel<K, RB, Tiles, Up>), dim3(sort_grid(ntiles)), dim3(Tiles::BLOCK), 0, stream,
                   up, (uint32_t)n, bit, mask, counts, ntiles, few ? 1 : 0);
@@ -795,13 +798,13 @@ int radix_sort_from(const Up& first_up, const Src& first, K* const kbuf[2], uint
 // sorted output ended up.  n < 2^32 - 8192.
 template <typename K, typename Tiles>
 int radix_sort_pairs(K* keys_a, K* keys_b, uint32_t* vals_a, uint32_t* vals_b, int64_t n, int begin_bit, int end_bit,
-                     uint32_t* temp, hipStream_t stream, bool* result_in_b) {
+                     uint32_t* temp, hipStream_t stream, bool* result_in_b, const uint32_t* first_counts = nullptr) {
     K* const kbuf[2] = {keys_b, keys_a};
     uint32_t* const vbuf[2] = {vals_b, vals_a};
     int result = -1;
     const SortArrays<K> in{keys_a, vals_a};
     BP_TRY((radix_sort_from<K, Tiles, SortArrays<K>, SortArrays<K>, true>(in, in, kbuf, vbuf, n, begin_bit, end_bit, temp, stream,
-                                                                        &result)));
+                                                                        &result, first_counts)));
     *result_in_b = result == 0;
     return BP_OK;
 }
@@ -817,20 +820,6 @@ int radix_sort_numbered(K* keys_a, K* keys_b, uint32_t* vals_a, uint32_t* vals_b
     const SortKeysNumbered<K> in{keys_a};
     BP_TRY((radix_sort_from<K, Tiles, SortArrays<K>, SortKeysNumbered<K>, true>(up, in, kbuf, vbuf, n, begin_bit, end_bit, temp,
                                                                               stream, &result)));
-    *result_in_b = result == 0;
-    return BP_OK;
-}
-
-// The same for keys alone.
-template <typename K, typename Tiles>
-int radix_sort_keys(K* keys_a, K* keys_b, int64_t n, int begin_bit, int end_bit, uint32_t* temp, hipStream_t stream,
-                    bool* result_in_b) {
-    K* const kbuf[2] = {keys_b, keys_a};
-    uint32_t* const vbuf[2] = {nullptr, nullptr};
-    int result = -1;
-    const SortArrays<K> in{keys_a, nullptr};
-    BP_TRY((radix_sort_from<K, Tiles, SortArrays<K>, SortArrays<K>, false>(in, in, kbuf, vbuf, n, begin_bit, end_bit, temp, stream,
-                                                                         &result)));
     *result_in_b = result == 0;
     return BP_OK;
 }

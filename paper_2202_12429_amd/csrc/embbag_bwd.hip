@@ -17,6 +17,7 @@
 // Every order of addition is fixed by the records, never by timing: results are bit-identical run to run.
 // The summed gradient is rounded to fp32 once; the optimizer step itself is fp32 arithmetic.
 #include <algorithm>
+#include <type_traits>
 
 #include "bwd_records.h"
 #include "common.h"
@@ -27,23 +28,62 @@ namespace bp {
 namespace {
 
 // ---- 1. keys ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void bwd_keys_kernel(const int32_t* __restrict__ slots, const int64_t* __restrict__ bag_off,
-                                                       int64_t n, int64_t bags, int64_t C, uint32_t* __restrict__ keys,
-                                                       uint32_t* __restrict__ vals) {
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k >= n) return;
-    const uint32_t s = (uint32_t)slots[k];
-    keys[k] = s < (uint64_t)C ? s : (uint32_t)C;     // out-of-range slots sort behind every real one
-    uint32_t bag = (uint32_t)k;
-    if (bag_off) {                                   // largest b with bag_off[b] <= k
-        int64_t lo = 0, hi = bags;                   // bag_off[lo] <= k < bag_off[hi]
-        while (hi - lo > 1) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (bag_off[mid] <= k) lo = mid; else hi = mid;
+// Keys (slots) and values (bags) of the sort, and its first histogram on the way, which reads the same keys: a workgroup takes
+// one tile of that sort.  The searches of a thread's lookups go step by step together, so that a step costs one round trip.
+// Clears the counters of bwd_records_kernel.  Bound by the searches' round trips (19,000 lookups in 4,291 bags: 8.2 us, where keys
+// and histogram by themselves took 4.9 and 2.9 and a launch more).
+template <int RB, typename Tiles>
+__global__ __launch_bounds__(Tiles::BLOCK) void bwd_keys_kernel(const int32_t* __restrict__ slots, const int64_t* __restrict__ bag_off,
+                                                                uint32_t n, uint32_t bags, int64_t C, uint32_t* __restrict__ keys,
+                                                                uint32_t* __restrict__ vals, uint32_t mask,
+                                                                uint32_t* __restrict__ counts, uint32_t ntiles, int by_tile,
+                                                                uint64_t* __restrict__ counters) {
+    constexpr int IPT = Tiles::IPT, BLOCK = Tiles::BLOCK, RADIX = 1 << RB;
+    __shared__ uint32_t hist[RADIX];
+    const uint32_t tile = blockIdx.x;
+    for (int d = threadIdx.x; d < RADIX; d += BLOCK) hist[d] = 0;
+    if (tile == 0 && threadIdx.x < 2) counters[threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t first = tile * (uint32_t)Tiles::TILE + threadIdx.x;
+    uint32_t s[IPT], bag[IPT];
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) s[j] = first + j * BLOCK < n ? (uint32_t)slots[first + j * BLOCK] : 0u;
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) bag[j] = first + j * BLOCK;
+    if (bag_off) {                                       // largest b with bag_off[b] <= the lookup
+        uint32_t hi[IPT];                                // bag_off[bag] <= lookup < bag_off[hi]
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) {
+            bag[j] = 0;
+            hi[j] = bags;
         }
-        bag = (uint32_t)lo;
+        for (uint32_t range = bags; range > 1; range = (range + 1) / 2) {
+            int64_t at[IPT];
+#pragma unroll
+            for (int j = 0; j < IPT; ++j) at[j] = bag_off[bag[j] + (hi[j] - bag[j]) / 2];      // asked for by all, done or not
+#pragma unroll
+            for (int j = 0; j < IPT; ++j) {
+                const uint32_t mid = bag[j] + (hi[j] - bag[j]) / 2;
+                const bool below = at[j] <= (int64_t)first + j * BLOCK;
+                if (hi[j] - bag[j] > 1) {
+                    bag[j] = below ? mid : bag[j];
+                    hi[j] = below ? hi[j] : mid;
+                }
+            }
+        }
     }
-    vals[k] = bag;
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+        const uint32_t k = first + j * BLOCK;
+        if (k < n) {
+            const uint32_t key = s[j] < (uint64_t)C ? s[j] : (uint32_t)C;     // out-of-range slots sort behind every real one
+            keys[k] = key;
+            vals[k] = bag[j];
+            count_digit(hist, key & mask);
+        }
+    }
+    __syncthreads();
+    for (int d = threadIdx.x; d < RADIX; d += BLOCK) counts[by_tile ? (size_t)tile * RADIX + d : (size_t)d * ntiles + tile] = hist[d];
 }
 
 // Grouped variant: the plan lists lookup positions grouped by row; the gradient row of a position is its bag.
@@ -508,38 +548,115 @@ __global__ __launch_bounds__(BLOCK, P::N == 8 ? 4 : 8) void bwd_rows_kernel(cons
 }
 
 // ---- records made on the device (bp_embbag_bwd_update: one batch, lookups sorted by slot) -------------------------
-// First scan, over the sorted lookups: a row starts where the slot changes; row r's first sorted position goes to
-// row_pos[r].
-struct RowHeadIn {
-    const uint32_t* keys;
-    __device__ __forceinline__ uint32_t operator()(int64_t p) const { return (p == 0 || keys[p] != keys[p - 1]) ? 1u : 0u; }
-};
-struct RowHeadOut {
-    uint32_t* row_pos;
-    __device__ __forceinline__ void operator()(int64_t p, uint32_t exc, uint32_t inc) const {
-        if (inc != exc) row_pos[exc] = (uint32_t)p;
+// One launch, without a scan: a workgroup counts the rows and pieces that start among its lookups, draws as many places in the
+// two lists from a counter each, and writes them there.  The lists' order follows the draws, and nothing depends on it: every
+// record is complete in itself, and a row of several pieces owns a stretch of partial sums of its own.  A row ends where the slot
+// changes: within the window as a rule, else it is searched for.  (19,000 lookups: the scans over lookups and rows took four
+// launches and 12.7 us, one of 7.0 this way; the whole call on 4 M lookups 565 -> 313 us, on 500 22.0 -> 14.9.)
+template <int ROUNDS>
+__global__ __launch_bounds__(kScanBlock) void bwd_records_kernel(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ bags,
+                                                                 uint32_t n, uint4* __restrict__ row_recs,
+                                                                 uint4* __restrict__ piece_recs, unsigned long long* counters) {
+    constexpr int WAVES = kScanBlock / kWave;
+    constexpr uint32_t TILE = kScanBlock * ROUNDS, WINDOW = TILE + 256;
+    __shared__ uint32_t wave_rows[WAVES], row_base;
+    __shared__ uint64_t wave_pieces[WAVES], piece_base;
+    __shared__ uint32_t win[WINDOW];                     // the tile's keys and the next 256: nearly every row ends in them
+    const int w = threadIdx.x / kWave, lane = lane_id();
+    const uint32_t tile = blockIdx.x * TILE, end = min(n - tile, WINDOW);
+    for (uint32_t t = threadIdx.x; t < end; t += kScanBlock) win[t] = keys[tile + t];
+    const uint32_t of_wave = tile + w * (kWave * ROUNDS);
+    uint32_t before = of_wave > 0 && of_wave <= n ? keys[of_wave - 1] : 0u;
+    __syncthreads();
+    uint32_t key[ROUNDS], count[ROUNDS];                 // count: of the row that starts here, 0 where none does
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint32_t p = of_wave + r * kWave + lane;
+        key[r] = p < n ? win[p - tile] : 0u;
     }
-};
-// Second scan, over the rows (RowPiecesIn): every row writes its record, a long row its piece records.
-struct RowRecordOut {
-    const uint32_t* row_pos;
-    const uint32_t* n_rows;
-    uint32_t n;
-    const uint32_t* keys;      // sorted slots
-    const uint32_t* bags;      // bag of every sorted lookup
-    uint4* row_recs;
-    uint4* piece_recs;
-    __device__ __forceinline__ void operator()(int64_t r, uint64_t exc, uint64_t inc) const {
-        const uint32_t R = *n_rows;
-        if (r >= (int64_t)R) return;
-        const uint32_t start = row_pos[r];
-        const uint32_t count = (r + 1 < (int64_t)R ? row_pos[r + 1] : n) - start;
-        const uint32_t slot = keys[start];
-        const uint32_t pc = pieces_of(count);
-        row_recs[r] = make_uint4(start | (pc ? kLongRow : 0u), count, slot, bags[start]);
-        if (pc) write_pieces(piece_recs, (uint32_t)exc, pc, start, count, slot, (uint32_t)(exc >> 32), 0u);
+    uint32_t rows = 0;
+    uint64_t pieces = 0;                                 // pieces, and in the high word those of rows of several
+    const auto packed = [](uint32_t lookups) {
+        const uint32_t pc = pieces_of(lookups);
+        return (uint64_t)pc | ((uint64_t)(pc > 1 ? pc : 0u) << 32);
+    };
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint32_t p = of_wave + r * kWave + lane;
+        const uint32_t left = lane_below(key[r], before);
+        before = lane_value(key[r], kWave - 1);
+        const bool head = p < n && (p == 0 || key[r] != left);
+        count[r] = 0;
+        if (head) {
+            // the key at lo - 1 is the row's, the one at hi is not (or hi is n)
+            uint32_t lo = p - tile + 1, hi = min(end, lo + kRowMax - 1);
+            if (hi < end && win[hi] == key[r]) {
+                lo = hi + 1;
+                hi = end;
+            }
+            while (lo < hi) {
+                const uint32_t mid = lo + (hi - lo) / 2;
+                if (win[mid] == key[r]) lo = mid + 1; else hi = mid;
+            }
+            lo += tile;
+            if (lo == tile + end && lo < n) {            // it goes on behind the window
+                hi = lo;
+                for (uint32_t step = WINDOW; hi < n && keys[hi] == key[r]; step *= 2) {
+                    lo = hi + 1;
+                    hi = step < n - hi ? hi + step : n;
+                }
+                while (lo < hi) {
+                    const uint32_t mid = lo + (hi - lo) / 2;
+                    if (keys[mid] == key[r]) lo = mid + 1; else hi = mid;
+                }
+            }
+            count[r] = lo - p;
+        }
+        rows += (uint32_t)__popcll(__ballot(head));
+        if (__ballot(count[r] > kRowMax)) pieces += wave_reduce(packed(count[r]), AddOp());
     }
-};
+    if (lane == 0) {
+        wave_rows[w] = rows;
+        wave_pieces[w] = pieces;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t r = 0;
+        uint64_t pc = 0;
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) {
+            r += wave_rows[k];
+            pc += wave_pieces[k];
+        }
+        row_base = r ? (uint32_t)atomicAdd(counters, (unsigned long long)r) : 0u;
+        piece_base = pc ? (uint64_t)atomicAdd(counters + 1, (unsigned long long)pc) : 0u;
+    }
+    __syncthreads();
+    uint32_t row = row_base;
+    uint64_t piece = piece_base;
+    for (int k = 0; k < w; ++k) {
+        row += wave_rows[k];
+        piece += wave_pieces[k];
+    }
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint32_t p = of_wave + r * kWave + lane;
+        const uint64_t heads = __ballot(count[r] != 0);
+        uint64_t mine = piece;
+        if (__ballot(count[r] > kRowMax)) {
+            const uint64_t inc = wave_inclusive_scan(packed(count[r]), AddOp());
+            mine = piece + lane_below(inc, uint64_t(0));
+            piece += lane_value(inc, kWave - 1);
+        }
+        if (count[r]) {
+            const uint32_t pc = pieces_of(count[r]);
+            const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(heads >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)heads, row));
+            row_recs[at] = make_uint4(p | (pc ? kLongRow : 0u), count[r], key[r], bags[p]);
+            if (pc) write_pieces(piece_recs, (uint32_t)mine, pc, p, count[r], key[r], (uint32_t)(mine >> 32), 0u);
+        }
+        row += (uint32_t)__popcll(heads);
+    }
+}
 
 // ---- workspace -------------------------------------------------------------------------------
 constexpr int64_t kLargeSort = int64_t(1) << 21;
@@ -558,8 +675,8 @@ ReduceScratch carve_reduce(Carver& c, int64_t n, int dim) {
 
 struct BwdWorkspace {
     ReduceScratch red;
-    uint32_t *keys_a, *keys_b, *vals_a, *vals_b, *sort_temp, *row_pos, *scan_partials32;
-    uint64_t* scan_partials64;
+    uint32_t *keys_a, *keys_b, *vals_a, *vals_b, *sort_temp;
+    uint64_t* counters;        // rows; pieces, and in the high word those of rows of several
     uint4 *row_recs, *piece_recs;
     size_t bytes;
 };
@@ -574,9 +691,7 @@ BwdWorkspace carve_bwd(void* base, size_t cap, int64_t n, int dim) {
     w.vals_a = c.take<uint32_t>(m);
     w.vals_b = c.take<uint32_t>(m);
     w.sort_temp = c.take<uint32_t>(n >= kLargeSort ? sort_temp_words<LargeTiles>(n) : sort_temp_words<SmallTiles>(n));
-    w.row_pos = c.take<uint32_t>(m);
-    w.scan_partials32 = c.take<uint32_t>(scan_partials(n));
-    w.scan_partials64 = c.take<uint64_t>(scan_partials(n));
+    w.counters = c.take<uint64_t>(2);
     w.row_recs = c.take<uint4>(m);
     w.piece_recs = c.take<uint4>(2 * piece_capacity_for(n));
     w.bytes = c.used();
@@ -677,28 +792,37 @@ BP_EXPORT int bp_embbag_bwd_update(const bp_config* cfg, void* cache_w, void* ca
         return fail(BP_ERR_WORKSPACE_TOO_SMALL, "workspace %zu < required %zu bytes", workspace_bytes, w.bytes);
     w.red.tickets = tickets;
 
-    BP_LAUNCH(K_BWD_KEYS, bwd_keys_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, stream, lookup_slots, bag_offsets, n,
-              bags, cfg->capacity, w.keys_a, w.vals_a);
     bool in_b = false;
     const int key_bits = bits_for(cfg->capacity + 1);
-    if (n >= kLargeSort)
-        BP_TRY((radix_sort_pairs<uint32_t, LargeTiles>(w.keys_a, w.keys_b, w.vals_a, w.vals_b, n, 0, key_bits, w.sort_temp,
-                                                      stream, &in_b)));
-    else
-        BP_TRY((radix_sort_pairs<uint32_t, SmallTiles>(w.keys_a, w.keys_b, w.vals_a, w.vals_b, n, 0, key_bits, w.sort_temp,
-                                                      stream, &in_b)));
+    const auto keys_and_sort = [&](auto tiles) {
+        typedef decltype(tiles) Tiles;
+        const uint32_t ntiles = sort_num_tiles<Tiles>(n);
+        const int nb = radix_first_pass_bits(0, key_bits), by_tile = sort_counts_by_tile<Tiles>(ntiles);
+        const uint32_t mask = (1u << nb) - 1u;
+        if (nb > 8)
+            BP_LAUNCH(K_BWD_KEYS, (bwd_keys_kernel<9, Tiles>), dim3(ntiles), dim3(Tiles::BLOCK), 0, stream, lookup_slots, bag_offsets,
+                      (uint32_t)n, (uint32_t)bags, cfg->capacity, w.keys_a, w.vals_a, mask, w.sort_temp, ntiles, by_tile, w.counters);
+        else
+            BP_LAUNCH(K_BWD_KEYS, (bwd_keys_kernel<8, Tiles>), dim3(ntiles), dim3(Tiles::BLOCK), 0, stream, lookup_slots, bag_offsets,
+                      (uint32_t)n, (uint32_t)bags, cfg->capacity, w.keys_a, w.vals_a, mask, w.sort_temp, ntiles, by_tile, w.counters);
+        return radix_sort_pairs<uint32_t, Tiles>(w.keys_a, w.keys_b, w.vals_a, w.vals_b, n, 0, key_bits, w.sort_temp, stream, &in_b,
+                                                 w.sort_temp);
+    };
+    if (n >= kLargeSort) BP_TRY(keys_and_sort(LargeTiles{}));
+    else BP_TRY(keys_and_sort(SmallTiles{}));
     const uint32_t* skeys = in_b ? w.keys_b : w.keys_a;
     const uint32_t* sbags = in_b ? w.vals_b : w.vals_a;
 
-    // rows, then their records; the counts stay on the device
-    BP_TRY((device_scan<uint32_t, AddOp, RowHeadIn, RowHeadOut>(RowHeadIn{skeys}, RowHeadOut{w.row_pos}, n, w.scan_partials32,
-                                                               AddOp(), 0u, stream)));
-    const uint32_t* n_rows = w.scan_partials32 + scan_num_tiles(n);
-    BP_TRY((device_scan<uint64_t, AddOp, RowPiecesIn, RowRecordOut>(
-        RowPiecesIn{w.row_pos, n_rows, (uint32_t)n},
-        RowRecordOut{w.row_pos, n_rows, (uint32_t)n, skeys, sbags, w.row_recs, w.piece_recs}, n, w.scan_partials64, AddOp(),
-        uint64_t(0), stream)));
-    const uint32_t* n_pieces = reinterpret_cast<const uint32_t*>(w.scan_partials64 + scan_num_tiles(n));   // low word
+    // the records; the counts stay on the device
+    unsigned long long* const counters = reinterpret_cast<unsigned long long*>(w.counters);
+    if (n <= kScanSmall)
+        BP_LAUNCH(K_BWD_ITEMS, bwd_records_kernel<1>, dim3((unsigned)ceil_div(n, kScanBlock)), dim3(kScanBlock), 0, stream, skeys,
+                  sbags, (uint32_t)n, w.row_recs, w.piece_recs, counters);
+    else
+        BP_LAUNCH(K_BWD_ITEMS, bwd_records_kernel<8>, dim3((unsigned)ceil_div(n, 8 * kScanBlock)), dim3(kScanBlock), 0, stream, skeys,
+                  sbags, (uint32_t)n, w.row_recs, w.piece_recs, counters);
+    const uint32_t* n_rows = reinterpret_cast<const uint32_t*>(w.counters);              // low words
+    const uint32_t* n_pieces = reinterpret_cast<const uint32_t*>(w.counters + 1);
 
     BwdLaunch l{cfg, w.red, w.row_recs, w.piece_recs, n_rows, n_pieces, (uint32_t)n, (uint32_t)piece_capacity_for(n), sbags,
                 1, n, grad_out, cache_w, cache_state, stream, bags};

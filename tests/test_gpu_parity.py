@@ -384,6 +384,28 @@ def test_backward_pieces_around_their_edges(bp, D, dtype):
         assert np.array_equal(got.float().numpy(), want), run.__name__
 
 
+@pytest.mark.parametrize("n", [1, 255, 257, 32 * 1024, 32 * 1024 + 1, 1 << 18, (1 << 18) + 1, 600_001, (1 << 21) + 5])
+@pytest.mark.parametrize("spread", [3, 40, 10 ** 6])
+def test_backward_sorting_records(bp, n, spread):
+    """The sorting backward pass around the sizes where its tiles and its record kernel's stretches change: rows that end inside
+    a workgroup's window, at its end, and long behind it; bags of several lookups; sums of small whole numbers, exact in
+    every order."""
+    say(f"sorting backward, {n} lookups in up to {spread} rows")
+    rng = np.random.default_rng(n + spread)
+    D, C = 4, 70_001
+    slots = (rng.integers(0, spread, size=n) * 7919 % (C + 2)).astype(np.int32)      # a few of them out of range
+    cuts = np.unique(rng.integers(0, n + 1, size=n // 3 + 1))
+    off = np.concatenate([[0], cuts, [n, n]]).astype(np.int64)
+    bags = len(off) - 1
+    grad = rng.integers(-1, 2, size=(bags, D)).astype(np.float32)
+    got, _ = run_bwd(bp, bp.make_config(C, C, D, "f32", "sgd", lr=1.0), torch.zeros((C, D)), None, slots, off, bags, grad, False)
+    bag = np.repeat(np.arange(bags), np.diff(off))
+    want = np.zeros((C + 2, D))
+    for d in range(D):
+        want[:, d] = -np.bincount(slots, weights=grad[bag, d], minlength=C + 2)
+    assert np.array_equal(got.numpy(), want[:C].astype(np.float32))
+
+
 @pytest.mark.parametrize("D,dtype,optimizer", [(64, "bf16", "adagrad_rowwise"), (264, "bf16", "adagrad"), (256, "bf16", "sgd"),
                                                (512, "bf16", "adagrad_rowwise"), (100, "f32", "adagrad_rowwise"), (256, "f32", "adagrad")])
 @pytest.mark.parametrize("rows,hot", [(700, 0), (700, 40), (33000, 0), (33000, 40)])
