@@ -136,7 +136,7 @@ def load_library():
 
 
 def _check(status: int, **info):
-    if status != 0:
+    if status:
         lib = load_library()
         msg = lib.bp_last_error_message().decode() or lib.bp_error_string(status).decode()
         raise BagpipeError(status, msg, **info)
@@ -156,6 +156,8 @@ def _ptr(t) -> Optional[int]:
     """Device (or pinned-host) address of a torch tensor, a raw integer address, or None."""
     if t is None:
         return None
+    if type(t) is _Span:
+        return t.ptr
     if isinstance(t, int):
         return t
     assert t.is_contiguous(), "tensors passed to the library must be contiguous"
@@ -188,19 +190,31 @@ def _span(t, a: int, b: int):
     """What t[a:b] is to the library (same bounds as a slice); the caller keeps t."""
     if t is None or not t.is_contiguous():
         return t[a:b]
-    a, b, _ = slice(a, b).indices(t.shape[0])
-    return _Span(t.data_ptr() + a * t.stride(0) * t.element_size(), b - a if b > a else 0)
+    if not 0 <= a <= b <= t.size(0):
+        a, b, _ = slice(a, b).indices(t.size(0))
+    return _Span(t.data_ptr() + a * t.stride(0) * t.itemsize, b - a if b > a else 0)
+
+
+def _count(t) -> int:
+    """Entries of a list that may be None."""
+    return 0 if t is None else t.n if type(t) is _Span else int(t.numel())
+
+
+def _rows(t) -> int:
+    return 0 if t is None else t.n if type(t) is _Span else int(t.shape[0])
 
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
-        if torch.cuda.is_initialized():
+        cuda = torch.cuda
+        if cuda.is_initialized():
             try:                             # the number alone: a Stream object costs the host more than the call itself
-                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+                raw = torch._C
+                return raw._cuda_getCurrentRawStream(raw._cuda_getDevice()) or None
             except AttributeError:           # a torch without these calls
                 pass
-        return torch.cuda.current_stream().cuda_stream or None
+        return cuda.current_stream().cuda_stream or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None
@@ -403,8 +417,8 @@ def bp_cache_apply(cfg: bp_config, cache_w, cache_state, backing_w, backing_stat
                    prefetch_ids, prefetch_slots, stream=None) -> None:
     """Lists are device tensors (slices of a Plan); a None or empty list means nothing to do.  backing_* may be
     pinned host tensors (device-visible) or device tensors."""
-    n_e = 0 if evict_ids is None else int(evict_ids.numel())
-    n_p = 0 if prefetch_ids is None else int(prefetch_ids.numel())
+    n_e = _count(evict_ids)
+    n_p = _count(prefetch_ids)
     _check(load_library().bp_cache_apply(
         ctypes.byref(cfg), _ptr(cache_w), _ptr(cache_state), _ptr(backing_w), _ptr(backing_state),
         _ptr(evict_ids) if n_e else None, _ptr(evict_slots) if n_e else None, n_e,
@@ -420,8 +434,8 @@ def bp_cache_apply_duplex_workspace_bytes(cfg: bp_config, n_evict: int) -> int:
 def bp_cache_apply_duplex(cfg: bp_config, cache_w, cache_state, backing_w, backing_state, evict_ids, evict_slots,
                           prefetch_ids, prefetch_slots, workspace, stream=None) -> None:
     """bp_cache_apply with both link directions busy at once; needs id-disjoint lists (any plan with L_eff >= 2)."""
-    n_e = 0 if evict_ids is None else int(evict_ids.numel())
-    n_p = 0 if prefetch_ids is None else int(prefetch_ids.numel())
+    n_e = _count(evict_ids)
+    n_p = _count(prefetch_ids)
     _check(load_library().bp_cache_apply_duplex(
         ctypes.byref(cfg), _ptr(cache_w), _ptr(cache_state), _ptr(backing_w), _ptr(backing_state),
         _ptr(evict_ids) if n_e else None, _ptr(evict_slots) if n_e else None, n_e,
@@ -433,8 +447,8 @@ def bp_cache_apply_handoff(cfg: bp_config, cache_w, cache_state, backing_w, back
                            prefetch_ids, prefetch_slots, n_early: int, mismatch_flag=None, stream=None) -> None:
     """Maintenance in one launch for lists of a FIFO plan: the last n_prefetch - n_early prefetches take the slots of
     the first evictions, in order.  mismatch_flag: uint32/int32 device tensor of one element, set to 1 on a bad pair."""
-    n_e = 0 if evict_ids is None else int(evict_ids.numel())
-    n_p = 0 if prefetch_ids is None else int(prefetch_ids.numel())
+    n_e = _count(evict_ids)
+    n_p = _count(prefetch_ids)
     _check(load_library().bp_cache_apply_handoff(
         ctypes.byref(cfg), _ptr(cache_w), _ptr(cache_state), _ptr(backing_w), _ptr(backing_state),
         _ptr(evict_ids) if n_e else None, _ptr(evict_slots) if n_e else None, n_e,
@@ -444,7 +458,7 @@ def bp_cache_apply_handoff(cfg: bp_config, cache_w, cache_state, backing_w, back
 
 def bp_cache_stage(cfg: bp_config, cache_w, cache_state, evict_slots, staging, stream=None) -> None:
     """First half of bp_cache_apply_duplex: evicted rows -> staging area (their slots may then be refilled)."""
-    n_e = 0 if evict_slots is None else int(evict_slots.numel())
+    n_e = _count(evict_slots)
     _check(load_library().bp_cache_stage(ctypes.byref(cfg), _ptr(cache_w), _ptr(cache_state),
                                          _ptr(evict_slots) if n_e else None, n_e, _ptr(staging),
                                          0 if staging is None else int(staging.numel()), _stream(stream)))
@@ -453,8 +467,8 @@ def bp_cache_stage(cfg: bp_config, cache_w, cache_state, evict_slots, staging, s
 def bp_cache_apply_staged(cfg: bp_config, cache_w, cache_state, backing_w, backing_state, evict_ids, evict_slots,
                           staging, prefetch_ids, prefetch_slots, stream=None) -> None:
     """Second half: staged rows -> backing table and prefetched rows -> cache in one launch (id-disjoint lists)."""
-    n_e = 0 if evict_ids is None else int(evict_ids.numel())
-    n_p = 0 if prefetch_ids is None else int(prefetch_ids.numel())
+    n_e = _count(evict_ids)
+    n_p = _count(prefetch_ids)
     _check(load_library().bp_cache_apply_staged(
         ctypes.byref(cfg), _ptr(cache_w), _ptr(cache_state), _ptr(backing_w), _ptr(backing_state),
         _ptr(evict_ids) if n_e else None, _ptr(evict_slots) if n_e else None, n_e, _ptr(staging),
@@ -520,7 +534,7 @@ def bp_pipeline_end(handle: int, stream=None) -> None:
 # ---------------------------------------------------------------------------------------------------
 def bp_embbag_fwd(cfg: bp_config, cache_w, lookup_slots, bag_offsets, bags: int, out, stream=None) -> None:
     """bag_offsets None = one lookup per bag.  out: fp32 device tensor [bags, dim], written in place."""
-    n = int(lookup_slots.numel())
+    n = _count(lookup_slots)
     _check(load_library().bp_embbag_fwd(ctypes.byref(cfg), _ptr(cache_w), _ptr(lookup_slots), _ptr(bag_offsets), n,
                                         int(bags), _ptr(out), _stream(stream)))
 
@@ -529,10 +543,10 @@ def bp_embbag_fwd_grouped(cfg: bp_config, cache_w, grouped_lookups, row_recs, pi
                           stream=None) -> None:
     """One lookup per bag.  grouped_lookups / row_recs / piece_recs: one batch's slices of the plan's grouping arrays
     (piece_recs may be None or empty).  out: fp32 device tensor [bags, dim], written in place."""
-    assert int(grouped_lookups.numel()) == int(bags)
-    n_pieces = 0 if piece_recs is None else int(piece_recs.shape[0])
+    assert _count(grouped_lookups) == int(bags)
+    n_pieces = _rows(piece_recs)
     _check(load_library().bp_embbag_fwd_grouped(ctypes.byref(cfg), _ptr(cache_w), _ptr(grouped_lookups), _ptr(row_recs),
-                                                int(row_recs.shape[0]), _ptr(piece_recs) if n_pieces else None, n_pieces,
+                                                _rows(row_recs), _ptr(piece_recs) if n_pieces else None, n_pieces,
                                                 int(bags), _ptr(out), _stream(stream)))
 
 
@@ -549,8 +563,8 @@ def bp_embbag_bwd_update_workspace_bytes(cfg: bp_config, n_lookups: int, bags: i
 def bp_embbag_bwd_update(cfg: bp_config, cache_w, cache_state, lookup_slots, bag_offsets, bags: int, grad_out,
                          workspace, tickets, stream=None) -> None:
     """tickets: see bwd_tickets()."""
-    n = int(lookup_slots.numel())
-    assert tickets.numel() * tickets.element_size() >= bp_embbag_bwd_ticket_bytes(n)
+    n = _count(lookup_slots)
+    assert tickets.numel() * tickets.itemsize >= _ticket_bytes(n)
     _check(load_library().bp_embbag_bwd_update(ctypes.byref(cfg), _ptr(cache_w), _ptr(cache_state),
                                                _ptr(lookup_slots), _ptr(bag_offsets), n, int(bags), _ptr(grad_out),
                                                _ptr(workspace), int(workspace.numel()), _ptr(tickets), _stream(stream)))
@@ -567,6 +581,11 @@ def bp_embbag_bwd_ticket_bytes(n_lookups: int) -> int:
     return int(load_library().bp_embbag_bwd_ticket_bytes(int(n_lookups)))
 
 
+def _ticket_bytes(n_lookups: int) -> int:
+    """bp_embbag_bwd_ticket_bytes without a call of the library: a training step asks on every batch."""
+    return (n_lookups // BWD_PIECE * 2 + 2) * 4
+
+
 def bwd_tickets(max_lookups: int, device="cuda"):
     """The counters of the backward entry points for batches of up to max_lookups lookups: they must be zero when a
     call starts and every call leaves them zero, so they are allocated zeroed, once."""
@@ -578,12 +597,12 @@ def bp_embbag_bwd_update_grouped(cfg: bp_config, cache_w, cache_state, grouped_l
                                  bag_offsets, bags: int, grad_out, workspace, tickets, stream=None) -> None:
     """grouped_lookups / row_recs / piece_recs: one batch's slices of the plan's grouping arrays (piece_recs may be
     None or empty).  tickets: see bwd_tickets()."""
-    n = int(grouped_lookups.numel())
-    n_pieces = 0 if piece_recs is None else int(piece_recs.shape[0])
-    assert tickets.numel() * tickets.element_size() >= bp_embbag_bwd_ticket_bytes(n)
+    n = _count(grouped_lookups)
+    n_pieces = _rows(piece_recs)
+    assert tickets.numel() * tickets.itemsize >= _ticket_bytes(n)
     _check(load_library().bp_embbag_bwd_update_grouped(
         ctypes.byref(cfg), _ptr(cache_w), _ptr(cache_state), _ptr(grouped_lookups), _ptr(row_recs),
-        int(row_recs.shape[0]), _ptr(piece_recs) if n_pieces else None, n_pieces,
+        _rows(row_recs), _ptr(piece_recs) if n_pieces else None, n_pieces,
         _ptr(bag_offsets), n, int(bags), _ptr(grad_out), _ptr(workspace), int(workspace.numel()), _ptr(tickets),
         _stream(stream)))
 
@@ -602,11 +621,11 @@ def bp_embbag_bwd_update_grouped_static_bytes(cfg: bp_config, n_lookups: int, ba
 def bp_embbag_bwd_update_grouped_static(cfg: bp_config, cache_w, cache_state, grouped_lookups, row_recs, piece_recs,
                                         bag_offsets, bags: int, grad_out, stream=None) -> None:
     """bp_embbag_bwd_update_grouped without workspace and tickets: the library's own fixed scratch array serves."""
-    n = int(grouped_lookups.numel())
-    n_pieces = 0 if piece_recs is None else int(piece_recs.shape[0])
+    n = _count(grouped_lookups)
+    n_pieces = _rows(piece_recs)
     _check(load_library().bp_embbag_bwd_update_grouped_static(
         ctypes.byref(cfg), _ptr(cache_w), _ptr(cache_state), _ptr(grouped_lookups), _ptr(row_recs),
-        int(row_recs.shape[0]), _ptr(piece_recs) if n_pieces else None, n_pieces,
+        _rows(row_recs), _ptr(piece_recs) if n_pieces else None, n_pieces,
         _ptr(bag_offsets), n, int(bags), _ptr(grad_out), _stream(stream)))
 
 

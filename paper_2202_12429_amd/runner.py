@@ -158,27 +158,31 @@ class CachedEmbeddingTrainer:
         a, b = int(off[i]), int(off[i + 1])
         return getattr(p, which + "_ids")[a:b], getattr(p, which + "_slots")[a:b]
 
-    def _spans(self, which: str, i: int):
+    def _evictions(self, i: int):
         p = self.plan_
-        off = getattr(p, which + "_offsets")
-        a, b = int(off[i]), int(off[i + 1])
-        return B._span(getattr(p, which + "_ids"), a, b), B._span(getattr(p, which + "_slots"), a, b)
+        a, b = p.evict_offsets.item(i), p.evict_offsets.item(i + 1)
+        return B._span(p.evict_ids, a, b), B._span(p.evict_slots, a, b)
+
+    def _prefetches(self, i: int):
+        p = self.plan_
+        a, b = p.prefetch_offsets.item(i), p.prefetch_offsets.item(i + 1)
+        return B._span(p.prefetch_ids, a, b), B._span(p.prefetch_slots, a, b)
 
     def slots(self, i: int):
-        a, b = int(self.iter_offsets[i]), int(self.iter_offsets[i + 1])
+        a, b = self.iter_offsets.item(i), self.iter_offsets.item(i + 1)
         return self.plan_.lookup_slots[a:b]
 
     # ---- (2)
     def maintain(self, i: int, stream=None) -> None:
-        e_ids, e_slots = self._spans("evict", i - 1) if i > 0 else (None, None)
+        e_ids, e_slots = self._evictions(i - 1) if i > 0 else (None, None)
         disjoint = self.plan_.L_eff >= 2          # a row evicted after batch i-1 is then not fetched for batch i
         if i == 0 and self._carried_evict is not None:
             e_ids, e_slots, l_prev = self._carried_evict
             disjoint = disjoint and l_prev >= 2    # ... under the lookahead the eviction was decided with
             self._carried_evict = None
-        p_ids, p_slots = self._spans("prefetch", i)
+        p_ids, p_slots = self._prefetches(i)
         if self._early is not None and disjoint and not self._n_emit:
-            n_early = int(self._early[i]) if i > 0 else int(p_ids.numel())
+            n_early = self._early.item(i) if i > 0 else B._count(p_ids)
             B.bp_cache_apply_handoff(self.cfg, self._cw, self._cs, self.backing_w, self.backing_state, e_ids,
                                      e_slots, p_ids, p_slots, n_early, self._mismatch, stream=stream)
         elif self.duplex and disjoint:
@@ -219,7 +223,7 @@ class CachedEmbeddingTrainer:
 
     def flush(self, stream=None) -> None:
         T = self._n_emit if self._n_emit else self.iter_offsets.shape[0] - 1
-        e_ids, e_slots = self._spans("evict", T - 1)
+        e_ids, e_slots = self._evictions(T - 1)
         B.bp_cache_apply(self.cfg, self._cw, self._cs, self.backing_w, self.backing_state, e_ids, e_slots,
                          None, None, stream=stream)
         if self._early is not None and int(self._mismatch.item()) != 0:       # synchronises
@@ -230,14 +234,14 @@ class CachedEmbeddingTrainer:
         """grouped: walk the plan's row records instead of a slot per lookup (bags of one lookup only); None: do so
         when the plan carries no slot map."""
         p = self.plan_
-        a, b = int(self.iter_offsets[i]), int(self.iter_offsets[i + 1])
+        a, b = self.iter_offsets.item(i), self.iter_offsets.item(i + 1)
         self._reserve(b - a, bags)
         out = self._out[:bags] if out is None else out
         if (p.lookup_slots is None) if grouped is None else grouped:
             if bag_offsets_dev is not None:
                 raise ValueError("the forward pass over the row records takes bags of one lookup; plan with slot_map=True")
-            ka, kb = int(p.keep_offsets[i]), int(p.keep_offsets[i + 1])
-            pa, pb = int(p.piece_offsets[i]), int(p.piece_offsets[i + 1])
+            ka, kb = p.keep_offsets.item(i), p.keep_offsets.item(i + 1)
+            pa, pb = p.piece_offsets.item(i), p.piece_offsets.item(i + 1)
             B.bp_embbag_fwd_grouped(self.cfg, self._cw, B._span(p.grouped_lookups, a, b),
                                     B._span(p.row_recs, ka, kb), B._span(p.piece_recs, pa, pb), bags, out, stream=stream)
         else:
@@ -247,14 +251,14 @@ class CachedEmbeddingTrainer:
     # ---- (4)
     def backward_update(self, i: int, bag_offsets_dev, bags: int, grad_out, stream=None, grouped: Optional[bool] = None) -> None:
         p = self.plan_
-        a, b = int(self.iter_offsets[i]), int(self.iter_offsets[i + 1])
+        a, b = self.iter_offsets.item(i), self.iter_offsets.item(i + 1)
         self._reserve(b - a, bags)
         use_grouped = (p.grouped_lookups is not None) if grouped is None else grouped
         if use_grouped:
             if b == a:
                 return
-            ka, kb = int(p.keep_offsets[i]), int(p.keep_offsets[i + 1])       # a batch's rows are its keep-list entries
-            pa, pb = int(p.piece_offsets[i]), int(p.piece_offsets[i + 1])
+            ka, kb = p.keep_offsets.item(i), p.keep_offsets.item(i + 1)       # a batch's rows are its keep-list entries
+            pa, pb = p.piece_offsets.item(i), p.piece_offsets.item(i + 1)
             B.bp_embbag_bwd_update_grouped(self.cfg, self._cw, self._cs, B._span(p.grouped_lookups, a, b),
                                            B._span(p.row_recs, ka, kb), B._span(p.piece_recs, pa, pb),
                                            bag_offsets_dev, bags, grad_out, self._bwd_ws, self._tickets, stream=stream)

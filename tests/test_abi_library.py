@@ -107,3 +107,23 @@ def test_current_stream_without_torch_internals(monkeypatch, missing):
     monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
     assert binding._stream(None) == 77
+
+
+def test_spans_are_slices():
+    """A span names what the tensor's slice would, whatever the bounds; anything not contiguous stays a slice."""
+    import torch
+    from paper_2202_12429_amd import binding
+    for t in (torch.arange(40, dtype=torch.int64), torch.arange(160, dtype=torch.int32).view(40, 4), torch.zeros(0, dtype=torch.int32)):
+        for a, b in ((0, 0), (0, 40), (3, 17), (17, 3), (-5, 40), (0, -1), (35, 60), (60, 70)):
+            want, got = t[a:b], binding._span(t, a, b)
+            assert (got.numel(), got.shape[0], binding._count(got), binding._rows(got)) == (want.shape[0],) * 4, (a, b)
+            assert want.numel() == 0 or binding._ptr(got) == want.data_ptr()
+    strided = torch.arange(40).view(20, 2)[:, 0]
+    assert torch.equal(binding._span(strided, 2, 5), strided[2:5])
+    assert binding._count(None) == binding._rows(None) == 0
+
+
+def test_ticket_bytes_are_the_librarys(lib):
+    from paper_2202_12429_amd import binding
+    for n in (0, 1, 255, 256, 257, 1 << 20, (1 << 31) - 1):
+        assert binding._ticket_bytes(n) == lib.bp_embbag_bwd_ticket_bytes(n)
