@@ -1182,8 +1182,10 @@ PlanWorkspace carve_plan(void* base, size_t cap, int64_t N, int T, int Lcap, boo
     const size_t n = (size_t)(N > 0 ? N : 1);
     w.keys_a = c.take<uint64_t>(n);
     w.keys_b = c.take<uint64_t>(n);
-    w.head_mask = c.take<uint64_t>((n + 63) / 64);
-    w.pairs_before = c.take<uint32_t>((n + 63) / 64);
+    const size_t words = (n + 63) / 64;            // the masks and their counts, in one piece: no more than a few lookups need
+    w.head_mask = c.take<uint64_t>(2 * words + (words + 1) / 2);
+    w.miss_mask = w.head_mask + words;
+    w.pairs_before = reinterpret_cast<uint32_t*>(w.head_mask + 2 * words);
     w.tile_batch = c.take<int32_t>((n >> kPosTileShift) + 2);
     // a workspace that is large enough for N lookups is so for fewer, which may have more tiles
     const int64_t in_small_tiles = std::min(N, kPlanSmallSort);
@@ -1208,7 +1210,6 @@ PlanWorkspace carve_plan(void* base, size_t cap, int64_t N, int T, int Lcap, boo
     w.iter_off = c.take<int64_t>(T + 1);
     w.rec_a = c.take<uint64_t>(n);
     w.rec_b = c.take<uint64_t>(n);
-    w.miss_mask = c.take<uint64_t>((n + 63) / 64);
     w.val2_a = c.take<uint32_t>(n);
     w.val2_b = c.take<uint32_t>(n);
     w.missord = c.take<uint32_t>(n);
