@@ -204,6 +204,16 @@ def _rows(t) -> int:
     return 0 if t is None else t.n if type(t) is _Span else int(t.shape[0])
 
 
+def _needed_count(t) -> int:
+    """Entries of a list that a call cannot do without: None, what a plan made without the list carries, raises here.  (Taken
+    for an empty batch it would be a step that trains nothing, or pools zeros, without an error.)"""
+    return t.n if type(t) is _Span else int(t.numel())
+
+
+def _needed_rows(t) -> int:
+    return t.n if type(t) is _Span else int(t.shape[0])
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
@@ -534,7 +544,7 @@ def bp_pipeline_end(handle: int, stream=None) -> None:
 # ---------------------------------------------------------------------------------------------------
 def bp_embbag_fwd(cfg: bp_config, cache_w, lookup_slots, bag_offsets, bags: int, out, stream=None) -> None:
     """bag_offsets None = one lookup per bag.  out: fp32 device tensor [bags, dim], written in place."""
-    n = _count(lookup_slots)
+    n = _needed_count(lookup_slots)
     _check(load_library().bp_embbag_fwd(ctypes.byref(cfg), _ptr(cache_w), _ptr(lookup_slots), _ptr(bag_offsets), n,
                                         int(bags), _ptr(out), _stream(stream)))
 
@@ -543,10 +553,10 @@ def bp_embbag_fwd_grouped(cfg: bp_config, cache_w, grouped_lookups, row_recs, pi
                           stream=None) -> None:
     """One lookup per bag.  grouped_lookups / row_recs / piece_recs: one batch's slices of the plan's grouping arrays
     (piece_recs may be None or empty).  out: fp32 device tensor [bags, dim], written in place."""
-    assert _count(grouped_lookups) == int(bags)
+    assert _needed_count(grouped_lookups) == int(bags)
     n_pieces = _rows(piece_recs)
     _check(load_library().bp_embbag_fwd_grouped(ctypes.byref(cfg), _ptr(cache_w), _ptr(grouped_lookups), _ptr(row_recs),
-                                                _rows(row_recs), _ptr(piece_recs) if n_pieces else None, n_pieces,
+                                                _needed_rows(row_recs), _ptr(piece_recs) if n_pieces else None, n_pieces,
                                                 int(bags), _ptr(out), _stream(stream)))
 
 
@@ -563,7 +573,7 @@ def bp_embbag_bwd_update_workspace_bytes(cfg: bp_config, n_lookups: int, bags: i
 def bp_embbag_bwd_update(cfg: bp_config, cache_w, cache_state, lookup_slots, bag_offsets, bags: int, grad_out,
                          workspace, tickets, stream=None) -> None:
     """tickets: see bwd_tickets()."""
-    n = _count(lookup_slots)
+    n = _needed_count(lookup_slots)
     assert tickets.numel() * tickets.itemsize >= _ticket_bytes(n)
     _check(load_library().bp_embbag_bwd_update(ctypes.byref(cfg), _ptr(cache_w), _ptr(cache_state),
                                                _ptr(lookup_slots), _ptr(bag_offsets), n, int(bags), _ptr(grad_out),
@@ -597,12 +607,12 @@ def bp_embbag_bwd_update_grouped(cfg: bp_config, cache_w, cache_state, grouped_l
                                  bag_offsets, bags: int, grad_out, workspace, tickets, stream=None) -> None:
     """grouped_lookups / row_recs / piece_recs: one batch's slices of the plan's grouping arrays (piece_recs may be
     None or empty).  tickets: see bwd_tickets()."""
-    n = _count(grouped_lookups)
+    n = _needed_count(grouped_lookups)
     n_pieces = _rows(piece_recs)
     assert tickets.numel() * tickets.itemsize >= _ticket_bytes(n)
     _check(load_library().bp_embbag_bwd_update_grouped(
         ctypes.byref(cfg), _ptr(cache_w), _ptr(cache_state), _ptr(grouped_lookups), _ptr(row_recs),
-        _rows(row_recs), _ptr(piece_recs) if n_pieces else None, n_pieces,
+        _needed_rows(row_recs), _ptr(piece_recs) if n_pieces else None, n_pieces,
         _ptr(bag_offsets), n, int(bags), _ptr(grad_out), _ptr(workspace), int(workspace.numel()), _ptr(tickets),
         _stream(stream)))
 
@@ -621,11 +631,11 @@ def bp_embbag_bwd_update_grouped_static_bytes(cfg: bp_config, n_lookups: int, ba
 def bp_embbag_bwd_update_grouped_static(cfg: bp_config, cache_w, cache_state, grouped_lookups, row_recs, piece_recs,
                                         bag_offsets, bags: int, grad_out, stream=None) -> None:
     """bp_embbag_bwd_update_grouped without workspace and tickets: the library's own fixed scratch array serves."""
-    n = _count(grouped_lookups)
+    n = _needed_count(grouped_lookups)
     n_pieces = _rows(piece_recs)
     _check(load_library().bp_embbag_bwd_update_grouped_static(
         ctypes.byref(cfg), _ptr(cache_w), _ptr(cache_state), _ptr(grouped_lookups), _ptr(row_recs),
-        _rows(row_recs), _ptr(piece_recs) if n_pieces else None, n_pieces,
+        _needed_rows(row_recs), _ptr(piece_recs) if n_pieces else None, n_pieces,
         _ptr(bag_offsets), n, int(bags), _ptr(grad_out), _stream(stream)))
 
 

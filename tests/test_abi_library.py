@@ -123,6 +123,28 @@ def test_spans_are_slices():
     assert binding._count(None) == binding._rows(None) == 0
 
 
+def test_lists_a_call_cannot_do_without(lib):
+    """A plan made without the slot map or the grouping carries None for these lists: no call takes that for an empty batch."""
+    import torch
+    import paper_2202_12429_amd as bp
+    cfg = bp.make_config(1000, 64, 16)
+    w, ws, tickets = torch.zeros((64, 16)), torch.zeros(1 << 16, dtype=torch.uint8), torch.zeros(64, dtype=torch.int32)
+    grad, off, none = torch.zeros((4, 16)), torch.zeros(5, dtype=torch.int64), torch.zeros(0, dtype=torch.int32)
+    for b in (None, off):
+        with pytest.raises(AttributeError):
+            bp.bp_embbag_fwd(cfg, w, None, b, 4, torch.zeros((4, 16)), stream=0)
+        with pytest.raises(AttributeError):
+            bp.bp_embbag_bwd_update(cfg, w, None, None, b, 4, grad, ws, tickets, stream=0)
+        for lookups, rows in ((None, none.view(0, 4)), (none, None), (None, None)):
+            with pytest.raises(AttributeError):
+                bp.bp_embbag_bwd_update_grouped(cfg, w, None, lookups, rows, None, b, 4, grad, ws, tickets, stream=0)
+            with pytest.raises(AttributeError):
+                bp.bp_embbag_bwd_update_grouped_static(cfg, w, None, lookups, rows, None, b, 4, grad, stream=0)
+    for lookups, rows in ((None, none.view(0, 4)), (none, None), (None, None)):
+        with pytest.raises(AttributeError):
+            bp.bp_embbag_fwd_grouped(cfg, w, lookups, rows, None, 0, torch.zeros((0, 16)), stream=0)
+
+
 def test_ticket_bytes_are_the_librarys(lib):
     from paper_2202_12429_amd import binding
     for n in (0, 1, 255, 256, 257, 1 << 20, (1 << 31) - 1):
