@@ -6,6 +6,8 @@
 //    lanes, several pieces per lane in flight; a wavefront's stores are one contiguous kilobyte.
 // bp_embbag_fwd_grouped: the same row copies walked by the plan's row and piece records instead of a slot per
 // lookup: every distinct row is fetched once and written to the bags that look it up.
+#include <algorithm>
+
 #include "bwd_records.h"
 #include "common.h"
 #include "row_access.h"
@@ -221,23 +223,33 @@ struct FwdLaunch {
     int64_t bags, n_lookups;
     float* out;
     hipStream_t stream;
+    // HIP takes fewer than 2^32 threads a launch, which 67 M bags of 64 lanes reach: more go in several launches.
     template <int GW, typename P>
     int run(int lpr) {
+        const int64_t most = (int64_t(1) << 31) / GW;
+        for (int64_t b0 = 0; b0 < bags; b0 += most) BP_TRY((run_bags<GW, P>(lpr, b0, std::min(most, bags - b0))));
+        return BP_OK;
+    }
+    template <int GW, typename P>
+    int run_bags(int lpr, int64_t b0, int64_t count) {
+        const auto* w = (const typename P::Raw*)cache_w;
+        const int64_t wst = cache_w_stride16(cfg) * P::kPerVec;
+        float* const to = out + b0 * cfg->dim;
         if (bag_off == nullptr) {
             const uint32_t inv = lpr == 1 ? 0u : (uint32_t)((uint64_t(1) << 32) / (uint32_t)lpr + 1);
-            const dim3 flat((unsigned)ceil_div(bags * lpr, (int64_t)kRowBlock * kFlatPieces));
-            BP_LAUNCH(K_FWD, (embbag_fwd_onehot_kernel<P, kFlatPieces>), flat, dim3(kRowBlock), 0, stream,
-                      (const typename P::Raw*)cache_w, slots, bags, cfg->capacity, (uint32_t)lpr, inv, cache_w_stride16(cfg) * P::kPerVec, cfg->dim, out);
+            const dim3 flat((unsigned)ceil_div(count * lpr, (int64_t)kRowBlock * kFlatPieces));
+            BP_LAUNCH(K_FWD, (embbag_fwd_onehot_kernel<P, kFlatPieces>), flat, dim3(kRowBlock), 0, stream, w, slots + b0, count,
+                      cfg->capacity, (uint32_t)lpr, inv, wst, cfg->dim, to);
             return BP_OK;
         }
-        const dim3 grid((unsigned)ceil_div(bags * GW, kRowBlock));
+        const dim3 grid((unsigned)ceil_div(count * GW, kRowBlock));
         const bool long_bags = 2 * n_lookups >= 13 * bags;
         if (long_bags)
-            BP_LAUNCH(K_FWD, (embbag_fwd_kernel<GW, P, 8>), grid, dim3(kRowBlock), 0, stream, (const typename P::Raw*)cache_w, slots,
-                      bag_off, bags, n_lookups, cfg->capacity, lpr, cache_w_stride16(cfg) * P::kPerVec, cfg->dim, out);
+            BP_LAUNCH(K_FWD, (embbag_fwd_kernel<GW, P, 8>), grid, dim3(kRowBlock), 0, stream, w, slots, bag_off + b0, count, n_lookups,
+                      cfg->capacity, lpr, wst, cfg->dim, to);
         else
-            BP_LAUNCH(K_FWD, (embbag_fwd_kernel<GW, P, 4>), grid, dim3(kRowBlock), 0, stream, (const typename P::Raw*)cache_w, slots,
-                      bag_off, bags, n_lookups, cfg->capacity, lpr, cache_w_stride16(cfg) * P::kPerVec, cfg->dim, out);
+            BP_LAUNCH(K_FWD, (embbag_fwd_kernel<GW, P, 4>), grid, dim3(kRowBlock), 0, stream, w, slots, bag_off + b0, count, n_lookups,
+                      cfg->capacity, lpr, wst, cfg->dim, to);
         return BP_OK;
     }
 };

@@ -129,6 +129,22 @@ def test_forward_bags_in_every_form(bp, D, dtype, bags, longest):
     assert np.array_equal(out.cpu().numpy(), want)
 
 
+def test_forward_more_lanes_than_a_launch_takes(bp):
+    """Bags enough that 64 lanes each are more than the 2^32 threads of one launch (68 GB of pooled rows of dim 256): row
+    copies, compared with torch's on the GPU stretch by stretch, the same bits."""
+    C, D, bags = 1000, 256, (1 << 26) + 5
+    say(f"forward D={D} bf16, {bags} bags of one lookup with offsets")
+    w = random_cache(C, D, "bf16", 5).cuda()
+    slots = torch.randint(0, C, (bags,), dtype=torch.int32, device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+    out = torch.empty((bags, D), device="cuda")
+    bp.bp_embbag_fwd(bp.make_config(C, C, D, "bf16"), w, slots, torch.arange(bags + 1, device="cuda"), bags, out)
+    rows = w.float()
+    for a in range(0, bags, 1 << 22):
+        assert torch.equal(out[a:a + (1 << 22)], rows[slots[a:a + (1 << 22)].long()]), a
+    del out
+    torch.cuda.empty_cache()
+
+
 def test_forward_edge_cases(bp):
     say("forward edge cases")
     C, D = 64, 16
