@@ -587,7 +587,7 @@ constexpr int kFlagsPerThread = 4;
 constexpr int kFlagsTile = kBlock * kFlagsPerThread;
 __global__ __launch_bounds__(kBlock) void plan_flags_kernel(const uint64_t* __restrict__ ukey, uint32_t M, int ib,
                                                             const PlanScalars* sc, int chunk, uint64_t* __restrict__ rec,
-                                                            uint64_t* __restrict__ miss_mask) {
+                                                            uint64_t* __restrict__ miss_mask, uint8_t* __restrict__ any_miss) {
     __shared__ uint64_t win[kFlagsTile + 1 + kFlagsWindow];
     const uint64_t imask = (uint64_t(1) << ib) - 1;
     const int64_t Leff = sc->L_eff;
@@ -649,15 +649,21 @@ __global__ __launch_bounds__(kBlock) void plan_flags_kernel(const uint64_t* __re
         }
         rec[q] = PairRecord{ib}.pack(g, t, (miss ? kMiss : 0) | (keep ? 0 : kEvict), (uint32_t)i);
         const uint64_t m = __ballot(miss);
-        if (lane_id() == 0) miss_mask[q / kWave] = m;
+        if (lane_id() == 0) {
+            miss_mask[q / kWave] = m;
+            any_miss[q / kWave] = m != 0;
+        }
     }
 }
 
 // The pair that fetched a pair's row: the last miss at or before it in (id, batch) order.  Kept as bit masks like the pairs'
 // starts.  An id's first pair is a miss, so the words without one that a pair looks back over are its own id's: none as a
-// rule, and never more than a 64th of the batches.
+// rule, but a row that stays cached through a long trace has as many as a 64th of the batches.  A byte a word says whether it
+// holds a miss, so such a pair goes back over 512 pairs a step (64 M lookups in 8,000 batches, the hottest rows in nearly all
+// of them: word by word 5,179 us a plan, by eights 4,289).
 struct FetchingPair {
     const uint64_t* miss_mask;
+    const uint8_t* any_miss;       // of every word; aligned to 8
     struct Words {                 // the pair's word and the one before, which nearly always hold the miss
         uint64_t own, before;
     };
@@ -668,7 +674,14 @@ struct FetchingPair {
             m = w.before;
             --word;
         }
-        while (m == 0 && word > 0) m = miss_mask[--word];
+        if (m == 0 && word > 0) {
+            const uint64_t* eights = reinterpret_cast<const uint64_t*>(any_miss);
+            int64_t e = (word - 1) / 8;
+            uint64_t any = eights[e] & (~uint64_t(0) >> (56 - 8 * ((word - 1) % 8)));      // the words below `word`
+            while (any == 0 && e > 0) any = eights[--e];
+            word = 8 * e + (any ? (63 - __clzll((long long)any)) / 8 : 0);
+            m = miss_mask[word];
+        }
         return (uint32_t)(word * kWave) + (kWave - 1) - (uint32_t)__clzll((long long)m);
     }
     __device__ __forceinline__ uint32_t of(uint32_t q) const { return in_word(q / kWave, (int)(q % kWave), load(q / kWave)); }
@@ -1165,6 +1178,7 @@ struct PlanWorkspace {
     int64_t *occ, *offsets, *prefetch_off, *evict_off, *iter_off;
     uint64_t *rec_a, *rec_b;
     uint64_t* miss_mask;     // misses among the pairs, 64 a word
+    uint8_t* any_miss;       // of every such word: it holds one
     uint32_t *val2_a, *val2_b, *missord, *evict_pair, *par, *pair_start;
     int64_t* cuts;           // trainer cuts of every batch, [T][kMaxTrainers + 1] at most
     int32_t* slot_of_pair;
@@ -1183,9 +1197,10 @@ PlanWorkspace carve_plan(void* base, size_t cap, int64_t N, int T, int Lcap, boo
     w.keys_a = c.take<uint64_t>(n);
     w.keys_b = c.take<uint64_t>(n);
     const size_t words = (n + 63) / 64;            // the masks and their counts, in one piece: no more than a few lookups need
-    w.head_mask = c.take<uint64_t>(2 * words + (words + 1) / 2);
+    w.head_mask = c.take<uint64_t>(2 * words + (words + 7) / 8 + (words + 1) / 2);
     w.miss_mask = w.head_mask + words;
-    w.pairs_before = reinterpret_cast<uint32_t*>(w.head_mask + 2 * words);
+    w.any_miss = reinterpret_cast<uint8_t*>(w.head_mask + 2 * words);
+    w.pairs_before = reinterpret_cast<uint32_t*>(w.head_mask + 2 * words + (words + 7) / 8);
     w.tile_batch = c.take<int32_t>((n >> kPosTileShift) + 2);
     // a workspace that is large enough for N lookups is so for fewer, which may have more tiles
     const int64_t in_small_tiles = std::min(N, kPlanSmallSort);
@@ -1454,8 +1469,8 @@ int plan_impl(const bp_config* cfg, const int64_t* ids, const int64_t* iter_offs
     // ---- 4. flags, TTL, fetching pair of every pair
     BP_LAUNCH(K_PLAN_FLAGS, plan_flags_kernel, dim3((unsigned)(M > 0 ? ceil_div((int64_t)M, kFlagsTile) : 1)), dim3(kBlock), 0,
               stream, (const uint64_t*)ukey, M, ib,
-              (const PlanScalars*)w.scalars, (int)chunk, w.rec_a, w.miss_mask);
-    const FetchingPair fetched_by{w.miss_mask};
+              (const PlanScalars*)w.scalars, (int)chunk, w.rec_a, w.miss_mask, w.any_miss);
+    const FetchingPair fetched_by{w.miss_mask, w.any_miss};
 
     // ---- 5. regroup by batch (the records travel as keys), lists
     // What travels with a record: the number of the pair that fetched its row (for a miss that is the pair itself,

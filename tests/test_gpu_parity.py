@@ -877,6 +877,27 @@ def test_plan_degenerate_traces(bp):
     plan_both(bp, np.array([4], dtype=np.int64), np.array([0, 0, 1, 1], dtype=np.int64), 9, 2, 1)
 
 
+@pytest.mark.parametrize("T", [520, 4100, 8000])
+def test_plan_rows_that_stay_for_many_words(bp, T):
+    """Rows that are fetched once and stay to the trace's end, or leave and come back after a few hundred batches: their pairs lie
+    many mask words, and many groups of eight such words, behind the miss that fetched them; with the trainer marking, and cut
+    into two chunks."""
+    say(f"plan of {T} batches with rows that stay")
+    rng = np.random.default_rng(T)
+    hot, R, L = 9, 400, 16
+    batches = []
+    for i in range(T):
+        stay = [h for h in range(hot) if h < 5 or (i // 550) % 2 == 0 or (i + h) % 97 > 40]
+        batches.append(np.array(stay + list(rng.integers(hot, R, size=rng.integers(0, 4))), np.int64))
+    off = np.concatenate([[0], np.cumsum([len(b) for b in batches])]).astype(np.int64)
+    ids = np.concatenate(batches)
+    plan_both(bp, ids, off, R, L, 200)
+    cuts = np.stack([np.zeros(T, np.int64), np.diff(off) // 2, np.diff(off)], axis=1)
+    marked = bp.bp_oracle_plan(bp.make_config(R, 200, 16, lookahead=L), dev(ids), off, trainer_cuts=cuts)
+    assert_plan_equal(marked, oracle.plan(ids, off, R, L, 200), len(ids))
+    run_chunked(bp, ids, off, R, L, 200, T // 2 + 1)
+
+
 def test_plan_many_batches_wide_group_keys(bp):
     """4,100 short batches (13 batch bits) with a capacity of 2^20 (wide slot and batch fields in the lookups' words),
     then with 9 slots: every slot changes hands hundreds of times, so the chains of the free ring are far longer than
