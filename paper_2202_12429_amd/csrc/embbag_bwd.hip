@@ -14,7 +14,8 @@
 //                  at once.  For a row of several pieces the piece's sum is stored, and whoever finds, by a counter,
 //                  that all the others have stored theirs adds the sums and updates the row.
 // ONE launch does all of it: workgroups [0, piece_blocks) take pieces, the rest take rows.
-// Every order of addition is fixed by the records, never by timing: results are bit-identical run to run.
+// Every order of addition is fixed by the row's own records and its type and width, never by timing or by the rest of the batch:
+// results are bit-identical run to run, and from one entry point to the other.
 // The summed gradient is rounded to fp32 once; the optimizer step itself is fp32 arithmetic.
 #include <algorithm>
 #include <type_traits>
@@ -337,9 +338,21 @@ __device__ __forceinline__ void finish_update(const UpdateParams& u, typename P:
         }
         if (active) s.store_f32(cache_s + slot * u.sst, c, u.lpr);
     } else {
-        double ss = 0.0;                       // mean of squares over the row: an fp64 sum, rounded once
+        // mean of squares over the row: an fp64 sum, rounded once.  bf16 rows: in fours of elements, the i-th of the row's
+        // first half with the i-th of its second, and then over the lanes; a lane by eights holds both, by fours one of them.
+        double ss = 0.0;
 #pragma unroll
-        for (int i = 0; i < N; ++i) ss += (double)g.v[i] * (double)g.v[i];
+        for (int i = 0; i < 4; ++i) ss += (double)g.v[i] * (double)g.v[i];
+        if constexpr (N == 8) {
+            double second = 0.0;
+#pragma unroll
+            for (int i = 4; i < N; ++i) second += (double)g.v[i] * (double)g.v[i];
+            ss += second;
+        } else if constexpr (P::BF16) {
+            const int half = u.lpr / 2;
+            const double second = __shfl(ss, c + half, GW);
+            ss = c < half ? ss + second : 0.0;
+        }
         ss = group_sum<GW>(ss);
         const float mean = (float)(ss / (double)u.dim);
         const float s = r.s_row + mean;
@@ -355,18 +368,21 @@ __device__ __forceinline__ void finish_update(const UpdateParams& u, typename P:
 }
 
 // Adds the gradient rows of the grouped lookups [p0, p1) into acc: bursts of four rows, the indices of the next
-// burst loaded while the rows of this one arrive.  idx holds the bag numbers of the first four lookups.
+// burst loaded while the rows of this one arrive.  idx holds the bag numbers of the first four lookups, and afterwards those
+// of the first four of [q0, q1) unless [p0, p1) is empty.
 template <typename P, int N>
-__device__ __forceinline__ void add_gradient_rows(SumPiece<N>& acc, uint32_t (&idx)[4], uint32_t p0, uint32_t p1,
-                                                  const uint32_t* __restrict__ bag_of, const float* __restrict__ grad,
-                                                  const UpdateParams& u, int c) {
+__device__ __forceinline__ void add_gradient_rows(SumPiece<N>& acc, uint32_t (&idx)[4], uint32_t p0, uint32_t p1, uint32_t q0,
+                                                  uint32_t q1, const uint32_t* __restrict__ bag_of,
+                                                  const float* __restrict__ grad, const UpdateParams& u, int c) {
     for (uint32_t p = p0; p < p1; p += 4) {
         P t[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)     // the bag number is clamped where it is used: its load stays in flight until then
             if (p + j < p1) t[j].load_f32(grad + (size_t)min(idx[j], u.bags - 1u) * u.dim, c, u.lpr);
+        const bool more = p + 4 < p1;
+        const uint32_t next = more ? p + 4 : q0, end = more ? p1 : q1;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) idx[j] = p + 4 + j < p1 ? bag_of[p + 4 + j] : 0u;
+        for (int j = 0; j < 4; ++j) idx[j] = next + j < end ? bag_of[next + j] : 0u;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             if (p + j < p1) acc.add(t[j]);
@@ -386,29 +402,81 @@ constexpr int kBwdWideBlock = GW <= 16 ? 256 : 16 * GW;
 template <int GW, int BLOCK>
 constexpr int kPieceThreads = kWavePieces<GW> ? kWave : BLOCK;
 
-// Sum over the lane groups that took a piece, in an order of its own that nothing but GW decides.  The whole sum is in the
-// first group.  By workgroup: every group leaves its sum in LDS, group 0 adds them up in group order; two barriers, and
-// `red` may be reused after the call.  By wavefront: in pairs, then pairs of pairs.
-template <int GW, int BLOCK, int N>
-__device__ __forceinline__ void piece_sum(SumPiece<N>& acc, double (*red)[N][GW], int j, int c) {
-    if constexpr (kWavePieces<GW>) {
+// The order of a piece's sum, the same in every form of the kernel for a type and a width: kShares shares, as many as the
+// form with the most lane groups has, of lookups one behind the other, are each summed in lookup order; share i then meets
+// share i + kShares/2, these sums meet in the same way, and so on.  A form with fewer lane groups gives group j the shares j,
+// j + groups, ..., which meet there.  (The pieces' sums of a row of several are shared out one by one and meet
+// alike.)  So neither the entry point nor what else is in the batch changes a row's result.
+constexpr int piece_groups(int gw) { return gw <= 4 ? kWave / gw : gw <= 16 ? 256 / gw : 16; }      // of the form with the most
+template <int GW, typename P>
+constexpr int kShares = !P::BF16   ? piece_groups(GW)
+                        : P::N == 8 ? std::max(piece_groups(GW), piece_groups(2 * GW))
+                                    : std::max(piece_groups(GW), piece_groups(GW > 1 ? GW / 2 : 1));
+// Places of a thread in LDS, N doubles each, for the sums below.
+template <int S, int PG, bool WAVE>
+constexpr int kHeldSums = S == 4 * PG ? 2 : S == 2 * PG || !WAVE ? 1 : 0;
+// The sum of the shares of lane group j, in their order: one(acc, share, next) adds up one of them and is told which one
+// follows (S: none).
+// Sums that wait for others do so in the thread's places in LDS: the kernel has no registers for them.
+template <int S, int PG, int N, int R, typename One>
+__device__ __forceinline__ SumPiece<N> sum_shares(uint32_t j, double (*held)[R], One&& one) {
+    constexpr int M = S / PG;
+    static_assert(S % PG == 0 && (M == 1 || M == 2 || M == 4), "every group has as many, which meet in pairs");
+    const auto put = [&](const SumPiece<N>& acc, int place) {
 #pragma unroll
-        for (int off = GW; off < kWave; off <<= 1)
+        for (int i = 0; i < N; ++i) held[place * N + i][threadIdx.x] = acc.v[i];
+    };
+    const auto meet = [&](SumPiece<N>& acc, int place) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) acc.v[i] += __shfl_xor(acc.v[i], off, kWave);
-    } else {
+        for (int i = 0; i < N; ++i) acc.v[i] += held[place * N + i][threadIdx.x];
+    };
+    SumPiece<N> acc;
+#pragma unroll 1
+    for (int t = 0; t < M; ++t) {
+        acc.zero();
+        one(acc, j + t * PG, t + 1 < M ? j + (t + 1) * PG : (uint32_t)S);
+        if constexpr (M > 1) {
+            if (t >= M / 2) meet(acc, t - M / 2);              // two: 0 and 1; four: 0 and 2, 1 and 3
+            if (t + 1 < M) put(acc, M == 4 ? t % 2 : 0);
+        }
+    }
+    if constexpr (M == 4) meet(acc, 0);
+    return acc;
+}
+// Sum over the lane groups that took a piece.  The whole sum is in the first group.  By workgroup: the upper half of the
+// wavefronts leaves its sums in LDS, in the threads' own places, for the lower half; the last four meet in one step, and the first
+// goes on by lane shuffles.  The places may be used again after the call.
+template <int GW, int BLOCK, int N, int R>
+__device__ __forceinline__ void piece_sum(SumPiece<N>& acc, double (*held)[R]) {
+    if constexpr (!kWavePieces<GW>) {
+        const uint32_t tid = threadIdx.x;
+        const auto leave = [&](uint32_t from, uint32_t to) {
+            if (tid >= from && tid < to) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) red[j][i][c] = acc.v[i];
-        __syncthreads();
-        if (j == 0) {
-            acc.zero();
-            for (int g = 0; g < BLOCK / GW; ++g) {
-#pragma unroll
-                for (int i = 0; i < N; ++i) acc.v[i] += red[g][i][c];
+                for (int i = 0; i < N; ++i) held[i][tid] = acc.v[i];
             }
+            __syncthreads();
+        };
+#pragma unroll
+        for (uint32_t half = BLOCK / 2; half > 2 * kWave; half /= 2) {
+            leave(half, 2 * half);
+            if (tid < half) {
+#pragma unroll
+                for (int i = 0; i < N; ++i) acc.v[i] += held[i][tid + half];
+            }
+        }
+        leave(kWave, 4 * kWave);
+        if (tid < kWave) {
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                acc.v[i] = (acc.v[i] + held[i][tid + 2 * kWave]) + (held[i][tid + kWave] + held[i][tid + 3 * kWave]);
         }
         __syncthreads();
     }
+#pragma unroll
+    for (int off = kWave / 2; off >= GW; off >>= 1)
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc.v[i] += __shfl_xor(acc.v[i], off, kWave);
 }
 
 // counts: the numbers of row and piece records when they were made on the device (bp_embbag_bwd_update), else NULL
@@ -463,7 +531,7 @@ __global__ __launch_bounds__(BLOCK, P::N == 8 ? 4 : 8) void bwd_rows_kernel(cons
                 const uint32_t start = rec[r].x & kPosMask, count = rec[r].y;
                 SumPiece<N> acc;
                 acc.zero();
-                if (active) add_gradient_rows<P, N>(acc, idx[r], start, start + count, bag_of, grad, u, c);
+                if (active) add_gradient_rows<P, N>(acc, idx[r], start, start + count, 0, 0, bag_of, grad, u, c);
                 finish_update<GW, P>(u, cache_w, cache_s, (int64_t)rec[r].z, c, row[r], acc.template rounded<P>(), active);
             }
         }
@@ -474,8 +542,9 @@ __global__ __launch_bounds__(BLOCK, P::N == 8 ? 4 : 8) void bwd_rows_kernel(cons
     constexpr bool WAVE = kWavePieces<GW>;
     constexpr int PG = kPieceThreads<GW, BLOCK> / GW;           // lane groups that share a piece
     constexpr int PER_BLOCK = BLOCK / kPieceThreads<GW, BLOCK>;
-    __shared__ double red[WAVE ? 1 : G][N][GW];
-    __shared__ uint32_t s_last;
+    constexpr int S = kShares<GW, P>;
+    constexpr int HELD = kHeldSums<S, PG, WAVE>;
+    __shared__ double held[HELD ? HELD * N : 1][HELD ? BLOCK : 1];
     const int pj = WAVE ? j % PG : j;
     const uint32_t n_pieces = n_pieces_ptr ? *n_pieces_ptr : n_pieces_host;
     const bool writer = active && pj == 0;
@@ -486,16 +555,16 @@ __global__ __launch_bounds__(BLOCK, P::N == 8 ? 4 : 8) void bwd_rows_kernel(cons
         if ((int64_t)slot >= C || count == 0 || start >= n || count > n - start || pieces == 0 || index >= pieces) continue;
         const bool direct = pieces == 1;
         if (!direct && (pbase >= partial_rows || pieces > partial_rows - pbase)) continue;
-        // lane group pj takes the pj-th stretch of the piece
-        const uint32_t per = (count + PG - 1) / PG;
-        const uint32_t p0 = start + min((uint32_t)pj * per, count), p1 = start + min((uint32_t)(pj + 1) * per, count);
+        const uint32_t per = (count + 4 * S - 1) / (4 * S) * 4;      // lookups of a share: whole bursts
+        const auto share_at = [&](uint32_t share) { return start + min(share * per, count); };
         uint32_t idx[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) idx[k] = p0 + k < p1 ? bag_of[p0 + k] : 0u;
-        SumPiece<N> acc;
-        acc.zero();
-        if (active) add_gradient_rows<P, N>(acc, idx, p0, p1, bag_of, grad, u, c);
-        piece_sum<GW, BLOCK, N>(acc, red, pj, c);
+        for (int k = 0; k < 4; ++k) idx[k] = share_at(pj) + k < share_at(pj + 1) ? bag_of[share_at(pj) + k] : 0u;
+        SumPiece<N> acc = sum_shares<S, PG, N>((uint32_t)pj, held, [&](SumPiece<N>& sum, uint32_t share, uint32_t next) {
+            if (active)
+                add_gradient_rows<P, N>(sum, idx, share_at(share), share_at(share + 1), share_at(next), share_at(next + 1), bag_of, grad, u, c);
+        });
+        piece_sum<GW, BLOCK, N>(acc, held);
         if (direct) {      // the row is asked for only now: one more round trip after a few hundred gradient rows
             if (pj == 0) {
                 const RowPiece<P> row = load_row<P>(u, cache_w, cache_s, (int64_t)slot, c, writer);
@@ -519,25 +588,26 @@ __global__ __launch_bounds__(BLOCK, P::N == 8 ? 4 : 8) void bwd_rows_kernel(cons
             last = __builtin_amdgcn_readfirstlane(drawn) + 1u == pieces;
         } else {
             __syncthreads();
-            if (threadIdx.x == 0)
-                s_last = __hip_atomic_fetch_add(&tickets[pbase], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == pieces ? 1u : 0u;
+            if (threadIdx.x == 0)                      // told through its own place in LDS
+                held[0][0] = __hip_atomic_fetch_add(&tickets[pbase], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == pieces ? 1.0 : 0.0;
             __syncthreads();
-            last = s_last != 0u;
-            __syncthreads();                           // everybody has read s_last before a later piece rewrites it
+            last = held[0][0] != 0.0;
+            __syncthreads();                           // everybody has read it before a later sum rewrites it
         }
         if (!last) continue;
-        acc.zero();
-        for (uint32_t b = (uint32_t)pj; b < pieces; b += 2 * PG) {      // lane groups take the pieces round-robin
-            SumPiece<N> t[2];
+        acc = sum_shares<S, PG, N>((uint32_t)pj, held, [&](SumPiece<N>& sum, uint32_t share, uint32_t) {
+            for (uint32_t b = share; b < pieces; b += 2 * S) {
+                SumPiece<N> t[2];
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                t[k].zero();
-                if (active && b + (uint32_t)k * PG < pieces) t[k].load_device(partial + (size_t)(pbase + b + k * PG) * u.dim, c);
+                for (int k = 0; k < 2; ++k) {
+                    t[k].zero();
+                    if (active && b + (uint32_t)k * S < pieces) t[k].load_device(partial + (size_t)(pbase + b + k * S) * u.dim, c);
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k) sum.add(t[k]);
             }
-#pragma unroll
-            for (int k = 0; k < 2; ++k) acc.add(t[k]);
-        }
-        piece_sum<GW, BLOCK, N>(acc, red, pj, c);
+        });
+        piece_sum<GW, BLOCK, N>(acc, held);
         if (pj == 0) {
             const RowPiece<P> row = load_row<P>(u, cache_w, cache_s, (int64_t)slot, c, writer);
             finish_update<GW, P>(u, cache_w, cache_s, (int64_t)slot, c, row, acc.template rounded<P>(), writer);
@@ -698,8 +768,9 @@ BwdWorkspace carve_bwd(void* base, size_t cap, int64_t n, int dim) {
     return w;
 }
 
-// Two choices that change no result, us of the kernel on tables of hundreds of MB, ids uniform / skewed (of
-// 200,000 lookups 181,000 / 86,000 rows distinct):
+// Two choices that change no bit of the result (kShares above), us of the kernel on tables of hundreds of MB, ids uniform / skewed
+// (of 200,000 lookups 181,000 / 86,000 rows distinct).  bp_embbag_bwd_update knows no counts when it launches, only bounds, and so
+// takes the forms for batches with long rows and as many rows as lookups:
 //   bf16 rows by fours or by eights a lane (dispatch_values).  By fours pieces are quicker in a launch that the chip holds at once
 //     (20,000 lookups, dim 64: 8.5 by fours, 11.5 by eights; without pieces 5.6, 5.2); a larger one has the more bytes in flight
 //     by eights (200,000, dim 128: 48.2 / 33.2 by fours, 42.9 / 33.5 by eights; 1.3 M: 276 / 206, 258 / 204).

@@ -452,6 +452,68 @@ def test_backward_in_every_form(bp, D, dtype, optimizer, rows, hot):
         np.testing.assert_allclose(got_s, want_s, rtol=1e-4, atol=1e-9)
 
 
+@pytest.mark.parametrize("D,dtype", [(8, "bf16"), (16, "bf16"), (24, "bf16"), (32, "bf16"), (64, "bf16"), (96, "bf16"), (128, "bf16"),
+                                     (192, "bf16"), (256, "bf16"), (512, "bf16"), (16, "f32"), (100, "f32"), (128, "f32"), (256, "f32")])
+def test_backward_bits_do_not_depend_on_the_batch(bp, D, dtype):
+    """A row's new weights and state are the same bits whatever else the batch holds and whichever entry point takes it: the same
+    rows alone, beside short rows, and in a batch of more than four chips of lanes, i.e. by fours and by eights a lane, in wide
+    workgroups and in ones of 256 threads.  Their gradients are large values that cancel and small ones, which an order of
+    its own would leave in other sums; those of the last rows have squares whose sum lies a few bits above a tie."""
+    say(f"backward bits D={D} {dtype}")
+    rng = np.random.default_rng(D)
+    counts = np.array([17, 18, 31, 64, 65, 100, 128, 200, 255, 256, 257, 300, 700, 4096, 4097, 9000] + [1] * 24)
+    K, hot = len(counts), int(counts.sum())
+    grads = []
+    for c in counts:
+        if c == 1:
+            g = np.zeros((1, D), np.float32)
+            at = rng.permutation(D)
+            g[0, at[0]], g[0, at[1]], g[0, at[2:]] = 1.0, 2.0 ** -12, 2.0 ** -27
+        else:
+            big = (rng.standard_normal((c // 3, D)) * 2.0 ** rng.integers(20, 34, size=(c // 3, 1))).astype(np.float32)
+            g = np.concatenate([big, -big, rng.standard_normal((c - 2 * (c // 3), D)).astype(np.float32)])
+            g = g[rng.permutation(c)]
+        grads.append(g)
+    grads, probes = np.concatenate(grads), np.repeat(np.arange(K), counts)
+    shuffle = rng.permutation(hot)
+    grads, probes = grads[shuffle], probes[shuffle]
+
+    def run_both(keep, fill):
+        """The rows of `keep`, `fill` more rows of one lookup among them."""
+        slots = np.concatenate([probes[keep], K + np.arange(fill)])
+        grad = np.concatenate([grads[keep], rng.standard_normal((fill, D)).astype(np.float32)])
+        n = len(slots)
+        where = np.argsort(np.concatenate([np.sort(rng.permutation(n)[:n - fill]), rng.permutation(n)[:fill]]), kind="stable")
+        slots, grad = slots[where], grad[where]                     # the rows' own lookups stay in their order
+        C = K + fill
+        w, s = torch.ones((C, D), dtype=torch.float32 if dtype == "f32" else torch.bfloat16), np.zeros(C, np.float32)
+        cfg = bp.make_config(C, C, D, dtype, "adagrad_rowwise", lr=0.01, eps=1e-8)
+        off = np.arange(n + 1)
+        got_w, got_s = run_bwd(bp, cfg, w, s, slots.astype(np.int32), off, n, grad, True)
+        ids = np.unique(slots, return_inverse=True)[1].astype(np.int64)              # a plan of one batch gives slots in id order
+        plan = bp.bp_oracle_plan(bp.make_config(C, C, D, dtype, "adagrad_rowwise", 1), dev(ids), np.array([0, n]), grouping=True)
+        used = np.unique(slots)
+        wd, sd = w.cuda()[torch.from_numpy(used).cuda()], torch.zeros(len(used), device="cuda")
+        cfg = bp.make_config(C, len(used), D, dtype, "adagrad_rowwise", lr=0.01, eps=1e-8)
+        ws = torch.empty(bp.bp_embbag_bwd_update_grouped_workspace_bytes(cfg, n, n, False), dtype=torch.uint8, device="cuda")
+        bp.bp_embbag_bwd_update_grouped(cfg, wd, sd, plan.grouped_lookups, plan.row_recs, plan.piece_recs, None, n, dev(grad), ws,
+                                        bp.bwd_tickets(n))
+        mine = np.flatnonzero(used < K)
+        assert np.array_equal(cache_numpy(wd.cpu())[mine], cache_numpy(got_w)[used[mine]]), "entry points differ"
+        assert np.array_equal(sd.cpu().numpy()[mine], got_s[used[mine]]), "entry points differ"
+        return cache_numpy(got_w)[used[mine]], got_s[used[mine]]
+
+    everything = np.ones(hot, bool)
+    short = np.isin(probes, np.flatnonzero(counts == 1))
+    want_w, want_s = run_both(everything, 0)
+    for fill in (500, (4 << 21) // D + 20_000):
+        got_w, got_s = run_both(everything, fill)
+        assert np.array_equal(got_s, want_s), np.flatnonzero(got_s != want_s)
+        assert np.array_equal(got_w, want_w)
+    got_w, got_s = run_both(short, 0)                                # no long row in the batch
+    assert np.array_equal(got_s, want_s[counts == 1]) and np.array_equal(got_w, want_w[counts == 1])
+
+
 @pytest.mark.parametrize("lens", [
     [64] * 9, [63, 65, 1, 127, 128, 129, 64], [1] * 63 + [700], [700] + [1] * 70, [64, 0, 64, 0, 0, 1, 63, 0] * 3, [0] * 200 + [640],
     [40, *[0] * 130, 40, *[1] * 20] * 2, [1, 2, 0, 3] * 50, [5000], [257, 0, 3000, 1, 1, 0, 900, *[0] * 70, 20], [1, 0] * 40 + [4000], [30] * 300],
