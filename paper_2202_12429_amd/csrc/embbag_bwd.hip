@@ -12,7 +12,8 @@
 //   piece records  a row with more lookups is cut into pieces of BP_BWD_PIECE lookups; one workgroup (narrow rows: one
 //                  wavefront) takes a piece, its lane groups add their shares and meet.  A one-piece row is updated
 //                  at once.  For a row of several pieces the piece's sum is stored, and whoever finds, by a counter,
-//                  that all the others have stored theirs adds the sums and updates the row.
+//                  that all the others have stored theirs adds the sums and updates the row (of more than 64 pieces: in
+//                  stretches of 64 first).
 // ONE launch does all of it: workgroups [0, piece_blocks) take pieces, the rest take rows.
 // Every order of addition is fixed by the row's own records and its type and width, never by timing or by the rest of the batch:
 // results are bit-identical run to run, and from one entry point to the other.
@@ -572,48 +573,65 @@ __global__ __launch_bounds__(BLOCK, P::N == 8 ? 4 : 8) void bwd_rows_kernel(cons
             }
             continue;
         }
-        // one of several pieces: leave the sum where whoever takes the row's last piece will find it, then take a ticket
+        // One of several pieces: leave the sum where whoever takes the last piece will find it, then take a ticket
         // (device-coherent stores, complete before this piece is counted; whoever counts the last piece then reads
-        // all the sums with device-coherent loads)
-        // The writers and the lane that draws the ticket are of one wavefront, which waits for its stores here by itself: a
-        // fence for the workgroup leaves them on their way, its barrier too.
-        static_assert(GW <= kWave, "the writers are lanes of the workgroup's, or the piece's, first wavefront");
-        if (writer) acc.store_device(partial + (size_t)(pbase + index) * u.dim, c);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        // all the sums with device-coherent loads).  The pieces of a row of more than kMeet meet in stretches of kMeet first,
+        // and then the stretches: whoever takes the row's last piece would read the sums of thousands one burst behind the other,
+        // most of all a wavefront of four-lane rows, with sixteen lane groups (a row's 4.2 M lookups, dim 16: 392 us in one
+        // step, 63 in two; dim 64 698 / 313; 262,144 lookups, dim 16: 30.0 / 11.8).
+        constexpr uint32_t kMeet = 64;
+        uint32_t mine = index, step = 1, first = index / kMeet * kMeet, members = min(kMeet, pieces - first);
+        uint32_t* ticket = tickets + pbase + first;
         bool last;
-        if constexpr (WAVE) {
-            uint32_t drawn = 0;
-            if (threadIdx.x % kWave == 0) drawn = __hip_atomic_fetch_add(&tickets[pbase], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            last = __builtin_amdgcn_readfirstlane(drawn) + 1u == pieces;
-        } else {
-            __syncthreads();
-            if (threadIdx.x == 0)                      // told through its own place in LDS
-                held[0][0] = __hip_atomic_fetch_add(&tickets[pbase], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == pieces ? 1.0 : 0.0;
-            __syncthreads();
-            last = held[0][0] != 0.0;
-            __syncthreads();                           // everybody has read it before a later sum rewrites it
+#pragma unroll 1
+        for (;;) {
+            // The writers and the lane that draws the ticket are of one wavefront, which waits for its stores here by itself: a
+            // fence for the workgroup leaves them on their way, its barrier too.
+            static_assert(GW <= kWave, "the writers are lanes of the workgroup's, or the piece's, first wavefront");
+            if (writer) acc.store_device(partial + (size_t)(pbase + mine) * u.dim, c);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            if constexpr (WAVE) {
+                uint32_t drawn = 0;
+                if (threadIdx.x % kWave == 0) drawn = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                last = __builtin_amdgcn_readfirstlane(drawn) + 1u == members;
+            } else {
+                __syncthreads();
+                if (threadIdx.x == 0)                      // told through its own place in LDS
+                    held[0][0] = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == members ? 1.0 : 0.0;
+                __syncthreads();
+                last = held[0][0] != 0.0;
+                __syncthreads();                           // everybody has read it before a later sum rewrites it
+            }
+            if (!last) break;
+            acc = sum_shares<S, PG, N>((uint32_t)pj, held, [&](SumPiece<N>& sum, uint32_t share, uint32_t) {
+                for (uint32_t b = share; b < members; b += 2 * S) {
+                    SumPiece<N> t[2];
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        t[k].zero();
+                        if (active && b + (uint32_t)k * S < members)
+                            t[k].load_device(partial + (size_t)(pbase + first + (b + k * S) * step) * u.dim, c);
+                    }
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) sum.add(t[k]);
+                }
+            });
+            piece_sum<GW, BLOCK, N>(acc, held);
+            if (threadIdx.x % kPieceThreads<GW, BLOCK> == 0)      // the counter is zero again for the next call
+                __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (step > 1 || pieces <= kMeet) break;
+            mine = first;                                         // the stretches, each in the place of its first piece
+            step = kMeet;
+            first = 0;
+            members = (pieces + kMeet - 1) / kMeet;
+            ticket = tickets + pbase + 1;                         // counts no stretch
         }
         if (!last) continue;
-        acc = sum_shares<S, PG, N>((uint32_t)pj, held, [&](SumPiece<N>& sum, uint32_t share, uint32_t) {
-            for (uint32_t b = share; b < pieces; b += 2 * S) {
-                SumPiece<N> t[2];
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    t[k].zero();
-                    if (active && b + (uint32_t)k * S < pieces) t[k].load_device(partial + (size_t)(pbase + b + k * S) * u.dim, c);
-                }
-#pragma unroll
-                for (int k = 0; k < 2; ++k) sum.add(t[k]);
-            }
-        });
-        piece_sum<GW, BLOCK, N>(acc, held);
         if (pj == 0) {
             const RowPiece<P> row = load_row<P>(u, cache_w, cache_s, (int64_t)slot, c, writer);
             finish_update<GW, P>(u, cache_w, cache_s, (int64_t)slot, c, row, acc.template rounded<P>(), writer);
         }
-        if (threadIdx.x % kPieceThreads<GW, BLOCK> == 0)      // the counter is zero again for the next call
-            __hip_atomic_store(&tickets[pbase], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 

@@ -452,6 +452,29 @@ def test_backward_in_every_form(bp, D, dtype, optimizer, rows, hot):
         np.testing.assert_allclose(got_s, want_s, rtol=1e-4, atol=1e-9)
 
 
+@pytest.mark.parametrize("D,dtype", [(4, "f32"), (16, "f32"), (32, "f32"), (64, "f32"), (8, "bf16"), (32, "bf16")])
+def test_backward_rows_of_many_pieces(bp, D, dtype):
+    """Rows whose pieces meet in stretches of 64: of one stretch to the last lookup, of one more, of ends of one piece, and
+    of 64 stretches and one lookup; sums of small whole numbers, exact in every order, and all counters left zero."""
+    say(f"backward many pieces D={D} {dtype}")
+    stretch = 64 * 256
+    counts = [stretch - 255, stretch, stretch + 1, 2 * stretch - 1, 2 * stretch, 3 * stretch + 256, 64 * stretch + 1]
+    C = len(counts)
+    rng = np.random.default_rng(D)
+    slots = rng.permutation(np.repeat(np.arange(C), counts)).astype(np.int32)
+    n, bags = len(slots), 4096
+    off = np.concatenate([[0], np.sort(rng.integers(0, n + 1, size=bags - 1)), [n]]).astype(np.int64)
+    grad = rng.integers(-2, 3, size=(bags, D)).astype(np.float32)
+    bag = np.repeat(np.arange(bags), np.diff(off))
+    want = np.stack([-np.bincount(slots, weights=grad[bag, d], minlength=C) for d in range(D)], axis=1)
+    w = torch.zeros((C, D), dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    want = torch.from_numpy(want).float().to(w.dtype).float().numpy()
+    cfg = bp.make_config(1000, C, D, dtype, "sgd", lr=1.0)
+    for run in (run_bwd, run_bwd_grouped):
+        got, _ = run(bp, cfg, w, None, slots, off, bags, grad, False)
+        assert np.array_equal(got.float().numpy(), want), run.__name__
+
+
 @pytest.mark.parametrize("D,dtype", [(8, "bf16"), (16, "bf16"), (24, "bf16"), (32, "bf16"), (64, "bf16"), (96, "bf16"), (128, "bf16"),
                                      (192, "bf16"), (256, "bf16"), (512, "bf16"), (16, "f32"), (100, "f32"), (128, "f32"), (256, "f32")])
 def test_backward_bits_do_not_depend_on_the_batch(bp, D, dtype):
