@@ -130,16 +130,14 @@ struct BagsOf64 {
     uint32_t mask_lo, mask_hi, first, flags;
 };
 static_assert(sizeof(BagsOf64) == 16, "one load");
-constexpr int kWalk = 64;             // offsets a lane looks at beyond its own bag: more starts do not fit a mask
 __device__ __forceinline__ BagsOf64 bags_of_64(const int64_t* __restrict__ bag_off, int64_t bags, int64_t b, int64_t from, int64_t end) {
     // `from`: the stretch's first lookup; bag b holds it and ends at `end`
     BagsOf64 r{0u, 0u, (uint32_t)b, 0u};
     const int64_t stop = from + 64;
     uint64_t mask = 0;
-    int walked = 0;
-    while (end < stop && ++b < bags) {          // bag b starts at `end`
+    while (end < stop && ++b < bags) {          // bag b starts at `end`, which lies behind the start before it: 63 steps at most
         const int64_t next = bag_off[b + 1];
-        if (next <= end || ++walked > kWalk) {
+        if (next <= end) {
             r.flags = BagsOf64::kGaps;
             break;
         }
@@ -241,23 +239,10 @@ struct SumPiece {
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] += o.v[i];
     }
-    // fp64 [.. D] partial rows: the piece of lane c starts at element c * N
-    __device__ __forceinline__ void load(const double* row, int c) {
-        const double2* p = reinterpret_cast<const double2*>(row + (size_t)c * N);
-#pragma unroll
-        for (int i = 0; i < N / 2; ++i) {
-            const double2 t = p[i];
-            v[2 * i] = t.x; v[2 * i + 1] = t.y;
-        }
-    }
-    __device__ __forceinline__ void store(double* row, int c) const {
-        double2* p = reinterpret_cast<double2*>(row + (size_t)c * N);
-#pragma unroll
-        for (int i = 0; i < N / 2; ++i) p[i] = make_double2(v[2 * i], v[2 * i + 1]);
-    }
-    // The same through device-coherent accesses: written through to memory and read from it, past the caches that
-    // the GPU's dies do not share, so that a sum stored by one workgroup can be read by any other without either of
-    // them writing back or dropping everything else its cache holds (what a device-wide fence would cost).
+    // fp64 [.. D] partial rows, the piece of lane c from element c * N on, through device-coherent accesses: written
+    // through to memory and read from it, past the caches that the GPU's dies do not share, so that a sum stored by one
+    // workgroup can be read by any other without either of them writing back or dropping everything else its cache
+    // holds (what a device-wide fence would cost).
     __device__ __forceinline__ void store_device(double* row, int c) const {
         uint64_t* p = reinterpret_cast<uint64_t*>(row + (size_t)c * N);
 #pragma unroll
