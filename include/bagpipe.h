@@ -388,8 +388,8 @@ int bp_embbag_fwd_grouped(const bp_config* cfg, const void* cache_w, const int32
  * tickets    device, at least bp_embbag_bwd_ticket_bytes(n_lookups) bytes of counters (uint32), ALL ZERO when the call
  *            starts its work on `stream`.  The call leaves them all zero again when that work has finished, so one
  *            buffer sized for the largest batch, zeroed once when it is allocated, serves every later call on the
- *            same stream (calls that overlap in time need buffers of their own).  They count, for a row whose
- *            lookups are spread over several workgroups, how many of those have stored their sum.
+ *            same stream (calls that overlap in time need buffers of their own).  They count, for a row that is cut
+ *            into several pieces, how many of those have stored their sum.
  * Limits: n_lookups < 2^31, bags < 2^31.  Slots outside [0, capacity) are ignored.  Asynchronous.
  * ------------------------------------------------------------------------------------------------ */
 int bp_embbag_bwd_update_workspace_bytes(const bp_config* cfg, int64_t n_lookups, int64_t bags, size_t* bytes);
@@ -402,9 +402,11 @@ int bp_embbag_bwd_update(const bp_config* cfg, void* cache_w, void* cache_state,
  * The same backward + update for a batch whose lookups the plan has already grouped by row (bp_plan's
  * optional outputs): no sort and no scan at run time, ONE kernel launch (three when bag_offsets is given).  A row of
  * up to BP_BWD_ROW_MAX lookups is summed and updated by one lane group; every piece of a long row by one workgroup,
- * and a row of several pieces is finished by whichever of its workgroups ends last, which adds the pieces' sums in
- * piece order.  Results are those of bp_embbag_bwd_update up to the order in which a row's gradients enter the
- * fp64 sum; that order is fixed by the records, never by timing.
+ * or by one wavefront where rows are narrow, and a row of several pieces is finished by whichever of those ends last,
+ * which adds the pieces' sums (of more than 64 pieces: in stretches of 64 first).  The order in which a row's gradients
+ * enter the fp64 sum, and their squares the row-wise mean, is fixed by the row's own lookups, the storage type and the
+ * width: never by timing or by the rest of the batch.  With the planner's order of a row's lookups (by position)
+ * results are those of bp_embbag_bwd_update bit for bit; other orders inside a row give other last bits.
  *
  * grouped_lookups     device, the batch's slice [iter_offsets[i], iter_offsets[i+1]) of the plan array
  * row_recs, n_rows    device, the batch's slice [keep_offsets[i], keep_offsets[i+1]) and its length
