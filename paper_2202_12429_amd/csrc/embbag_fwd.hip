@@ -1,9 +1,9 @@
 // bp_embbag_fwd: EmbeddingBag-sum forward over cache slots (the trainer's embedding lookup, Section 2.1,
 // served from the GPU-resident cache of Section 3.2).
-//  - bags of several lookups: one lane group per bag; every lane owns a 16-byte piece of the row, accumulates in
-//    fp32 in lookup order and writes its piece of the pooled row;
-//  - one lookup per bag (a row copy): the output is a flat array of 16-byte pieces, one per lane with no idle
-//    lanes, several pieces per lane in flight; a wavefront's stores are one contiguous kilobyte.
+//  - bags of several lookups: one lane group per bag; every lane owns a piece of the row (16 bytes, or 8 of bf16 rows by
+//    fours), accumulates in fp32 in lookup order and writes its piece of the pooled row;
+//  - one lookup per bag (a row copy): the output is a flat array of 16-byte pieces (bf16 rows go by fours), one per lane with
+//    no idle lanes, several pieces per lane in flight; a wavefront's stores are one contiguous kilobyte.
 // bp_embbag_fwd_grouped: the same row copies walked by the plan's row and piece records instead of a slot per
 // lookup: every distinct row is fetched once and written to the bags that look it up.
 #include <algorithm>

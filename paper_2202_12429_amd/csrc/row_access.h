@@ -152,9 +152,13 @@ int dispatch_row(int lpr, F&& f) {
 // eights a lane.  By fours a lane's fp32 operands (gradients, pooled rows, state) are 16 bytes beside its neighbour's and take
 // half the registers; by eights a lane group is half as wide, and a wavefront has twice the rows in flight.  Forward, us by
 // eights / by fours, one lookup a bag: 1.3 M of dim 128, pooled rows written six batches in turn 187 / 177, always the same
-// 293 / 120; over row records 147 / 135; 30,000 of dim 24: 4.1 / 3.7, 6.7 / 5.9.  Pooling reads more than it writes, and 16 bytes a
-// lane of the row come cheaper than 8: 65,535 bags of 25 in the mean, dim 128: 35 / 51, of 3: 10.6 / 11.4, of 1: 10.2 / 9.0.  Rows
-// wider than 64 lanes by fours are taken by eights.
+// 293 / 120; over row records 147 / 135; 30,000 of dim 24: 4.1 / 3.7, 6.7 / 5.9.  Which is quicker depends on where the buffers
+// lie, by something that their distance does not tell (cache and pooled rows in one allocation, twenty distances of 0 to 300 MB:
+// 185 to 191 / 164 to 166).  In a training step on a cache of 16 M rows, twelve placements: by eights 170 to 171 in ten and 197
+// and 199 in two, by fours 176 to 182; but the backward pass behind it takes 228 to 242 after eights, 216 to 243 after fours,
+// both together 414 / 410 in the mean.  Pooling reads more than it writes, and 16 bytes a lane of the row come cheaper
+// than 8: 65,535 bags of 25 in the mean, dim 128: 35 / 51, of 3: 10.6 / 11.4, of 1: 10.2 / 9.0.  Rows wider than 64 lanes by
+// fours are taken by eights.
 template <bool SPLIT, typename F>
 int dispatch_values(const bp_config* cfg, bool eights, F&& f) {
     const bool bf16 = cfg->weight_dtype == BP_BF16;
