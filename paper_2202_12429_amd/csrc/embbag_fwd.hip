@@ -215,6 +215,11 @@ struct FwdRowsLaunch {
 //     2,688 / 2,673).
 //   short bags take four: at a mean of 6.5 the two are about even, and below it the guards of rows that are not there are
 //     the cost (f32, 32,768 bags of mean 1: dim 64 3.7 / 4.3, dim 256 8.3 / 9.1).
+//   but the shortest bags (a mean of less than 1.75) of bf16 rows by eights that fill a group of 8 lanes or more take eight from
+//     2^20 lanes on: such launches are nearly all pooled stores, and the deeper form holds fewer wavefronts on a CU (dim 64,
+//     262,144 bags of mean 1: 22.5 / 14.7; dim 512, 131,072 of mean 1.5: 76.2 / 50.8, of mean 2: 51.5 / 52.5).  Rows that leave
+//     lanes idle do not gain (dim 96, 262,144 of mean 1: 21.9 / 24.8).
+constexpr int64_t kManyLanes = int64_t(1) << 20;            // twice what the chip holds
 struct FwdLaunch {
     const bp_config* cfg;
     const void* cache_w;
@@ -243,8 +248,8 @@ struct FwdLaunch {
             return BP_OK;
         }
         const dim3 grid((unsigned)ceil_div(count * GW, kRowBlock));
-        const bool long_bags = 2 * n_lookups >= 13 * bags;
-        if (long_bags)
+        const bool long_bags = 2 * n_lookups >= 13 * bags, shortest = 4 * n_lookups < 7 * bags;
+        if (long_bags || (P::BF16 && P::N == 8 && GW >= 8 && lpr == GW && shortest && bags * GW >= kManyLanes))
             BP_LAUNCH(K_FWD, (embbag_fwd_kernel<GW, P, 8>), grid, dim3(kRowBlock), 0, stream, w, slots, bag_off + b0, count, n_lookups,
                       cfg->capacity, lpr, wst, cfg->dim, to);
         else
@@ -253,6 +258,25 @@ struct FwdLaunch {
         return BP_OK;
     }
 };
+
+// bf16 rows of bags of several lookups: by fours a lane or by eights (row_access.h)?  By fours while the launch is no more than
+// the chip holds at once, where latency rules and half the registers and whole lines of pooled rows help.  Larger launches read
+// rows at the rate of their requests, which by fours are twice as many, the more the longer the bags and the more lanes idle:
+// they stay by fours only where nearly all they do is write pooled rows, up to a limit on lanes * mean^2 that grows with the
+// rows that fill their group.  us by eights (in the depth they take) / by fours, bags of a Poisson length, three outputs in turn:
+//   dim 64: 32,768 bags of mean 1 4.3 / 3.9, 262,144 14.7 / 14.7; 524,288 of mean 2 30.0 / 39.1
+//   dim 128: 65,536 of mean 1 9.1 / 7.5; 131,072 of mean 2 15.7 / 18.5, 524,288 52.5 / 66.9     dim 256: 32,768 of mean 1 9.0 / 7.1
+//   dim 24: 1,048,576 of mean 1 25.1 / 33.7     dim 96: 16,384 of mean 1 3.9 / 3.7, 262,144 21.9 / 29.7
+bool pooled_by_eights(int dim, int64_t n, int64_t bags) {
+    constexpr double kChipLanes = 1 << 19;
+    const int lanes = dim / 4, group = group_width(lanes);
+    const double all = (double)group * (double)bags;
+    if (2 * n >= 5 * bags) return true;
+    if (lanes <= 2 || all <= kChipLanes) return false;
+    const bool full = lanes == group;
+    const double mean = std::max((double)n / (double)bags, full ? 0.0 : 0.7);
+    return all * mean * mean > (full && lanes >= 32 ? 8 << 20 : full && lanes >= 16 ? 4 << 20 : 1 << 20);
+}
 
 }  // namespace
 }  // namespace bp
@@ -270,7 +294,7 @@ BP_EXPORT int bp_embbag_fwd(const bp_config* cfg, const void* cache_w, const int
     if (!cache_w || !out || (n_lookups && !lookup_slots)) return fail(BP_ERR_INVALID_ARG, "NULL pointer");
     if (((uintptr_t)cache_w | (uintptr_t)out) & 15) return fail(BP_ERR_INVALID_ARG, "cache_w and out must be 16-byte aligned");
     FwdLaunch l{cfg, cache_w, lookup_slots, bag_offsets, bags, n_lookups, out, (hipStream_t)stream};
-    return dispatch_values<false>(cfg, bag_offsets && 2 * n_lookups >= 5 * bags, l);      // pooling by eights from a mean of 2.5
+    return dispatch_values<false>(cfg, bag_offsets && pooled_by_eights(cfg->dim, n_lookups, bags), l);
 }
 
 BP_EXPORT int bp_embbag_fwd_grouped(const bp_config* cfg, const void* cache_w, const int32_t* grouped_lookups,

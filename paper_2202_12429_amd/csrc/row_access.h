@@ -157,8 +157,8 @@ int dispatch_row(int lpr, F&& f) {
 // 185 to 191 / 164 to 166).  In a training step on a cache of 16 M rows, twelve placements: by eights 170 to 171 in ten and 197
 // and 199 in two, by fours 176 to 182; but the backward pass behind it takes 228 to 242 after eights, 216 to 243 after fours,
 // both together 414 / 410 in the mean.  Pooling reads more than it writes, and 16 bytes a lane of the row come cheaper
-// than 8: 65,535 bags of 25 in the mean, dim 128: 35 / 51, of 3: 10.6 / 11.4, of 1: 10.2 / 9.0.  Rows wider than 64 lanes by
-// fours are taken by eights.
+// than 8: 65,535 bags of 25 in the mean, dim 128: 35 / 51 (pooled_by_eights has the rule).  Rows wider than 64 lanes by fours
+// are taken by eights.
 template <bool SPLIT, typename F>
 int dispatch_values(const bp_config* cfg, bool eights, F&& f) {
     const bool bf16 = cfg->weight_dtype == BP_BF16;

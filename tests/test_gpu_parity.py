@@ -129,6 +129,35 @@ def test_forward_bags_in_every_form(bp, D, dtype, bags, longest):
     assert np.array_equal(out.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("D,bags,mean", [
+    # bf16 rows pooled by fours up to 2^19 lanes, then by the lanes and the mean; by eights in bursts of eight from 2^20 lanes on
+    (64, 32768, 2.0), (64, 32800, 2.0), (64, 262000, 1.0), (64, 262500, 1.0), (64, 262500, 1.8), (128, 262000, 1.0), (128, 262500, 1.0),
+    (256, 40000, 1.8), (24, 65536, 2.0), (24, 65600, 2.0), (24, 131200, 1.0), (32, 65600, 2.0), (8, 600000, 2.0), (512, 16384, 1.5),
+    (512, 16300, 1.5), (512, 16384, 2.0), (96, 300000, 0.3)])
+def test_forward_short_bags_in_every_form(bp, D, bags, mean):
+    """Short bags of bf16 rows on both sides of every line where their form changes, bags of 0, 1, 2, ... lookups: fp32 sums in
+    lookup order bit for bit."""
+    say(f"forward short bags D={D} {bags} bags of {mean}")
+    C = 3000
+    rng = np.random.default_rng(D + bags)
+    lens = rng.poisson(mean, size=bags)
+    lens[0] += max(0, int(np.ceil(mean * bags)) - lens.sum())            # the mean is what it says, at least
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    w = random_cache(C, D, "bf16", D).cuda()
+    slots = torch.from_numpy(rng.integers(0, C, size=int(off[-1])).astype(np.int32)).cuda()
+    out = torch.full((bags, D), 3.0, device="cuda")
+    bp.bp_embbag_fwd(bp.make_config(C, C, D, "bf16"), w, slots, dev(off), bags, out)
+    rows, want, first = w.float(), torch.zeros((bags, D), device="cuda"), dev(off[:-1])
+    short = lens.copy()
+    short[0] = 0                                                         # the first bag may be long: by itself below
+    for j in range(int(short.max())):
+        has = torch.from_numpy(np.flatnonzero(short > j)).cuda()
+        want[has] += rows[slots[first[has] + j].long()]
+    for s in slots[:lens[0]].long().tolist():
+        want[0] += rows[s]
+    assert torch.equal(out, want)
+
+
 def test_forward_more_lanes_than_a_launch_takes(bp):
     """Bags enough that 64 lanes each are more than the 2^32 threads of one launch (68 GB of pooled rows of dim 256): row
     copies, compared with torch's on the GPU stretch by stretch, the same bits."""
