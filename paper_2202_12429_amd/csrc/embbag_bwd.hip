@@ -12,8 +12,8 @@
 //   piece records  a row with more lookups is cut into pieces of BP_BWD_PIECE lookups; one workgroup (narrow rows: one
 //                  wavefront) takes a piece, its lane groups add their shares and meet.  A one-piece row is updated
 //                  at once.  For a row of several pieces the piece's sum is stored, and whoever finds, by a counter,
-//                  that all the others have stored theirs adds the sums and updates the row (of more than 64 pieces: in
-//                  stretches of 64 first).
+//                  that all the others have stored theirs adds the sums and updates the row (of very many pieces: in
+//                  stretches first).
 // ONE launch does all of it: workgroups [0, piece_blocks) take pieces, the rest take rows.
 // Every order of addition is fixed by the row's own records and its type and width, never by timing or by the rest of the batch:
 // results are bit-identical run to run, and from one entry point to the other.
@@ -354,9 +354,9 @@ __device__ __forceinline__ void finish_update(const UpdateParams& u, typename P:
 }
 
 // Adds the gradient rows of the grouped lookups [p0, p1) into acc: bursts of four rows, the indices of the next
-// burst loaded while the rows of this one arrive.  idx holds the bag numbers of the first four lookups, and afterwards those
-// of the first four of [q0, q1) unless [p0, p1) is empty.
-template <typename P, int N>
+// burst loaded while the rows of this one arrive.  idx holds the bag numbers of the first four lookups; FOLLOWED: and afterwards
+// those of the first four of [q0, q1), unless [p0, p1) is empty.
+template <bool FOLLOWED, typename P, int N>
 __device__ __forceinline__ void add_gradient_rows(SumPiece<N>& acc, uint32_t (&idx)[4], uint32_t p0, uint32_t p1, uint32_t q0,
                                                   uint32_t q1, const uint32_t* __restrict__ bag_of,
                                                   const float* __restrict__ grad, const UpdateParams& u, int c) {
@@ -365,7 +365,7 @@ __device__ __forceinline__ void add_gradient_rows(SumPiece<N>& acc, uint32_t (&i
 #pragma unroll
         for (int j = 0; j < 4; ++j)     // the bag number is clamped where it is used: its load stays in flight until then
             if (p + j < p1) t[j].load_f32(grad + (size_t)min(idx[j], u.bags - 1u) * u.dim, c, u.lpr);
-        const bool more = p + 4 < p1;
+        const bool more = !FOLLOWED || p + 4 < p1;
         const uint32_t next = more ? p + 4 : q0, end = more ? p1 : q1;
 #pragma unroll
         for (int j = 0; j < 4; ++j) idx[j] = next + j < end ? bag_of[next + j] : 0u;
@@ -382,32 +382,34 @@ __device__ __forceinline__ void add_gradient_rows(SumPiece<N>& acc, uint32_t (&i
 template <int GW>
 constexpr bool kWavePieces = GW <= 4;
 // A workgroup of 256 threads, or one of sixteen lane groups, where a group's share of a piece is sixteen lookups at most: four
-// bursts one behind the other where 64-lane rows have sixteen in 256 threads (BwdLaunch has the rule).
-template <int GW>
-constexpr int kBwdWideBlock = GW <= 16 ? 256 : 16 * GW;
+// bursts one behind the other where 64-lane rows have sixteen in 256 threads (BwdLaunch has the rule).  Eight groups for the
+// widest bf16 rows, which have no form by fours: four shares a group of 256 threads would wait in 32 KB of LDS, one workgroup
+// a CU less (58,000 rows of dim 512: 49.2 us, 43.6 with two shares).
+template <int GW, typename P>
+constexpr int kBwdWideBlock = GW <= 16 ? 256 : P::N == 8 && GW == 64 ? 512 : 16 * GW;
 template <int GW, int BLOCK>
 constexpr int kPieceThreads = kWavePieces<GW> ? kWave : BLOCK;
 
-// The order of a piece's sum, the same in every form of the kernel for a type and a width: kShares shares, as many as the
-// form with the most lane groups has, of lookups one behind the other, are each summed in lookup order; share i then meets
-// share i + kShares/2, these sums meet in the same way, and so on.  A form with fewer lane groups gives group j the shares j,
-// j + groups, ..., which meet there.  (The pieces' sums of a row of several are shared out one by one and meet
-// alike.)  So neither the entry point nor what else is in the batch changes a row's result.
+// The order of a piece's sum, the same in every form of the kernel for a type and a width: kShares shares of lookups one behind
+// the other are each summed in lookup order; share i then meets share i + kShares/2, these sums meet in the same way, and so
+// on.  A form with fewer lane groups gives group j the shares j, j + groups, ..., which meet there; one with more leaves groups
+// without a share.  (The pieces' sums of a row of several are shared out one by one and meet alike.)  So neither the entry
+// point nor what else is in the batch changes a row's result.  As many shares as the form by fours has lane groups at most: it
+// serves the small launches, which wait for their pieces.  With as many as the form by eights, a second share a group cost them 5
+// to 10 % (bf16 rows of dim 16, 2,000 lookups: 4.30 / 4.57 us), and the form by eights gains nothing by them.
 constexpr int piece_groups(int gw) { return gw <= 4 ? kWave / gw : gw <= 16 ? 256 / gw : 16; }      // of the form with the most
 template <int GW, typename P>
-constexpr int kShares = !P::BF16   ? piece_groups(GW)
-                        : P::N == 8 ? std::max(piece_groups(GW), piece_groups(2 * GW))
-                                    : std::max(piece_groups(GW), piece_groups(GW > 1 ? GW / 2 : 1));
+constexpr int kShares = P::N == 4 ? piece_groups(GW) : GW == 64 ? 8 : piece_groups(2 * GW);
 // Places of a thread in LDS, N doubles each, for the sums below.
 template <int S, int PG, bool WAVE>
 constexpr int kHeldSums = S == 4 * PG ? 2 : S == 2 * PG || !WAVE ? 1 : 0;
-// The sum of the shares of lane group j, in their order: one(acc, share, next) adds up one of them and is told which one
-// follows (S: none).
+// The sum of the shares of lane group j, in their order: one(acc, share, next) adds up one of them (from S on there is nothing
+// to add) and is told which one follows (S: none).  Shares of `per` of `count`: those from count / per on are empty, and without a second one nothing waits.
 // Sums that wait for others do so in the thread's places in LDS: the kernel has no registers for them.
 template <int S, int PG, int N, int R, typename One>
-__device__ __forceinline__ SumPiece<N> sum_shares(uint32_t j, double (*held)[R], One&& one) {
-    constexpr int M = S / PG;
-    static_assert(S % PG == 0 && (M == 1 || M == 2 || M == 4), "every group has as many, which meet in pairs");
+__device__ __forceinline__ SumPiece<N> sum_shares(uint32_t j, uint32_t count, uint32_t per, double (*held)[R], One&& one) {
+    constexpr int M = S > PG ? S / PG : 1;
+    static_assert((S % PG == 0 || PG % S == 0) && (M == 1 || M == 2 || M == 4), "every group has as many, which meet in pairs");
     const auto put = [&](const SumPiece<N>& acc, int place) {
 #pragma unroll
         for (int i = 0; i < N; ++i) held[place * N + i][threadIdx.x] = acc.v[i];
@@ -417,24 +419,34 @@ __device__ __forceinline__ SumPiece<N> sum_shares(uint32_t j, double (*held)[R],
         for (int i = 0; i < N; ++i) acc.v[i] += held[place * N + i][threadIdx.x];
     };
     SumPiece<N> acc;
-#pragma unroll 1
-    for (int t = 0; t < M; ++t) {
+    if constexpr (M == 1) {
         acc.zero();
-        one(acc, j + t * PG, t + 1 < M ? j + (t + 1) * PG : (uint32_t)S);
-        if constexpr (M > 1) {
-            if (t >= M / 2) meet(acc, t - M / 2);              // two: 0 and 1; four: 0 and 2, 1 and 3
-            if (t + 1 < M) put(acc, M == 4 ? t % 2 : 0);
+        one(acc, j, (uint32_t)S);
+    } else {
+        int turns = 1;                                              // the same in every lane
+#pragma unroll
+        for (int t = 1; t < M; ++t) turns += count > t * PG * per;
+#pragma unroll 1
+        for (int t = 0;; ++t) {
+            acc.zero();
+            one(acc, j + t * PG, t + 1 < M ? j + (t + 1) * PG : (uint32_t)S);
+            if (M == 4 && t >= 2) meet(acc, t - 2);                 // of four: 0 and 2, 1 and 3
+            if (t + 1 >= turns) break;
+            put(acc, M == 4 ? t % 2 : 0);
         }
+        if (M == 4 && turns == 3) meet(acc, 1);
+        else if (turns > 1) meet(acc, 0);
     }
-    if constexpr (M == 4) meet(acc, 0);
     return acc;
 }
-// Sum over the lane groups that took a piece.  The whole sum is in the first group.  By workgroup: the upper half of the
-// wavefronts leaves its sums in LDS, in the threads' own places, for the lower half; the last four meet in one step, and the first
-// goes on by lane shuffles.  The places may be used again after the call.
+// Sum over the lane groups that took a piece.  The whole sum is in the first group.  By workgroup: the wavefronts behind the
+// first four leave their sums in LDS, in the threads' own places, for those, then three of the four for the first, which goes on
+// by lane shuffles.  The places may be used again after the call.
 template <int GW, int BLOCK, int N, int R>
 __device__ __forceinline__ void piece_sum(SumPiece<N>& acc, double (*held)[R]) {
     if constexpr (!kWavePieces<GW>) {
+        constexpr uint32_t FOUR = 4 * kWave;
+        static_assert(BLOCK == FOUR || BLOCK == 2 * FOUR || BLOCK == 4 * FOUR, "halves of halves");
         const uint32_t tid = threadIdx.x;
         const auto leave = [&](uint32_t from, uint32_t to) {
             if (tid >= from && tid < to) {
@@ -443,20 +455,24 @@ __device__ __forceinline__ void piece_sum(SumPiece<N>& acc, double (*held)[R]) {
             }
             __syncthreads();
         };
-#pragma unroll
-        for (uint32_t half = BLOCK / 2; half > 2 * kWave; half /= 2) {
-            leave(half, 2 * half);
-            if (tid < half) {
-#pragma unroll
-                for (int i = 0; i < N; ++i) acc.v[i] += held[i][tid + half];
-            }
-        }
-        leave(kWave, 4 * kWave);
-        if (tid < kWave) {
+        const auto meet_four = [&](uint32_t step) {            // this one and those step, 2 * step and 3 * step on
 #pragma unroll
             for (int i = 0; i < N; ++i)
-                acc.v[i] = (acc.v[i] + held[i][tid + 2 * kWave]) + (held[i][tid + kWave] + held[i][tid + 3 * kWave]);
+                acc.v[i] = (acc.v[i] + held[i][tid + 2 * step]) + (held[i][tid + step] + held[i][tid + 3 * step]);
+        };
+        if constexpr (BLOCK > FOUR) {
+            leave(FOUR, BLOCK);
+            if (tid < FOUR) {
+                if constexpr (BLOCK == 4 * FOUR) {
+                    meet_four(FOUR);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < N; ++i) acc.v[i] += held[i][tid + FOUR];
+                }
+            }
         }
+        leave(kWave, FOUR);
+        if (tid < kWave) meet_four(kWave);
         __syncthreads();
     }
 #pragma unroll
@@ -517,7 +533,7 @@ __global__ __launch_bounds__(BLOCK, P::N == 8 ? 4 : 8) void bwd_rows_kernel(cons
                 const uint32_t start = rec[r].x & kPosMask, count = rec[r].y;
                 SumPiece<N> acc;
                 acc.zero();
-                if (active) add_gradient_rows<P, N>(acc, idx[r], start, start + count, 0, 0, bag_of, grad, u, c);
+                if (active) add_gradient_rows<false, P, N>(acc, idx[r], start, start + count, 0, 0, bag_of, grad, u, c);
                 finish_update<GW, P>(u, cache_w, cache_s, (int64_t)rec[r].z, c, row[r], acc.template rounded<P>(), active);
             }
         }
@@ -546,9 +562,10 @@ __global__ __launch_bounds__(BLOCK, P::N == 8 ? 4 : 8) void bwd_rows_kernel(cons
         uint32_t idx[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) idx[k] = share_at(pj) + k < share_at(pj + 1) ? bag_of[share_at(pj) + k] : 0u;
-        SumPiece<N> acc = sum_shares<S, PG, N>((uint32_t)pj, held, [&](SumPiece<N>& sum, uint32_t share, uint32_t next) {
+        SumPiece<N> acc = sum_shares<S, PG, N>((uint32_t)pj, count, per, held, [&](SumPiece<N>& sum, uint32_t share, uint32_t next) {
             if (active)
-                add_gradient_rows<P, N>(sum, idx, share_at(share), share_at(share + 1), share_at(next), share_at(next + 1), bag_of, grad, u, c);
+                add_gradient_rows<(S > PG), P, N>(sum, idx, share_at(share), share_at(share + 1), share_at(next), share_at(next + 1),
+                                                 bag_of, grad, u, c);
         });
         piece_sum<GW, BLOCK, N>(acc, held);
         if (direct) {      // the row is asked for only now: one more round trip after a few hundred gradient rows
@@ -560,12 +577,15 @@ __global__ __launch_bounds__(BLOCK, P::N == 8 ? 4 : 8) void bwd_rows_kernel(cons
         }
         // One of several pieces: leave the sum where whoever takes the last piece will find it, then take a ticket
         // (device-coherent stores, complete before this piece is counted; whoever counts the last piece then reads
-        // all the sums with device-coherent loads).  The pieces of a row of more than kMeet meet in stretches of kMeet first,
+        // all the sums with device-coherent loads).  The pieces of a row of very many meet in stretches of kStretch first,
         // and then the stretches: whoever takes the row's last piece would read the sums of thousands one burst behind the other,
         // most of all a wavefront of four-lane rows, with sixteen lane groups (a row's 4.2 M lookups, dim 16: 392 us in one
-        // step, 63 in two; dim 64 698 / 313; 262,144 lookups, dim 16: 30.0 / 11.8).
-        constexpr uint32_t kMeet = 64;
-        uint32_t mine = index, step = 1, first = index / kMeet * kMeet, members = min(kMeet, pieces - first);
+        // step, 63 in two; dim 64 698 / 313; 262,144 lookups, dim 16: 30.0 / 11.8).  The second step costs 1.2 us: up to five bursts
+        // a share there is one (200,000 lookups, the hottest row's 66 pieces, dim 16: 11.5 in one step, 12.6 in two).
+        constexpr uint32_t kStretch = 64, kAtOnce = 10 * S;
+        const bool at_once = pieces <= kAtOnce;
+        uint32_t mine = index, step = 1, first = at_once ? 0u : index / kStretch * kStretch;
+        uint32_t members = at_once ? pieces : min(kStretch, pieces - first);
         uint32_t* ticket = tickets + pbase + first;
         bool last;
 #pragma unroll 1
@@ -589,8 +609,8 @@ __global__ __launch_bounds__(BLOCK, P::N == 8 ? 4 : 8) void bwd_rows_kernel(cons
                 __syncthreads();                           // everybody has read it before a later sum rewrites it
             }
             if (!last) break;
-            acc = sum_shares<S, PG, N>((uint32_t)pj, held, [&](SumPiece<N>& sum, uint32_t share, uint32_t) {
-                for (uint32_t b = share; b < members; b += 2 * S) {
+            acc = sum_shares<S, PG, N>((uint32_t)pj, members, 1, held, [&](SumPiece<N>& sum, uint32_t share, uint32_t) {
+                for (uint32_t b = share; b < members && (PG <= S || share < S); b += 2 * S) {
                     SumPiece<N> t[2];
 #pragma unroll
                     for (int k = 0; k < 2; ++k) {
@@ -605,11 +625,11 @@ __global__ __launch_bounds__(BLOCK, P::N == 8 ? 4 : 8) void bwd_rows_kernel(cons
             piece_sum<GW, BLOCK, N>(acc, held);
             if (threadIdx.x % kPieceThreads<GW, BLOCK> == 0)      // the counter is zero again for the next call
                 __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (step > 1 || pieces <= kMeet) break;
+            if (step > 1 || at_once) break;
             mine = first;                                         // the stretches, each in the place of its first piece
-            step = kMeet;
+            step = kStretch;
             first = 0;
-            members = (pieces + kMeet - 1) / kMeet;
+            members = (pieces + kStretch - 1) / kStretch;
             ticket = tickets + pbase + 1;                         // counts no stretch
         }
         if (!last) continue;
@@ -778,9 +798,8 @@ BwdWorkspace carve_bwd(void* base, size_t cap, int64_t n, int dim) {
 //     (20,000 lookups, dim 64: 8.5 by fours, 11.5 by eights; without pieces 5.6, 5.2); a larger one has the more bytes in flight
 //     by eights (200,000, dim 128: 48.2 / 33.2 by fours, 42.9 / 33.5 by eights; 1.3 M: 276 / 206, 258 / 204).
 //   256 threads or sixteen lane groups, for rows of 32 and 64 lanes: the wide workgroup has a piece done sooner, which small
-//     launches wait for (fp32, dim 256, row-wise Adagrad, 20,000 lookups: 18.5 / 19.5 with 256 threads, 12.9 / 14.1 wide); large ones
-//     lose, whose rows hold a workgroup's place until its last one ends (200,000: 92 / 70, 99 / 77).  32-lane rows that leave
-//     lanes idle do not gain (dim 100, 20,000: 13.3, 13.4 either way).
+//     launches wait for (fp32, dim 256, row-wise Adagrad, 20,000 lookups, skewed: 18.2 with 256 threads, 11.8 wide); large ones
+//     lose, whose rows hold a workgroup's place until its last one ends (200,000: 65.8, 70.3).
 struct BwdLaunch {
     const bp_config* cfg;
     ReduceScratch red;
@@ -799,9 +818,9 @@ struct BwdLaunch {
     int launch() { return dispatch_values<true>(cfg, n_pieces == 0 || chips(group_width(cfg->dim / 4)) > 1, *this); }
     template <int GW, typename P>
     int run(int lpr) {
-        if constexpr (kBwdWideBlock<GW> != 256) {
+        if constexpr (kBwdWideBlock<GW, P> != 256) {
             const bool wide = n_pieces > 0 && chips(GW) <= 4 && (GW == 64 || lpr == GW);
-            if (wide) return run_block<GW, P, kBwdWideBlock<GW>>(lpr);
+            if (wide) return run_block<GW, P, kBwdWideBlock<GW, P>>(lpr);
         }
         return run_block<GW, P, 256>(lpr);
     }
