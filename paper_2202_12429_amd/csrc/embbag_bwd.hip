@@ -799,7 +799,9 @@ BwdWorkspace carve_bwd(void* base, size_t cap, int64_t n, int dim) {
 //     by eights (200,000, dim 128: 48.2 / 33.2 by fours, 42.9 / 33.5 by eights; 1.3 M: 276 / 206, 258 / 204).
 //   256 threads or sixteen lane groups, for rows of 32 and 64 lanes: the wide workgroup has a piece done sooner, which small
 //     launches wait for (fp32, dim 256, row-wise Adagrad, 20,000 lookups, skewed: 18.2 with 256 threads, 11.8 wide); large ones
-//     lose, whose rows hold a workgroup's place until its last one ends (200,000: 65.8, 70.3).
+//     lose, whose rows hold a workgroup's place until its last one ends (200,000: 65.8, 70.3).  Rows that leave lanes idle gain
+//     in launches that the chip holds at once (dim 100, 20,000 skewed: 11.1, 9.2; bf16 dim 192, 200,000: 42.2, 45.3), and so few
+//     pieces that they are likely short are not worth it (30,000 lookups of 18,000 rows, one piece, dim 256: 14.4, 15.4).
 struct BwdLaunch {
     const bp_config* cfg;
     ReduceScratch red;
@@ -815,11 +817,12 @@ struct BwdLaunch {
     hipStream_t stream;
     int64_t bags;
     int64_t chips(int lanes) const { return ceil_div((int64_t)n_rows * lanes, int64_t(256) * 2048); }      // that the rows fill
+    bool long_rows() const { return (int64_t)n_pieces * 4096 >= (int64_t)n_rows; }
     int launch() { return dispatch_values<true>(cfg, n_pieces == 0 || chips(group_width(cfg->dim / 4)) > 1, *this); }
     template <int GW, typename P>
     int run(int lpr) {
         if constexpr (kBwdWideBlock<GW, P> != 256) {
-            const bool wide = n_pieces > 0 && chips(GW) <= 4 && (GW == 64 || lpr == GW);
+            const bool wide = long_rows() && chips(GW) <= (lpr == GW ? 4 : 1);
             if (wide) return run_block<GW, P, kBwdWideBlock<GW, P>>(lpr);
         }
         return run_block<GW, P, 256>(lpr);
