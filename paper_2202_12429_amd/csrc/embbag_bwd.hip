@@ -791,12 +791,12 @@ BwdWorkspace carve_bwd(void* base, size_t cap, int64_t n, int dim) {
     return w;
 }
 
-// Two choices that change no bit of the result (kShares above), us of the kernel on tables of hundreds of MB, ids uniform / skewed
-// (of 200,000 lookups 181,000 / 86,000 rows distinct).  bp_embbag_bwd_update knows no counts when it launches, only bounds, and so
+// Two choices that change no bit of the result (kShares above), us of the kernel on caches of hundreds of MB, ids uniform / skewed
+// (of 200,000 lookups 181,000 / 53,000 rows distinct).  bp_embbag_bwd_update knows no counts when it launches, only bounds, and so
 // takes the forms for batches with long rows and as many rows as lookups:
 //   bf16 rows by fours or by eights a lane (dispatch_values).  By fours pieces are quicker in a launch that the chip holds at once
-//     (20,000 lookups, dim 64: 8.5 by fours, 11.5 by eights; without pieces 5.6, 5.2); a larger one has the more bytes in flight
-//     by eights (200,000, dim 128: 48.2 / 33.2 by fours, 42.9 / 33.5 by eights; 1.3 M: 276 / 206, 258 / 204).
+//     (20,000 lookups, dim 64: 3.8 / 6.6 by fours, 3.7 / 8.1 by eights); a larger one has the more bytes in flight by eights
+//     (200,000, dim 128, row-wise Adagrad: 50 / 29.5 by fours, 44 / 27.8 by eights; 1.3 M: 249 / 178, 235 / 177).
 //   256 threads or sixteen lane groups, for rows of 32 and 64 lanes: the wide workgroup has a piece done sooner, which small
 //     launches wait for (fp32, dim 256, row-wise Adagrad, 20,000 lookups, skewed: 18.2 with 256 threads, 11.8 wide); large ones
 //     lose, whose rows hold a workgroup's place until its last one ends (200,000: 65.8, 70.3).  Rows that leave lanes idle gain
