@@ -404,8 +404,9 @@ constexpr int kShares = P::N == 4 ? piece_groups(GW) : GW == 64 ? 8 : piece_grou
 template <int S, int PG, bool WAVE>
 constexpr int kHeldSums = S == 4 * PG ? 2 : S == 2 * PG || !WAVE ? 1 : 0;
 // The sum of the shares of lane group j, in their order: one(acc, share, next) adds up one of them (from S on there is nothing
-// to add) and is told which one follows (S: none).  Shares of `per` of `count`: those from count / per on are empty, and without a second one nothing waits.
-// Sums that wait for others do so in the thread's places in LDS: the kernel has no registers for them.
+// to add) and is told which one follows (S: none).  Shares are of `per` of `count`: those from count / per on are empty, and
+// where a group's second is, nothing waits.  Sums that wait for others do so in the thread's places in LDS: the kernel has no
+// registers for them.
 template <int S, int PG, int N, int R, typename One>
 __device__ __forceinline__ SumPiece<N> sum_shares(uint32_t j, uint32_t count, uint32_t per, double (*held)[R], One&& one) {
     constexpr int M = S > PG ? S / PG : 1;
