@@ -311,5 +311,9 @@ BP_EXPORT int bp_embbag_fwd_grouped(const bp_config* cfg, const void* cache_w, c
         return fail(BP_ERR_INVALID_ARG, "cache_w, out, row_recs and piece_recs must be 16-byte aligned");
     FwdRowsLaunch l{cfg, cache_w, reinterpret_cast<const uint32_t*>(grouped_lookups), reinterpret_cast<const uint4*>(row_recs),
                     reinterpret_cast<const uint4*>(piece_recs), n_rows, n_pieces, bags, out, (hipStream_t)stream};
-    return dispatch_values<false>(cfg, false, l);
+    // bf16 rows of 33 to 64 lanes by fours leave a workgroup four lane groups, which write a piece's bags 64 one behind the other:
+    // small launches with pieces wait for that, where eight groups by eights write 32 (dim 160, 4,000 lookups, 19 pieces 6.2 us by
+    // fours, 4.5 by eights, 16,000 7.5 / 6.9, 30,000 8.3 / 9.3; dim 256 4,000 6.4 / 6.2, 8,000 7.3 / 7.5; without pieces 3.0 / 3.1).
+    const int lanes = cfg->dim / 4;
+    return dispatch_values<false>(cfg, lanes > 32 && n_pieces > 0 && bags * lanes <= 700'000, l);
 }

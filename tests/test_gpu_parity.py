@@ -248,6 +248,24 @@ def test_forward_grouped(bp, D, dtype, pad):
     assert np.array_equal(got, ref.cpu().numpy())
 
 
+@pytest.mark.parametrize("D", [128, 136, 160, 192, 256])
+@pytest.mark.parametrize("lanes", [20_000, 700_000, 701_000])
+def test_forward_grouped_wide_rows_in_small_launches(bp, D, lanes):
+    """bf16 rows of more than 32 lanes by fours on both sides of the size up to which they go by eights, with pieces and without:
+    what bp_embbag_fwd writes, bit for bit."""
+    C, bags = 3000, lanes * 4 // D
+    say(f"forward over row records D={D} bf16 {bags} bags")
+    rng = np.random.default_rng(D + lanes)
+    w = random_cache(C, D, "bf16", D).cuda()
+    cfg = bp.make_config(10 * C, C, D, "bf16")
+    for slots in (np.minimum(rng.zipf(1.25, size=bags) - 1, C - 1).astype(np.int32), (np.arange(bags) % max(C, bags // 8 + 1) % C).astype(np.int32)):
+        gl, rows, pieces = one_hot_grouping(slots, C)
+        out, ref = torch.full((bags, D), float("nan"), device="cuda"), torch.full((bags, D), float("nan"), device="cuda")
+        bp.bp_embbag_fwd_grouped(cfg, w, dev(gl), dev(rows), dev(pieces) if len(pieces) else None, bags, out)
+        bp.bp_embbag_fwd(cfg, w, dev(slots), None, bags, ref)
+        assert torch.equal(out, ref) and torch.equal(ref, w.float()[dev(slots).long()])
+
+
 def test_forward_grouped_edge_cases(bp):
     say("forward over row records: edge cases")
     C, D, bags = 64, 16, 40
